@@ -413,14 +413,16 @@ fov_status plan_forward(const FrameDesc* frames, int nf, int in_dtype, int out_d
     const int r_cap = cs.r_cap;
     const int tile = (cs.bmax + (1 << L) - 1) >> L;
     const int sr = cfg.strip_rows;
-    size_t lds = forward_lds_bytes(in_dtype, r_cap, tile, tile, sr);
+    size_t lds = forward_lds_bytes(in_dtype, out_dtype, r_cap, tile, tile, sr);
     // vertical pairs at the cap need tiles twice as tall; by default only when the CU holds as
     // many workgroups with them
-    bool merge = cfg.merge != 0 && L == 0 && r_cap > 0;
+    const bool fixed = forward_fixed(in_dtype, out_dtype, r_cap);
+    bool merge = (fixed ? cfg.merge > 0 : cfg.merge != 0) && L == 0 && r_cap > 0;
     if (merge) {
-        const size_t lds2 = forward_lds_bytes(in_dtype, r_cap, tile, 2 * tile, sr);
+        const size_t lds2 = forward_lds_bytes(in_dtype, out_dtype, r_cap, tile, 2 * tile, sr);
         if (lds2 + 64 > dev->lds_limit ||
-            (cfg.merge < 0 && forward_occupancy(in_dtype, out_dtype, lds2) < forward_occupancy(in_dtype, out_dtype, lds)))
+            (cfg.merge < 0 && forward_occupancy(in_dtype, out_dtype, r_cap, lds2) <
+                                  forward_occupancy(in_dtype, out_dtype, r_cap, lds)))
             merge = false;
         else
             lds = lds2;
@@ -450,7 +452,7 @@ fov_status plan_forward(const FrameDesc* frames, int nf, int in_dtype, int out_d
     a.wstride = round_up(2 * r_cap + 1, 16);
     // Fragments of radius <= 2/3 of r_cap become one work item per channel (the latency-bound
     // items at the end of the queue then run their channels side by side).
-    const bool chan = cfg.chan_split != 0 && L == 0 && cs.c > 1 && cs.c <= 16 && a.nfrag < (1 << kChanShift);
+    const bool chan = (fixed ? cfg.chan_split > 0 : cfg.chan_split != 0) && L == 0 && cs.c > 1 && cs.c <= 16 && a.nfrag < (1 << kChanShift);
     const int cs_rmax = chan ? (2 * r_cap) / 3 : -1;
     a.cs_rmax = cs_rmax;
     a.cmax = cs.c;

@@ -65,20 +65,6 @@ __device__ __forceinline__ double fragment_sigma(const FrameParams& fp, int lb, 
     return fp.sigma_map ? clip_map_sigma((double)as_global(fp.sigma_map)[lb], fp.cap) : fragment_sigma_ramp(fp, bx, by);
 }
 
-// Fragment gid of the launch, its frame read from the kernel arguments (ARGS: launches of up to
-// kArgFrames frames) or from the device table.
-template <bool ARGS>
-__device__ __forceinline__ Frag frag_of(const FwdLaunch& a, const FrameDesc* __restrict__ table,
-                                        const int32_t* __restrict__ prefix, int gid) {
-    if constexpr (ARGS) {
-        int f = 0;
-        while (f + 1 < a.nframes && gid >= a.kprefix[f + 1]) ++f;
-        return describe_at(&a.fr[f], a.kprefix[f], gid);
-    } else {
-        return describe(table, prefix, a.nframes, gid);
-    }
-}
-
 // The fragment's taps in LDS: V copies (V = 16 / sizeof(T)), copy k holding tap i at element
 // k * stride + kAdjWeightLead + k + i (stride a multiple of 4) with zeros around, so that a run of
 // taps starting at any tap t >= -kAdjWeightLead + 1 starts on a 16-byte boundary in one of them and
@@ -111,7 +97,7 @@ __global__ __launch_bounds__(kThreads) void fov_adj_window_kernel(const FwdLaunc
                                            // rows, columns kPadA..
     __shared__ double part_of_wave[kThreads / 64];
     const int gid = blockIdx.x / csplit, share = blockIdx.x - gid * csplit;
-    const Frag F = frag_of<ARGS>(a, table, prefix, gid);
+    const Frag F = frag_of<ARGS>(a, table, prefix, a.nframes, gid);
     const FrameDesc& d = *F.fd;
     const int per = (s.cmax + csplit - 1) / csplit;
     const int c_begin = share * per, c_end = min(d.c, c_begin + per);
@@ -365,7 +351,7 @@ __global__ __launch_bounds__(kThreads) void fov_adj_sum_kernel(const FwdLaunch a
                                                                const int32_t* __restrict__ radius,
                                                                const T* __restrict__ scratch) {
     const int gid = blockIdx.x;
-    const Frag Q = frag_of<ARGS>(a, table, prefix, gid);
+    const Frag Q = frag_of<ARGS>(a, table, prefix, a.nframes, gid);
     const FrameDesc& d = *Q.fd;
     const FrameParams& fp = d.p;
     const int nbx = fp.nbx, nby = d.nby;

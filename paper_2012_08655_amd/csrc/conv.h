@@ -399,12 +399,14 @@ __device__ __forceinline__ int frame_search(const int32_t* __restrict__ prefix, 
 // Everything the kernels need to know about one fragment.
 struct Frag {
     const FrameDesc* fd;
+    int f;  // the frame's index in the launch
     int lb, bx, by, xa, ya, bw, bh;
 };
 
-__device__ __forceinline__ Frag describe_at(const FrameDesc* fd, int first, int gid) {
+__device__ __forceinline__ Frag describe_at(const FrameDesc* fd, int f, int first, int gid) {
     Frag F;
     F.fd = fd;
+    F.f = f;
     const FrameParams& fp = fd->p;
     F.lb = gid - first;
     F.by = F.lb / fp.nbx;
@@ -422,7 +424,29 @@ __device__ __forceinline__ Frag describe_at(const FrameDesc* fd, int first, int 
 __device__ __forceinline__ Frag describe(const FrameDesc* __restrict__ table, const int32_t* __restrict__ prefix,
                                          int nframes, int gid) {
     const int f = frame_search(prefix, nframes, gid);
-    return describe_at(table + f, prefix[f], gid);
+    return describe_at(table + f, f, prefix[f], gid);
+}
+
+// Frame f of the launch, in the kernel arguments (ARGS: launches of up to kArgFrames frames) or the
+// device table.
+template <bool ARGS>
+__device__ __forceinline__ const FrameDesc& frame_of(const FwdLaunch& a, const FrameDesc* __restrict__ table, int f) {
+    if constexpr (ARGS) return a.fr[f];
+    else return table[f];
+}
+
+// Fragment gid of the launch, its frame read from the kernel arguments (ARGS: launches of up to
+// kArgFrames frames) or from the device table.
+template <bool ARGS>
+__device__ __forceinline__ Frag frag_of(const FwdLaunch& a, const FrameDesc* __restrict__ table,
+                                        const int32_t* __restrict__ prefix, int nframes, int gid) {
+    if constexpr (ARGS) {
+        int f = 0;
+        while (f + 1 < nframes && gid >= a.kprefix[f + 1]) ++f;
+        return describe_at(&a.fr[f], f, a.kprefix[f], gid);
+    } else {
+        return describe(table, prefix, nframes, gid);
+    }
 }
 
 }  // namespace

@@ -87,9 +87,14 @@ fov_status launch_forward(const FwdLaunch& a, int in_dtype, int out_dtype, size_
                           hipStream_t stream, size_t lds_limit, int cus, bool persist,
                           hipEvent_t ev_start = nullptr, hipEvent_t ev_stop = nullptr);
 
-// The main forward kernel for a dtype pair and dispatch mode (to find its node
-// in a captured graph); NULL for an unsupported pair.
-const void* forward_main_kernel(int in_dtype, int out_dtype, bool persist);
+// The main forward kernel of a batch table launched one workgroup per slot, for
+// a dtype pair (to find its node in a captured graph); NULL for an unsupported
+// pair.
+const void* forward_main_kernel(int in_dtype, int out_dtype, int r_cap);
+
+// Whether launches of this dtype pair with radii up to r_cap run on the matrix
+// cores (8-bit output; see fixed.h).
+bool forward_fixed(int in_dtype, int out_dtype, int r_cap);
 
 // Device plan for foveate_plan(): sigma and radius of every fragment.
 fov_status launch_plan(const FrameParams& fp, int nblk, double* sigma_out, int32_t* r_out, hipStream_t stream);
@@ -97,7 +102,7 @@ fov_status launch_plan(const FrameParams& fp, int nblk, double* sigma_out, int32
 // LDS bytes a forward workgroup needs for radius r_cap and output tiles of
 // tile_w x tile_h pixels (the fragment side B divided by the split, rounded
 // up; tile_h = 2B when vertical pairs are merged).
-size_t forward_lds_bytes(int in_dtype, int r_cap, int tile_w, int tile_h, int strip_rows);
+size_t forward_lds_bytes(int in_dtype, int out_dtype, int r_cap, int tile_w, int tile_h, int strip_rows);
 
 // Padded-tile rows of a tile tile_h pixels tall at radius r (what a strip
 // height above it cannot change).
@@ -105,7 +110,7 @@ int forward_tile_rows(int r, int tile_h);
 
 // Workgroups of the main kernel (one workgroup per queue slot) that one CU
 // holds at once with `lds` bytes of dynamic LDS each.
-int forward_occupancy(int in_dtype, int out_dtype, size_t lds);
+int forward_occupancy(int in_dtype, int out_dtype, int r_cap, size_t lds);
 
 // Largest strip height the kernel stages at once.
 int forward_strip_max();

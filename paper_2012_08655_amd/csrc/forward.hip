@@ -35,6 +35,7 @@
 #include <hip/hip_ext.h>
 
 #include "conv.h"
+#include "fixed.h"
 
 #include <algorithm>
 #include <cmath>
@@ -292,8 +293,8 @@ __device__ __forceinline__ void copy_fragment(const Frag& F, int c_lo, int c_hi)
 // in flight while the current one is computed), horizontal pass into the
 // column-major intermediate, vertical pass into the output.
 template <typename TIn, typename TOut, typename TS, typename TC>
-__device__ __forceinline__ void process_fragment(const FwdLaunch& a, int gid, int r, const Frag& F, int c_lo,
-                                                 int c_hi, const TC* __restrict__ wts, unsigned char* smem) {
+__device__ __forceinline__ void process_fragment(int r_cap, int strip_rows, int r, const Frag& F, int c_lo, int c_hi,
+                                                 const TC* __restrict__ wg, unsigned char* smem) {
     const FrameDesc& d = *F.fd;
     if (r == 0) {
         copy_fragment<TIn, TOut>(F, c_lo, c_hi);
@@ -301,7 +302,7 @@ __device__ __forceinline__ void process_fragment(const FwdLaunch& a, int gid, in
     }
     const int tid = threadIdx.x;
     const Geom g = geom(r, F.bw, F.bh);
-    const int SR = min(min(a.strip_rows, kStripMax), g.TH);
+    const int SR = min(min(strip_rows, kStripMax), g.TH);
     // 8-bit input: the symmetric horizontal pass wants each output's centre on a 4-sample group,
     // so the tile starts sh = (-r) mod 4 columns further left.
     constexpr bool kSym = std::is_same<TS, _Float16>::value;
@@ -315,11 +316,10 @@ __device__ __forceinline__ void process_fragment(const FwdLaunch& a, int gid, in
     // integer samples, which it reads as fp16 subnormals; the scaling is exact).
     TC* w = reinterpret_cast<TC*>(smem + kTileLead);
     TC* ws = w + round_up(g.N, 4);
-    TS* tile = reinterpret_cast<TS*>(smem + kTileLead + tap_lds_bytes(a.r_cap, sizeof(TC)));
+    TS* tile = reinterpret_cast<TS*>(smem + kTileLead + tap_lds_bytes(r_cap, sizeof(TC)));
     TC* inter = reinterpret_cast<TC*>(reinterpret_cast<unsigned char*>(tile) +
                                       align16((size_t)SR * TP * sizeof(TS)));  // [column][row]
     {
-        const TC* __restrict__ wg = wts + (size_t)gid * a.wstride;
         for (int i = tid; i < g.N; i += kThreads) {
             const TC v = wg[i];
             w[i] = v;
@@ -426,6 +426,59 @@ __device__ __forceinline__ void process_fragment(const FwdLaunch& a, int gid, in
     }
 }
 
+// Counts of a launch: from the arguments or (replayed launches) the device header.
+struct Counts {
+    int nslots, nframes;
+};
+
+template <bool ARGS>
+__device__ __forceinline__ Counts counts(const FwdLaunch& a) {
+    Counts n{a.nslots, a.nframes};
+    if (!ARGS && a.hdr) {
+        n.nslots = __builtin_amdgcn_readfirstlane(a.hdr[2]);
+        n.nframes = __builtin_amdgcn_readfirstlane(a.hdr[0]);
+    }
+    return n;
+}
+
+// A work item: fragment gid of radius r (a merged pair: the taller rectangle), its rectangle and its
+// channels c_lo .. c_hi - 1.
+struct Item {
+    int gid, r, c_lo, c_hi;
+    Frag F;
+};
+
+// The work item in queue slot q; false if the slot holds none.
+template <bool ARGS>
+__device__ __forceinline__ bool decode(const FwdLaunch& a, const int32_t* __restrict__ order,
+                                       const FrameDesc* __restrict__ table, const int32_t* __restrict__ prefix,
+                                       int nframes, int q, Item* it) {
+    const int2 ent = reinterpret_cast<const int2*>(order)[q];  // (work item, radius word)
+    int item = __builtin_amdgcn_readfirstlane(ent.x);
+    if (item < 0) return false;  // empty slot
+    const int L = a.split_log2;
+    int c_lo = 0, c_hi = 1 << 30;                    // clipped to the frame's below
+    if (a.cs_rmax >= 0 && (item & kChanItem)) {  // one channel of a fragment split by channel
+        c_lo = (item >> kChanShift) & 15;
+        c_hi = c_lo + 1;
+        item &= kChanItemMask;
+    }
+    const int gid = item >> (2 * L);
+    const int rr = __builtin_amdgcn_readfirstlane(ent.y);
+    Frag F = frag_of<ARGS>(a, table, prefix, nframes, gid);
+    if (rr >> 16) {  // merged with the fragment below (same taps): one taller tile
+        const Frag F2 = describe_at(F.fd, F.f, gid - F.lb, gid + F.fd->p.nbx);
+        F.bh = F2.ya + F2.bh - F.ya;
+    }
+    if (!narrow_to_tile(F, L, item & ((1 << (2 * L)) - 1))) return false;
+    it->gid = gid;
+    it->r = rr & 0xFFFF;
+    it->c_lo = c_lo;
+    it->c_hi = min(c_hi, F.fd->c);
+    it->F = F;
+    return it->c_lo < it->c_hi;
+}
+
 // Work items are taken from the queue (by decreasing radius, so the costliest
 // start first); an item is a whole fragment or, with a split, one output tile
 // of it (same radius and taps, its own halo).  PERSIST = false: one workgroup per queue slot,
@@ -433,46 +486,78 @@ __device__ __forceinline__ void process_fragment(const FwdLaunch& a, int gid, in
 // PERSIST = true: a grid sized to what the chip holds at once; workgroup b
 // takes slots b, b + grid, b + 2 grid, ... (round-robin over the cost-sorted
 // queue balances the load without atomics).
-template <typename TIn, typename TOut, typename TS, typename TC, bool PERSIST>
+template <typename TIn, typename TOut, typename TS, typename TC, bool PERSIST, bool ARGS>
 __global__ __launch_bounds__(kThreads) void fov_fwd_kernel(const FwdLaunch a, const int32_t* __restrict__ radius,
                                                            const TC* __restrict__ wts,
                                                            const int32_t* __restrict__ order,
                                                            const FrameDesc* __restrict__ table,
                                                            const int32_t* __restrict__ prefix) {
     extern __shared__ __align__(16) unsigned char smem[];
-    const int nslots = a.hdr ? a.hdr[2] : a.nslots;
-    const int nframes = a.hdr ? a.hdr[0] : a.nframes;
-    const int L = a.split_log2;
-    for (int q = blockIdx.x; q < nslots; q += gridDim.x) {
-        const int2 ent = reinterpret_cast<const int2*>(order)[q];  // (work item, radius word)
-        int item = ent.x;
-        if (item < 0) {  // empty slot
-            if (!PERSIST) break;
-            continue;
+    const Counts n = counts<ARGS>(a);
+    for (int q = blockIdx.x; q < n.nslots; q += gridDim.x) {
+        Item it;
+        if (decode<ARGS>(a, order, table, prefix, n.nframes, q, &it)) {
+            it.F.fd = &frame_of<ARGS>(a, table, it.F.f);
+            process_fragment<TIn, TOut, TS, TC>(a.r_cap, a.strip_rows, it.r, it.F, it.c_lo, it.c_hi,
+                                                wts + (size_t)it.gid * a.wstride, smem);
         }
-        int c_lo = 0, c_hi = 1 << 30;  // channels of this item (clipped to the frame's below)
-        if (a.cs_rmax >= 0 && (item & kChanItem)) {  // one channel of a fragment split by channel
-            c_lo = (item >> kChanShift) & 15;
-            c_hi = c_lo + 1;
-            item &= kChanItemMask;
-        }
-        const int gid = item >> (2 * L);
-        const int rr = ent.y;
-        const int r = rr & 0xFFFF;
-        Frag F = describe(table, prefix, nframes, gid);
-        if (rr >> 16) {  // merged with the fragment below (same taps): one taller tile
-            const Frag F2 = describe_at(F.fd, gid - F.lb, gid + F.fd->p.nbx);
-            F.bh = F2.ya + F2.bh - F.ya;
-        }
-        if (!narrow_to_tile(F, L, item & ((1 << (2 * L)) - 1))) {
-            if (!PERSIST) break;
-            continue;
-        }
-        c_hi = min(c_hi, F.fd->c);
-        if (c_lo < c_hi) process_fragment<TIn, TOut, TS, TC>(a, gid, r, F, c_lo, c_hi, wts, smem);
         if (!PERSIST) break;
         __syncthreads();  // this fragment's LDS reads are done before the next one is staged
     }
+}
+
+// ---- 8-bit main kernel ---------------------------------------------------------------------------
+// 8-bit frames to 8-bit frames in launches of radius up to kFxRadius: one workgroup per queue slot, its
+// tiles on the matrix cores (fixed.h); r = 0 is copied.
+//
+// The FP32 passes for a tile that the matrix cores leave.  A function of its own: it is rare, and inlined
+// it would take registers from the common path.
+__device__ __attribute__((noinline)) void fp32_tile(FrameDesc fd, const float* wg, int r_cap, int strip_rows, int r,
+                                                    int xa, int ya, int bw, int bh, int c_lo, int c_hi) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    Frag P;
+    P.fd = &fd;
+    P.f = P.lb = P.bx = P.by = 0;  // not used by the passes
+    P.xa = xa;
+    P.ya = ya;
+    P.bw = bw;
+    P.bh = bh;
+    process_fragment<uint8_t, uint8_t, _Float16, float>(r_cap, strip_rows, r, P, c_lo, c_hi, wg, smem);
+}
+
+template <bool ARGS>
+__global__ __launch_bounds__(kThreads, 3) void fov_fwd_u8_kernel(const FwdLaunch a, const float* __restrict__ wts,
+                                                                 const int32_t* __restrict__ order,
+                                                                 const FrameDesc* __restrict__ table,
+                                                                 const int32_t* __restrict__ prefix) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    const Counts n = counts<ARGS>(a);
+    if ((int)blockIdx.x >= n.nslots) return;
+    Item it;
+    if (!decode<ARGS>(a, order, table, prefix, n.nframes, blockIdx.x, &it)) return;
+    const FrameDesc& d = frame_of<ARGS>(a, table, it.F.f);
+    it.F.fd = &d;
+    if (it.r == 0) {
+        copy_fragment<uint8_t, uint8_t>(it.F, it.c_lo, it.c_hi);
+        return;
+    }
+    const float* wg = wts + (size_t)it.gid * a.wstride;
+    const int r = it.r, nk = fx_blocks(r);
+    for (int c0 = it.c_lo; c0 < it.c_hi; c0 += kFxChan)
+        for (int ty = 0; ty < it.F.bh; ty += kFxTile)
+            for (int tx = 0; tx < it.F.bw; tx += kFxTile) {
+                if (c0 > it.c_lo || (ty | tx)) __syncthreads();  // the previous tile's LDS is read
+                const FxJob t{r, it.F.xa + tx, it.F.ya + ty, min(it.F.bw - tx, kFxTile), min(it.F.bh - ty, kFxTile), c0,
+                              min(it.c_hi - c0, kFxChan)};
+                bool left;
+                if (nk == 2) left = fx_tile<2>(d, t, wg, smem);
+                else if (nk == 3) left = fx_tile<3>(d, t, wg, smem);
+                else left = fx_tile<4>(d, t, wg, smem);
+                if (left) {
+                    __syncthreads();
+                    fp32_tile(d, wg, a.r_cap, a.strip_rows, r, t.xa, t.ya, t.bw, t.bh, c0, c0 + t.nc);
+                }
+            }
 }
 
 constexpr int kOrderThreads = 1024;
@@ -503,25 +588,15 @@ __global__ __launch_bounds__(64) void fov_plan_weights_kernel(const FwdLaunch a,
                                                               int32_t* __restrict__ okey, int nrings, int nang,
                                                               TC* __restrict__ wts) {
     const int lane = threadIdx.x;
-    const int nframes = a.hdr ? a.hdr[0] : a.nframes;
-    const int nfrag = a.hdr ? a.hdr[1] : a.nfrag;
+    int nframes = a.nframes, nfrag = a.nfrag;
+    if (a.hdr) {
+        nframes = __builtin_amdgcn_readfirstlane(a.hdr[0]);
+        nfrag = __builtin_amdgcn_readfirstlane(a.hdr[1]);
+    }
     for (int gid = blockIdx.x; gid < nfrag; gid += gridDim.x) {
     Frag F;
-    if (a.from_args) {
-        int f = 0;
-        while (f + 1 < nframes && gid >= a.kprefix[f + 1]) ++f;
-        F = describe_at(&a.fr[f], a.kprefix[f], gid);
-        if (gid == 0) {
-            // publish the frame table for the main kernel
-            constexpr int kWords = sizeof(FrameDesc) / 4;
-            const int32_t* src = reinterpret_cast<const int32_t*>(a.fr);
-            int32_t* dst = reinterpret_cast<int32_t*>(a.table);
-            for (int i = lane; i < nframes * kWords; i += 64) dst[i] = src[i];
-            for (int i = lane; i <= nframes; i += 64) a.prefix[i] = a.kprefix[i];
-        }
-    } else {
-        F = describe(a.table, a.prefix, nframes, gid);
-    }
+    if (a.from_args) F = frag_of<true>(a, a.table, a.prefix, nframes, gid);
+    else F = frag_of<false>(a, a.table, a.prefix, nframes, gid);
     const FrameParams& fp = F.fd->p;
     const double sigma = fp.sigma_map ? clip_map_sigma((double)fp.sigma_map[F.lb], fp.cap)
                                       : fragment_sigma_ramp(fp, F.bx, F.by);
@@ -715,10 +790,10 @@ __global__ void fov_plan_kernel(FrameParams fp, int n, double* sigma_out, int32_
     r_out[b] = radius_of(s);
 }
 
-template <typename TIn, typename TOut, typename TS, typename TC, bool PERSIST>
+template <typename TIn, typename TOut, typename TS, typename TC, bool PERSIST, bool ARGS>
 fov_status launch_main(const FwdLaunch& a, size_t lds, const PlanBuffers& plan, hipStream_t stream,
                        size_t lds_limit, int cus, hipEvent_t ev_start, hipEvent_t ev_stop) {
-    auto kern = fov_fwd_kernel<TIn, TOut, TS, TC, PERSIST>;
+    auto kern = fov_fwd_kernel<TIn, TOut, TS, TC, PERSIST, ARGS>;
     fov_status st = allow_dyn_lds((const void*)kern, lds_limit);
     if (st != FOV_OK) return st;
     int grid = a.nslots;
@@ -739,6 +814,25 @@ fov_status launch_main(const FwdLaunch& a, size_t lds, const PlanBuffers& plan, 
     return FOV_OK;
 }
 
+template <bool ARGS>
+fov_status launch_u8(const FwdLaunch& a, size_t lds, const PlanBuffers& plan, hipStream_t stream, size_t lds_limit,
+                     hipEvent_t ev_start, hipEvent_t ev_stop) {
+    auto kern = fov_fwd_u8_kernel<ARGS>;
+    fov_status st = allow_dyn_lds((const void*)kern, lds_limit);
+    if (st != FOV_OK) return st;
+    const dim3 grid(a.nslots);
+    const auto args = [&](auto&& launch) {
+        launch(a, (const float*)plan.weights, (const int32_t*)plan.order, (const FrameDesc*)a.table, (const int32_t*)a.prefix);
+    };
+    if (ev_start || ev_stop)
+        args([&](auto... x) { hipExtLaunchKernelGGL(kern, grid, dim3(kThreads), lds, stream, ev_start, ev_stop, 0, x...); });
+    else
+        args([&](auto... x) { hipLaunchKernelGGL(kern, grid, dim3(kThreads), lds, stream, x...); });
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return hip_error(e, "forward kernel launch");
+    return FOV_OK;
+}
+
 template <typename TIn, typename TOut, typename TS, typename TC>
 fov_status launch_typed(const FwdLaunch& a, size_t lds, const PlanBuffers& plan, hipStream_t stream,
                         size_t lds_limit, int cus, bool persist, hipEvent_t ev_start, hipEvent_t ev_stop) {
@@ -754,8 +848,12 @@ fov_status launch_typed(const FwdLaunch& a, size_t lds, const PlanBuffers& plan,
                        a.split_log2, nrings, nang, a.nslots, a.hdr, plan.order, a.cs_rmax, a.cmax);
     e = hipGetLastError();
     if (e != hipSuccess) return hip_error(e, "order kernel launch");
-    if (persist) return launch_main<TIn, TOut, TS, TC, true>(a, lds, plan, stream, lds_limit, cus, ev_start, ev_stop);
-    return launch_main<TIn, TOut, TS, TC, false>(a, lds, plan, stream, lds_limit, cus, ev_start, ev_stop);
+    if constexpr (std::is_same<TOut, uint8_t>::value)
+        if (forward_fixed(FOV_U8, FOV_U8, a.r_cap))
+            return (a.from_args ? launch_u8<true> : launch_u8<false>)(a, lds, plan, stream, lds_limit, ev_start, ev_stop);
+    const auto main = a.from_args ? (persist ? launch_main<TIn, TOut, TS, TC, true, true> : launch_main<TIn, TOut, TS, TC, false, true>)
+                                  : (persist ? launch_main<TIn, TOut, TS, TC, true, false> : launch_main<TIn, TOut, TS, TC, false, false>);
+    return main(a, lds, plan, stream, lds_limit, cus, ev_start, ev_stop);
 }
 
 int stage_size(int in_dtype) { return in_dtype == FOV_U8 ? 2 : (in_dtype == FOV_F32 ? 4 : 8); }
@@ -786,15 +884,22 @@ int forward_strip_max() { return kStripMax; }
 
 int forward_tile_rows(int r, int tile_h) { return geom(r, 1, tile_h).TH; }
 
-size_t forward_lds_bytes(int in_dtype, int r_cap, int tile_w, int tile_h, int strip_rows) {
+bool forward_fixed(int in_dtype, int out_dtype, int r_cap) {
+    return in_dtype == FOV_U8 && out_dtype == FOV_U8 && r_cap >= 1 && r_cap <= kFxRadius;
+}
+
+size_t forward_lds_bytes(int in_dtype, int out_dtype, int r_cap, int tile_w, int tile_h, int strip_rows) {
     const Geom g = geom(r_cap, tile_w, tile_h);
     int rows = strip_rows < g.TH ? strip_rows : g.TH;
     if (rows > kStripMax) rows = kStripMax;
     const int es = stage_size(in_dtype), ec = compute_size(in_dtype);
     // 8-bit input: (-r) mod 4 leading columns; 2r + ((-r) mod 4) never decreases with r, so r_cap sizes them
     const int TW = g.TW + (in_dtype == FOV_U8 ? ((-r_cap) & 3) : 0);
-    return kTileLead + tap_lds_bytes(r_cap, ec) + align16((size_t)rows * tile_pitch(TW, es) * es) +
-           (size_t)g.G * kPH * inter_pitch(g.TH, ec) * ec + 64;
+    const size_t fp32 = kTileLead + tap_lds_bytes(r_cap, ec) + align16((size_t)rows * tile_pitch(TW, es) * es) +
+                        (size_t)g.G * kPH * inter_pitch(g.TH, ec) * ec + 64;
+    if (!forward_fixed(in_dtype, out_dtype, r_cap)) return fp32;
+    // the matrix-core tiles and the FP32 passes take turns in one allocation
+    return std::max(fp32, (size_t)fx_lds(fx_blocks(r_cap), kFxChan).total);
 }
 
 fov_status launch_forward(const FwdLaunch& a, int in_dtype, int out_dtype, size_t lds, const PlanBuffers& plan,
@@ -812,24 +917,17 @@ fov_status launch_forward(const FwdLaunch& a, int in_dtype, int out_dtype, size_
     return set_error(FOV_EDTYPE, "unsupported dtype pair");
 }
 
-int forward_occupancy(int in_dtype, int out_dtype, size_t lds) {
-    const void* k = forward_main_kernel(in_dtype, out_dtype, false);
+int forward_occupancy(int in_dtype, int out_dtype, int r_cap, size_t lds) {
+    const void* k = forward_main_kernel(in_dtype, out_dtype, r_cap);
     return k ? occupancy_of(k, lds) : 0;
 }
 
-const void* forward_main_kernel(int in_dtype, int out_dtype, bool persist) {
-    if (in_dtype == FOV_U8 && out_dtype == FOV_U8)
-        return persist ? (const void*)fov_fwd_kernel<uint8_t, uint8_t, _Float16, float, true>
-                       : (const void*)fov_fwd_kernel<uint8_t, uint8_t, _Float16, float, false>;
-    if (in_dtype == FOV_U8 && out_dtype == FOV_F32)
-        return persist ? (const void*)fov_fwd_kernel<uint8_t, float, _Float16, float, true>
-                       : (const void*)fov_fwd_kernel<uint8_t, float, _Float16, float, false>;
-    if (in_dtype == FOV_F32 && out_dtype == FOV_F32)
-        return persist ? (const void*)fov_fwd_kernel<float, float, float, float, true>
-                       : (const void*)fov_fwd_kernel<float, float, float, float, false>;
-    if (in_dtype == FOV_F64 && out_dtype == FOV_F64)
-        return persist ? (const void*)fov_fwd_kernel<double, double, double, double, true>
-                       : (const void*)fov_fwd_kernel<double, double, double, double, false>;
+const void* forward_main_kernel(int in_dtype, int out_dtype, int r_cap) {
+    if (forward_fixed(in_dtype, out_dtype, r_cap)) return (const void*)fov_fwd_u8_kernel<false>;
+    if (in_dtype == FOV_U8 && out_dtype == FOV_U8) return (const void*)fov_fwd_kernel<uint8_t, uint8_t, _Float16, float, false, false>;
+    if (in_dtype == FOV_U8 && out_dtype == FOV_F32) return (const void*)fov_fwd_kernel<uint8_t, float, _Float16, float, false, false>;
+    if (in_dtype == FOV_F32 && out_dtype == FOV_F32) return (const void*)fov_fwd_kernel<float, float, float, float, false, false>;
+    if (in_dtype == FOV_F64 && out_dtype == FOV_F64) return (const void*)fov_fwd_kernel<double, double, double, double, false, false>;
     return nullptr;
 }
 

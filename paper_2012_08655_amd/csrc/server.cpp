@@ -193,12 +193,12 @@ fov_status build_graph(ServerImpl* s, Slot& sl) {
     // capped vertical pairs as one item (as the plain forward does by default) when the taller
     // tiles let as many workgroups share a CU
     const int B = s->cfg.max_block, sr = choose_strip_rows();
-    size_t lds = forward_lds_bytes(s->cfg.in_dtype, s->r_cap, B, B, sr);
+    size_t lds = forward_lds_bytes(s->cfg.in_dtype, s->cfg.out_dtype, s->r_cap, B, B, sr);
     if (lds + 64 > dev->lds_limit) return set_error(FOV_ERANGE, "max_sigma needs more LDS than a workgroup may use");
-    const size_t lds2 = forward_lds_bytes(s->cfg.in_dtype, s->r_cap, B, 2 * B, sr);
-    const bool merge = s->r_cap > 0 && lds2 + 64 <= dev->lds_limit &&
-                       forward_occupancy(s->cfg.in_dtype, s->cfg.out_dtype, lds2) >=
-                           forward_occupancy(s->cfg.in_dtype, s->cfg.out_dtype, lds);
+    const size_t lds2 = forward_lds_bytes(s->cfg.in_dtype, s->cfg.out_dtype, s->r_cap, B, 2 * B, sr);
+    const bool merge = s->r_cap > 0 && !forward_fixed(s->cfg.in_dtype, s->cfg.out_dtype, s->r_cap) && lds2 + 64 <= dev->lds_limit &&
+                       forward_occupancy(s->cfg.in_dtype, s->cfg.out_dtype, s->r_cap, lds2) >=
+                           forward_occupancy(s->cfg.in_dtype, s->cfg.out_dtype, s->r_cap, lds);
     if (merge) lds = lds2;
     PlanBuffers plan;
     const FwdLaunch a = capacity_launch(s, sl, &plan, merge);
@@ -222,7 +222,7 @@ fov_status build_graph(ServerImpl* s, Slot& sl) {
     sl.graph = g;
     // The main kernel was captured with one workgroup per slot of the largest
     // batch; each replay sets its grid to the batch's own slot count.
-    const void* main_fn = forward_main_kernel(s->cfg.in_dtype, s->cfg.out_dtype, false);
+    const void* main_fn = forward_main_kernel(s->cfg.in_dtype, s->cfg.out_dtype, s->r_cap);
     size_t nnodes = 0;
     e = hipGraphGetNodes(g, nullptr, &nnodes);
     if (e != hipSuccess) return hip_error(e, "hipGraphGetNodes");

@@ -113,7 +113,7 @@ fov_tuning to_public(const LaunchCfg& c, float us) {
 // fill the chip several times over are not split (more halo work for nothing;
 // their work-item counts also make the single-workgroup order pass slow).
 constexpr int64_t kSplitMaxFragments = 4096;
-std::vector<LaunchCfg> candidates(const DeviceInfo& dev, int in_dtype, const CallShape& cs) {
+std::vector<LaunchCfg> candidates(const DeviceInfo& dev, int in_dtype, int out_dtype, const CallShape& cs) {
     std::vector<LaunchCfg> out;
     for (int L = 0; L <= 2; ++L) {
         const int tile = (cs.bmax + (1 << L) - 1) >> L;
@@ -127,7 +127,7 @@ std::vector<LaunchCfg> candidates(const DeviceInfo& dev, int in_dtype, const Cal
                 const int eff = std::min(sr, rows);
                 if (eff == prev) continue;
                 prev = eff;
-                if (forward_lds_bytes(in_dtype, cs.r_cap, tile, th, sr) + 64 > dev.lds_limit) continue;
+                if (forward_lds_bytes(in_dtype, out_dtype, cs.r_cap, tile, th, sr) + 64 > dev.lds_limit) continue;
                 for (bool persist : {false, true})
                     for (int chan : {0, 1}) {
                         if (chan && (L > 0 || cs.c < 2 || cs.c > 16)) continue;
@@ -157,7 +157,7 @@ fov_status autotune_frames(const std::vector<FrameDesc>& frames, int in_dtype, i
     if (reps < 0 || reps > 1000) return set_error(FOV_EINVAL, "reps must be in 0..1000");
     if (reps == 0) reps = 5;
     const CallShape cs = call_shape(frames.data(), (int)frames.size());
-    const std::vector<LaunchCfg> cands = candidates(*dev, in_dtype, cs);
+    const std::vector<LaunchCfg> cands = candidates(*dev, in_dtype, out_dtype, cs);
     if (cands.empty()) {
         // no configuration fits: let a plain call report the LDS error
         const LaunchCfg d = default_cfg();
