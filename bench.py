@@ -442,7 +442,7 @@ def main():
     torch.cuda.synchronize()
 
     # Timed region: exactly `steps` frames.  The library times the main kernel
-    # (plan and order kernels excluded) of one call in PROFILE_EVERY with HIP
+    # of one call in PROFILE_EVERY with HIP
     # events that the kernel's own dispatch stamps on the launch stream (a
     # stamped dispatch does not overlap the next kernel, so the other calls
     # run without events).
@@ -456,7 +456,7 @@ def main():
     wall = time.perf_counter() - t0
     kms = fov.profile_end(nprof)
     assert len(kms) == nprof
-    # Device time of whole calls (plan, order and main kernels), untimed: torch
+    # Device time of whole calls, untimed: torch
     # events around each call put marker packets between calls.
     nlat = min(args.steps, 200)
     ev = [(torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)) for _ in range(nlat)]
@@ -503,8 +503,7 @@ def main():
                    "frame_pixels": H * W, "channels": C, "block": 32},
         "frame_latency_ms": {"p50": round(float(np.percentile(call_ms, 50)), 5),
                              "p99": round(float(np.percentile(call_ms, 99)), 5),
-                             "kind": "plain per-frame launch: device time of one call (plan, order and main "
-                                     "kernels), HIP events"},
+                             "kind": "plain per-frame launch: device time of one call, HIP events"},
         "roofline": {"bound": "alu", "kernel": "fov_fwd_kernel<u8,u8,f32>",
                      "achieved": round(achieved_tflops, 3), "peak": PEAK_FP32_TFLOPS, "unit": "TFLOP/s",
                      "frac": round(achieved_tflops / PEAK_FP32_TFLOPS, 4), "traffic": traffic,
@@ -512,7 +511,7 @@ def main():
                      "mean_launch_ms": round(float(kms.mean()), 5),
                      "timed_launches": "%d of %d (one in %d)" % (len(kms), args.steps, PROFILE_EVERY),
                      "hbm_GBs_algorithmic": round(achieved_gbs, 1)},
-        "launch_config": tuned or "default (split 1, 64 strip rows, one workgroup per queue slot)",
+        "launch_config": tuned or "default (split 1, 64 strip rows, one workgroup per work item)",
         "paper_context": "GTX 1060: 1.65 ms kernel for one 1920x1080 RGB frame (~1257 Mpix/s), 165 Hz with transfers",
     }
     if not args.no_extra:

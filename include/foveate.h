@@ -164,10 +164,9 @@ fov_status foveate_forward(const fov_tensor* in, const fov_tensor* out, const fo
                            int32_t np, void* stream);
 
 /*
- * Foveate nframes frames of possibly different sizes in one launch: the
- * fragments of all frames form one queue, ordered by decreasing radius (their
- * cost), that a persistent grid drains (Alg. 1 run over a batch; each frame
- * keeps its own fixation and ramp).
+ * Foveate nframes frames of possibly different sizes in one launch over the
+ * fragments of all frames (Alg. 1 run over a batch; each frame keeps its own
+ * fixation and ramp).
  *   ins[i], outs[i] : views of one frame each (n == 1), any (c, h, w) and
  *                     strides; all frames share one dtype pair (as forward).
  *                     No output may overlap any input or another output.
@@ -182,21 +181,15 @@ fov_status foveate_forward_batch(const fov_tensor* ins, const fov_tensor* outs, 
 /*
  * foveate_forward for callers that cannot allocate device memory (code under
  * HIP graph capture, tight serving loops, harnesses that forbid hipMalloc).
- * Same arguments, kernels and bitwise the same outputs as foveate_forward,
- * but the plan workspace is a fixed 16 MiB array of device memory that the
- * library's code object holds on every GPU it runs on until the process ends;
- * the call makes no hipMalloc, hipFree, pinned or other allocation.  Limits:
+ * Same arguments, kernel and bitwise the same outputs as foveate_forward; the
+ * launch uses no device memory of the library's own, and the call makes no
+ * hipMalloc, hipFree, pinned or other allocation.  Limits:
  *   - at most 16 frames per call (n <= 16; their descriptors travel in the
  *     kernel arguments), else FOV_EINVAL;
- *   - the call's plan workspace (per fragment about 4 * (2r_max + 1) bytes of
- *     taps plus a few words of queue) must fit the 16 MiB, else FOV_EINVAL
- *     with the size it needed; a 3840x2160 frame in 32 px fragments fits at
- *     every radius the on-chip memory allows.
- * Every call on one GPU uses that GPU's single array: calls that overlap on
- * the device (different streams, or host threads without ordering) race and
- * may produce wrong outputs; order them on one stream.  Nothing the array
- * keeps from an earlier call is read before it is rewritten.  The first call
- * on each device looks the array's device address up (hipGetSymbolAddress).
+ *   - the plans of the call's fragments, counted as written out (per fragment
+ *     about 4 * (2r_max + 1) bytes of taps plus a few words), must stay within
+ *     16 MiB, else FOV_EINVAL with the size; a 3840x2160 frame in 32 px
+ *     fragments does at every radius the on-chip memory allows.
  */
 fov_status foveate_forward_noalloc(const fov_tensor* in, const fov_tensor* out, const fov_params* p,
                                    int32_t np, void* stream);
@@ -223,17 +216,18 @@ fov_status foveate_backward(const fov_tensor* grad_out, const fov_tensor* grad_i
  *   strip_rows : rows of the padded tile (halo included) staged in LDS at
  *                once: 16, 32 or 64.  Fewer rows need less LDS per workgroup.
  *   persistent : 1 = a grid sized to what the chip holds at once strides
- *                over the work queue; 0 = one workgroup per queue slot.
+ *                over the work items; 0 = one workgroup per work item.
  *   merge      : 1 = a fragment on an even row whose sigma and the sigma of
  *                the fragment below both equal the cap is one work item with
  *                it (equal taps: the halo rows the two share are computed
  *                once); needs split 1.  By default it is on unless its taller
  *                tiles would let fewer workgroups share a CU.
- *   chan_split : 1 = a fragment whose radius is at most 2/3 of the largest
- *                radius of the call is one work item per channel (such items
- *                come last in the queue and are latency bound: their channels
- *                then run side by side); needs split 1 and at most 16
- *                channels.  By default on for frames of several channels.
+ *   chan_split : 1 = a fragment is one work item per channel (short, latency
+ *                bound items: its channels then run side by side); needs split
+ *                1 and at most 16 channels.  By default on for frames of
+ *                several channels.
+ * 8-bit output of radii up to 48 runs on a kernel of its own that takes a
+ * fragment's channels together and follows `split` alone.
  *   time_us    : (output of foveate_autotune) median time of one call.
  */
 typedef struct {
@@ -250,7 +244,7 @@ typedef struct {
  * side, the bit length of the largest radius, the bit length of the fragment
  * count and the frame-count class (1, 2..16, more).  Later forward calls of
  * that class, from any thread, use the cached configuration; others use the
- * defaults (split 1, 64 strip rows, one workgroup per queue slot, merge and
+ * defaults (split 1, 64 strip rows, one workgroup per work item, merge and
  * chan_split as described above).  Writes
  * the chosen configuration to *best (may be NULL).  Arguments and errors as
  * foveate_forward / foveate_forward_batch; `out` holds the foveated frames on
@@ -291,7 +285,7 @@ fov_status foveate_tuning_load(const char* path);
  * (the per-frame loop of Alg. 1), with continuous batching: a scheduler thread
  * admits queued frames while the bytes of admitted, unfinished frames stay
  * within an HBM budget, launches everything admitted as one batched forward
- * (the queue of foveate_forward_batch) on one of several streams, and admits
+ * (foveate_forward_batch) on one of several streams, and admits
  * and launches frames that arrive while other batches are on the device, so
  * consecutive batches overlap on the GPU.  Frames stay where the caller put
  * them (device memory); results are identical to foveate_forward's.
@@ -427,8 +421,7 @@ fov_status foveate_pipeline_destroy(fov_pipeline* pl);
 /*
  * Kernel timing for measurement.  Between foveate_profile_begin(capacity) and
  * foveate_profile_end(), each forward call made by this thread records the
- * start and end of its main kernel (the per-fragment blur; the plan and order
- * kernels that precede it are not included) in a pair of HIP events that the
+ * start and end of its kernel in a pair of HIP events that the
  * kernel's dispatch stamps on its stream, up to `capacity` calls.  foveate_profile_end waits for the
  * recorded events, writes up to `capacity` durations in milliseconds to ms
  * (host array, may be NULL), stores how many in *count and releases the

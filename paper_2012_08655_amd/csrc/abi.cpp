@@ -77,7 +77,7 @@ fov_status device_info(const DeviceInfo** out) {
 
 // Library-owned workspace, one per (device, stream): work queued on one stream
 // is ordered, so consecutive calls on that stream may reuse it.  It holds a
-// device buffer (plans, queues, frame tables) and a pinned host buffer for
+// device buffer (frame tables, adjoint windows) and a pinned host buffer for
 // uploading frame tables.  Both only grow; before a device buffer in use is
 // freed the stream is drained, and before the pinned buffer is rewritten the
 // previous upload from it is waited for.
@@ -356,13 +356,13 @@ fov_status prepare(const fov_tensor* in, const fov_tensor* out, const fov_params
 size_t frame_table_bytes(int nf) { return ((size_t)nf * sizeof(FrameDesc) + (size_t)(nf + 1) * 4 + 255) / 256 * 256; }
 
 // Place a launch's frame descriptors where its kernels read them: in the
-// kernel arguments (up to kArgFrames; the plan kernel copies them to dtab) or
-// uploaded to dtab from the workspace's pinned buffer.
+// kernel arguments (up to kArgFrames) or uploaded to dtab from the workspace's
+// pinned buffer.
 fov_status stage_frame_table(const FrameDesc* frames, int nf, const int32_t* prefix, Workspace* ws, char* dtab,
                              size_t tbytes, hipStream_t stream, FwdLaunch* a) {
-    a->table = reinterpret_cast<FrameDesc*>(dtab);
-    a->prefix = reinterpret_cast<int32_t*>(dtab + (size_t)nf * sizeof(FrameDesc));
     if (nf > kArgFrames) {
+        a->table = reinterpret_cast<FrameDesc*>(dtab);
+        a->prefix = reinterpret_cast<int32_t*>(dtab + (size_t)nf * sizeof(FrameDesc));
         if (ws->upload_pending) {
             hipError_t e = hipEventSynchronize(ws->upload_done);
             if (e != hipSuccess) return hip_error(e, "hipEventSynchronize(upload)");
@@ -396,6 +396,15 @@ CallShape call_shape(const FrameDesc* frames, int nf) {
     return cs;
 }
 
+// Bytes that the plans of a call's fragments (radius, taps and queue slots of every fragment) take when
+// written out; foveate_forward_noalloc's size limit is stated in them.
+size_t plan_bytes(const FwdLaunch& a, bool by_channel, int tap_size) {
+    const auto up = [](size_t v, size_t m) { return (v + m - 1) / m * m; };
+    const size_t nfrag = a.nfrag, pad = 8 * (size_t)std::min(a.r_cap + 1, 1024);
+    const size_t slots = by_channel && nfrag < ((size_t)1 << 26) ? a.cmax * (nfrag + pad) : (nfrag << (2 * a.split_log2)) + pad;
+    return up(2 * up(nfrag * 4, 16) + up(slots * 8, 16) + 256 + nfrag * up(2 * (size_t)a.r_cap + 1, 16) * tap_size, 256);
+}
+
 // Launch shape of one forward call over a list of frames (any shapes, one
 // dtype pair): counts, radius bound, LDS and scratch sizes; no device work.
 fov_status plan_forward(const FrameDesc* frames, int nf, int in_dtype, int out_dtype, const LaunchCfg* cfg_in,
@@ -417,7 +426,7 @@ fov_status plan_forward(const FrameDesc* frames, int nf, int in_dtype, int out_d
     // vertical pairs at the cap need tiles twice as tall; by default only when the CU holds as
     // many workgroups with them
     const bool fixed = forward_fixed(in_dtype, out_dtype, r_cap);
-    bool merge = (fixed ? cfg.merge > 0 : cfg.merge != 0) && L == 0 && r_cap > 0;
+    bool merge = !fixed && cfg.merge != 0 && L == 0 && r_cap > 0;
     if (merge) {
         const size_t lds2 = forward_lds_bytes(in_dtype, out_dtype, r_cap, tile, 2 * tile, sr);
         if (lds2 + 64 > dev->lds_limit ||
@@ -430,7 +439,6 @@ fov_status plan_forward(const FrameDesc* frames, int nf, int in_dtype, int out_d
     if (lds + 64 > dev->lds_limit)
         return set_error(FOV_ERANGE, "radius " + std::to_string(r_cap) + " needs " + std::to_string(lds) +
                                          " bytes of LDS; the device allows " + std::to_string(dev->lds_limit));
-    const int wsize = in_dtype == FOV_F64 ? 8 : 4;
     FwdLaunch& a = fp->a;
     std::memset(&a, 0, sizeof(a));
     // first fragment of each frame: in the kernel arguments' copy for calls of at most kArgFrames
@@ -449,34 +457,32 @@ fov_status plan_forward(const FrameDesc* frames, int nf, int in_dtype, int out_d
     a.merge = merge ? 1 : 0;
     a.r_cap = r_cap;
     a.strip_rows = sr;
-    a.wstride = round_up(2 * r_cap + 1, 16);
-    // Fragments of radius <= 2/3 of r_cap become one work item per channel (the latency-bound
-    // items at the end of the queue then run their channels side by side).
-    const bool chan = (fixed ? cfg.chan_split > 0 : cfg.chan_split != 0) && L == 0 && cs.c > 1 && cs.c <= 16 && a.nfrag < (1 << kChanShift);
-    const int cs_rmax = chan ? (2 * r_cap) / 3 : -1;
-    a.cs_rmax = cs_rmax;
     a.cmax = cs.c;
-    a.nslots = cs_rmax >= 0 ? queue_slots_by_channel(a.nfrag, r_cap, cs.c) : queue_slots(a.nfrag << (2 * L), r_cap);
+    a.even = 1;
+    for (int i = 0; i < nf; ++i) a.even &= prefix[i + 1] - prefix[i] == prefix[1];
+    // one work item per channel, unless a configuration says otherwise
+    a.chan = !fixed && cfg.chan_split != 0 && L == 0 && cs.c > 1 && cs.c <= 16 &&
+             cs.nfrag * cs.c <= ((int64_t)1 << 30);
+    a.nitems = a.chan ? a.nfrag * cs.c : a.nfrag << (2 * L);
     fp->lds = lds;
     fp->persistent = cfg.persistent;
-    fp->pbytes = (plan_bytes(a.nfrag, a.nslots, a.wstride, wsize) + 255) / 256 * 256;
-    fp->tbytes = frame_table_bytes(nf);
+    fp->tbytes = nf > kArgFrames ? frame_table_bytes(nf) : 0;
+    fp->plan_bytes = plan_bytes(a, cfg.chan_split != 0 && L == 0 && cs.c > 1 && cs.c <= 16, in_dtype == FOV_F64 ? 8 : 4) +
+                     frame_table_bytes(nf);
     fp->lds_limit = dev->lds_limit;
     fp->cus = dev->cus;
     return FOV_OK;
 }
 
-// Plan, order and main kernels of a planned call, with its plan workspace at
-// `scratch` (at least fp.pbytes + fp.tbytes bytes of device memory).  Frame
-// tables of more than kArgFrames frames are uploaded from ws's pinned buffer
-// (ws may be NULL for calls of at most kArgFrames frames).
-fov_status launch_planned(const FrameDesc* frames, int nf, int in_dtype, int out_dtype, ForwardPlan& fp,
-                          void* scratch, Workspace* ws, hipStream_t stream, bool profile) {
+// The kernel of a planned call.  Frame tables of more than kArgFrames frames
+// are uploaded from ws's pinned buffer to its device buffer (ws may be NULL
+// for calls of at most kArgFrames frames).
+fov_status launch_planned(const FrameDesc* frames, int nf, int in_dtype, int out_dtype, ForwardPlan& fp, Workspace* ws,
+                          hipStream_t stream, bool profile) {
     fov_status s;
     FwdLaunch& a = fp.a;
-    const PlanBuffers plan = carve_plan(scratch, a.nfrag, a.nslots);
-    if ((s = stage_frame_table(frames, nf, fp.prefix(), ws, static_cast<char*>(scratch) + fp.pbytes,
-                               fp.tbytes, stream, &a)) != FOV_OK)
+    if ((s = stage_frame_table(frames, nf, fp.prefix(), ws, ws ? static_cast<char*>(ws->dev) : nullptr, fp.tbytes, stream,
+                               &a)) != FOV_OK)
         return s;
     hipEvent_t e0 = nullptr, e1 = nullptr;
     if (profile && g_prof.on && g_prof.calls++ % g_prof.every == 0 && g_prof.used < g_prof.ev.size()) {
@@ -484,24 +490,22 @@ fov_status launch_planned(const FrameDesc* frames, int nf, int in_dtype, int out
         e1 = g_prof.ev[g_prof.used].second;
         ++g_prof.used;
     }
-    return launch_forward(a, in_dtype, out_dtype, fp.lds, plan, stream, fp.lds_limit, fp.cus, fp.persistent, e0, e1);
+    return launch_forward(a, in_dtype, out_dtype, fp.lds, stream, fp.lds_limit, fp.cus, fp.persistent, e0, e1);
 }
 
-// One forward launch over a list of frames (any shapes, one dtype pair), its
-// plan workspace in the library's per-(device, stream) workspace.  Up to
+// One forward launch over a list of frames (any shapes, one dtype pair).  Up to
 // kArgFrames descriptors travel in the kernel arguments; more are uploaded
-// as a device table from pinned memory.
+// as a device table from pinned memory to the per-(device, stream) workspace.
 fov_status run_forward(const std::vector<FrameDesc>& frames, int in_dtype, int out_dtype, hipStream_t stream,
                        const LaunchCfg* cfg_in, bool profile) {
     if (frames.empty()) return FOV_OK;
     fov_status s;
     ForwardPlan fp;
     if ((s = plan_forward(frames.data(), (int)frames.size(), in_dtype, out_dtype, cfg_in, &fp)) != FOV_OK) return s;
-    const bool upload = (int)frames.size() > kArgFrames;
     Workspace* ws = nullptr;
     std::unique_lock<std::mutex> hold;
-    if ((s = workspace(stream, fp.pbytes + fp.tbytes, upload ? fp.tbytes : 0, &ws, &hold)) != FOV_OK) return s;
-    return launch_planned(frames.data(), (int)frames.size(), in_dtype, out_dtype, fp, ws->dev, ws, stream, profile);
+    if (fp.tbytes > 0 && (s = workspace(stream, fp.tbytes, fp.tbytes, &ws, &hold)) != FOV_OK) return s;
+    return launch_planned(frames.data(), (int)frames.size(), in_dtype, out_dtype, fp, ws, stream, profile);
 }
 
 // Scratch of the adjoint's horizontal transposes, per launch: frames are

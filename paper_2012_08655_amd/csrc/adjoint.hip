@@ -59,12 +59,6 @@ __device__ __forceinline__ Window window_of(const Frag& F, int r, int h, int w) 
     return v;
 }
 
-// Blur strength of fragment (bx, by), local index lb, of a frame: from the sigma map or from the
-// midpoint's eccentricity (Sec. 2).
-__device__ __forceinline__ double fragment_sigma(const FrameParams& fp, int lb, int bx, int by) {
-    return fp.sigma_map ? clip_map_sigma((double)as_global(fp.sigma_map)[lb], fp.cap) : fragment_sigma_ramp(fp, bx, by);
-}
-
 // The fragment's taps in LDS: V copies (V = 16 / sizeof(T)), copy k holding tap i at element
 // k * stride + kAdjWeightLead + k + i (stride a multiple of 4) with zeros around, so that a run of
 // taps starting at any tap t >= -kAdjWeightLead + 1 starts on a 16-byte boundary in one of them and

@@ -72,6 +72,13 @@ __device__ __forceinline__ global_ptr<T> as_global(T* p) {
 // Index of the calling wavefront in its workgroup, as a scalar (uniform) value.
 __device__ __forceinline__ int wave_id() { return __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); }
 
+// A value that is the same in every lane, held in scalar registers.
+__device__ __forceinline__ double uniform(double v) {
+    const uint64_t u = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)u), hi = __builtin_amdgcn_readfirstlane((uint32_t)(u >> 32));
+    return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
+}
+
 // ---- LDS window loads -------------------------------------------------------------------------
 template <typename T>
 __device__ __forceinline__ void load4_row(const T* p, T (&b)[4]) {
@@ -384,6 +391,80 @@ __host__ __device__ inline uint32_t div_magic(uint32_t d) { return d > 1 ? 0xFFF
 
 __device__ __forceinline__ int div_by(int x, uint32_t m) { return m ? (int)__umulhi((uint32_t)x, m) : x; }
 
+// Blur strength of fragment (bx, by), local index lb, of a frame: from the sigma map or from the
+// midpoint's eccentricity (Sec. 2).
+__device__ __forceinline__ double fragment_sigma(const FrameParams& fp, int lb, int bx, int by) {
+    return fp.sigma_map ? clip_map_sigma((double)as_global(fp.sigma_map)[lb], fp.cap) : fragment_sigma_ramp(fp, bx, by);
+}
+
+// x summed over the wavefront by a butterfly (distances 32, 16, 8, 4, 2, 1), in every lane.  The last four
+// steps rotate within rows of 16 lanes: after the steps above a value repeats every 2 off lanes, so the lane
+// off further round holds what the lane at distance off does.
+__device__ __forceinline__ double wave_sum(double x) {
+    union Words {
+        double d;
+        uint32_t u[2];
+    };
+    const auto add = [](const Words& a, const Words& b) { return a.d + b.d; };
+    Words v{x};
+    {
+        const auto lo = __builtin_amdgcn_permlane32_swap(v.u[0], v.u[0], false, false);
+        const auto hi = __builtin_amdgcn_permlane32_swap(v.u[1], v.u[1], false, false);
+        Words a, b;
+        a.u[0] = lo[0], a.u[1] = hi[0], b.u[0] = lo[1], b.u[1] = hi[1];
+        v.d = add(a, b);
+    }
+    {
+        const auto lo = __builtin_amdgcn_permlane16_swap(v.u[0], v.u[0], false, false);
+        const auto hi = __builtin_amdgcn_permlane16_swap(v.u[1], v.u[1], false, false);
+        Words a, b;
+        a.u[0] = lo[0], a.u[1] = hi[0], b.u[0] = lo[1], b.u[1] = hi[1];
+        v.d = add(a, b);
+    }
+#define FOV_ROTATE_ADD(ctrl)                                                              \
+    {                                                                                     \
+        Words b;                                                                          \
+        b.u[0] = __builtin_amdgcn_mov_dpp((int)v.u[0], ctrl, 0xf, 0xf, true);            \
+        b.u[1] = __builtin_amdgcn_mov_dpp((int)v.u[1], ctrl, 0xf, 0xf, true);            \
+        v.d = add(v, b);                                                                  \
+    }
+    FOV_ROTATE_ADD(0x128)  // row_ror:8
+    FOV_ROTATE_ADD(0x124)
+    FOV_ROTATE_ADD(0x122)
+    FOV_ROTATE_ADD(0x121)
+#undef FOV_ROTATE_ADD
+    return v.d;
+}
+
+// The normalised taps w_k = exp(-k^2/(2 sigma^2)) / sum of a fragment (Eq. 1 cut at 3 sigma), in FP64.  The
+// sum is taken by one wavefront (every wave forms it for itself): lane l adds its taps l, l + 64, ... in
+// order, then a butterfly over the lanes.
+struct Taps {
+    double inv, sum, e0, e1;  // e0, e1: this lane's first two terms
+    __device__ __forceinline__ Taps(double sigma, int r, int lane) {
+        const int N = 2 * r + 1;
+        inv = r > 0 ? 1.0 / (2.0 * sigma * sigma) : 0.0;
+        e0 = lane < N ? raw(lane, r) : 0.0;
+        double part = e0;
+        e1 = 0.0;
+        if (N > 64) {
+            e1 = lane + 64 < N ? raw(lane + 64, r) : 0.0;
+            part += e1;
+            for (int j0 = 128; j0 < N; j0 += 64)
+                if (j0 + lane < N) part += raw(j0 + lane, r);
+        }
+        sum = wave_sum(part);
+    }
+    __device__ __forceinline__ double raw(int j, int r) const {
+        const double k = (double)(j - r);
+        return exp(-(k * k) * inv);
+    }
+    // Tap 64 q + lane.
+    __device__ __forceinline__ double tap(int q, int r, int lane) const {
+        return (q == 0 ? e0 : (q == 1 ? e1 : raw(64 * q + lane, r))) / sum;
+    }
+};
+
 // ---- fragments of a launch ---------------------------------------------------------------------
 // Last frame whose first fragment is <= gid (prefix has nframes+1 entries).
 __device__ __forceinline__ int frame_search(const int32_t* __restrict__ prefix, int nframes, int gid) {
@@ -403,21 +484,27 @@ struct Frag {
     int lb, bx, by, xa, ya, bw, bh;
 };
 
-__device__ __forceinline__ Frag describe_at(const FrameDesc* fd, int f, int first, int gid) {
+// Fragment (bx, by) of frame f.
+__device__ __forceinline__ Frag fragment_at(const FrameDesc* fd, int f, int bx, int by) {
     Frag F;
     F.fd = fd;
     F.f = f;
     const FrameParams& fp = fd->p;
-    F.lb = gid - first;
-    F.by = F.lb / fp.nbx;
-    F.bx = F.lb - F.by * fp.nbx;
+    F.bx = bx;
+    F.by = by;
+    F.lb = by * fp.nbx + bx;
     const int B = fp.block;
-    const int X0 = fp.origin_x + F.bx * B, Y0 = fp.origin_y + F.by * B;
+    const int X0 = fp.origin_x + bx * B, Y0 = fp.origin_y + by * B;
     F.xa = max(X0, 0);
     F.ya = max(Y0, 0);
     F.bw = min(X0 + B, fd->w) - F.xa;
     F.bh = min(Y0 + B, fd->h) - F.ya;
     return F;
+}
+
+__device__ __forceinline__ Frag describe_at(const FrameDesc* fd, int f, int first, int gid) {
+    const int lb = gid - first, by = lb / fd->p.nbx;
+    return fragment_at(fd, f, lb - by * fd->p.nbx, by);
 }
 
 // Fragment gid, reading frames from the device table (main kernel).

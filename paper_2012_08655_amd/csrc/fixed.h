@@ -86,9 +86,16 @@ __host__ __device__ constexpr int fx_digits(int nk) { return 32 * nk + 40; }
 // Floats of one undecided pixel's column of horizontal sums.
 __host__ __device__ constexpr int fx_col(int nk) { return 32 * (nk - 1) + 4; }
 
-// LDS layout: taps w[N] and 2^24 w_k (k = 1..r); the tap sum, M, the count of
-// undecided pixels and the channels left over; the undecided pixels; the digit
-// copies (later the columns of the recomputation); the channel planes.
+// What the tap wave tells the others, and the tile's undecided pixels: how many, and whether there are too
+// many of them.
+struct FxHead {
+    int F, und, over;
+    float bias, lim;  // added to every sum; 1/2 - e1 - the constant part of e2
+};
+
+// LDS layout: taps w[N] and 2^24 w_k (k = 1..r); the FxHead; the undecided
+// pixels; the digit copies (later the columns of the recomputation); the
+// channel planes.
 struct FxLds {
     int ws, misc, list, digits, tile, total;
 };
@@ -96,7 +103,7 @@ __host__ __device__ constexpr FxLds fx_lds(int nk, int nchan) {
     FxLds l{};
     l.ws = fx_col(nk) * 4;
     l.misc = l.ws + (16 * (nk - 1) + 4) * 4;
-    l.list = l.misc + 16;
+    l.list = l.misc + 32;
     l.digits = l.list + kFxCap * 2;
     const int dig = 12 * fx_digits(nk), cols = kFxBatch * fx_col(nk) * 4;
     l.tile = l.digits + ((dig > cols ? dig : cols) + 15) / 16 * 16;
@@ -114,7 +121,7 @@ __device__ __forceinline__ void load_words(uint32_t* v, global_ptr<const uint8_t
     __builtin_memcpy(v, (const void*)p, 4 * N);
 }
 
-// Staging of a tile's samples (rows y0.., columns x0.., clamped to the frame) as bytes x ^ 0x80, planes
+// Staging of a tile's samples (rows y0.., columns x0.., clamped to the frame) in LDS, channel planes
 // apart.  A lane takes 16 columns of a row at a time (8 lanes to a row, 4 where a window is two blocks
 // wide): fewer and wider loads than one group of four columns per lane, whose 12-byte loads cost the
 // L1 twice the accesses per row.
@@ -134,8 +141,7 @@ struct FxStager {
     bool rgb, later;         // later: the samples are in v (else in LDS already)
 
     __device__ __forceinline__ void put(unsigned char* tile, int i, int ch, int g, uint32_t t) const {
-        *reinterpret_cast<uint32_t*>(tile + (lrow + 4 * kRows * i) * fx_pitch(NK) + col + ch * fx_plane(NK) + 4 * g) =
-            t ^ 0x80808080u;
+        *reinterpret_cast<uint32_t*>(tile + (lrow + 4 * kRows * i) * fx_pitch(NK) + col + ch * fx_plane(NK) + 4 * g) = t;
     }
     // Three words of four interleaved pixels to their channels' words.
     __device__ __forceinline__ void put_rgb(unsigned char* tile, int i, int g, uint32_t a, uint32_t b, uint32_t c) const {
@@ -264,38 +270,46 @@ struct FxStager {
 template <int NK>
 __device__ __forceinline__ float fx_row_sum(const unsigned char* plane, int row, int cc, int r, float w0s,
                                             const float* __restrict__ ws) {
-    const uint32_t* line = reinterpret_cast<const uint32_t*>(plane + row * fx_pitch(NK));
-    auto dword = [&](int g) { return line[g] ^ 0x80808080u; };
-    const uint32_t s = (uint32_t)cc & 3u, sr = (s + 1) & 3u;
-    int gl = (cc >> 2) - 1, gr = (cc + 1) >> 2;  // groups of columns cc-4.. and cc+1..
-    uint32_t Lh = dword(gl + 1), Rl = dword(gr);
-    float acc = fmaf(w0s, (float)as_h2((Lh >> (8 * s)) & 0xffu).x, 0.0f);
     // byte selectors: samples cc+1, cc+2 | cc+3, cc+4 and cc-1, cc-2 | cc-3, cc-4, each in 16 bits
-    const uint32_t z = 0x0c000c00u;
-    const uint32_t r12 = sr | (sr + 1) << 16 | z, r34 = (sr + 2) | (sr + 3) << 16 | z;
-    const uint32_t l12 = (s + 3) | (s + 2) << 16 | z, l34 = (s + 1) | s << 16 | z;
-    auto tap = [&](float w, float x) { acc = fmaf(w, x, acc); };
+    const uint32_t s = (uint32_t)cc & 3u, sr = (s + 1) & 3u, z = 0x0c000c00u;
+    const uint32_t r12 = sr | (sr + 1) << 16 | z, r34 = r12 + 0x00020002u;
+    const uint32_t l34 = (s + 1) | s << 16 | z, l12 = l34 + 0x00020002u;
+    const uint32_t* line = reinterpret_cast<const uint32_t*>(plane + row * fx_pitch(NK));
+    const uint32_t* left = line + (cc >> 2);         // words downwards, from the one of column cc
+    const uint32_t* right = line + ((cc + 1) >> 2);  // words upwards, from the one of column cc + 1
+    uint32_t Lh = left[0], Rl = right[0];
+    float acc = fmaf(w0s, (float)as_h2((Lh >> (8 * s)) & 0xffu).x, 0.0f);
+    const auto tap = [&](float w, float x) { acc = fmaf(w, x, acc); };
     int k = 0;
-#pragma unroll 2
-    for (; k + 4 <= r; k += 4, --gl, ++gr) {
-        const uint32_t Ll = dword(gl), Rh = dword(gr + 1);
-        const h2v a = as_h2(perm(Rh, Rl, r12) + perm(Lh, Ll, l12));
-        const h2v b = as_h2(perm(Rh, Rl, r34) + perm(Lh, Ll, l34));
-        const float4 w = *reinterpret_cast<const float4*>(ws + k);
+    for (; k + 8 <= r; k += 8, left -= 2, right += 2) {
+        const uint32_t La = left[-1], Lb = left[-2], Ra = right[1], Rb = right[2];
+        const h2v a = as_h2(perm(Ra, Rl, r12) + perm(Lh, La, l12));
+        const h2v b = as_h2(perm(Ra, Rl, r34) + perm(Lh, La, l34));
+        const h2v c = as_h2(perm(Rb, Ra, r12) + perm(La, Lb, l12));
+        const h2v d = as_h2(perm(Rb, Ra, r34) + perm(La, Lb, l34));
+        const float4 w = *reinterpret_cast<const float4*>(ws + k), y = *reinterpret_cast<const float4*>(ws + k + 4);
         tap(w.x, (float)a.x);
         tap(w.y, (float)a.y);
         tap(w.z, (float)b.x);
         tap(w.w, (float)b.y);
-        Lh = Ll;
-        Rl = Rh;
+        tap(y.x, (float)c.x);
+        tap(y.y, (float)c.y);
+        tap(y.z, (float)d.x);
+        tap(y.w, (float)d.y);
+        Lh = Lb;
+        Rl = Rb;
     }
-    if (k < r) {
-        const uint32_t Ll = dword(gl), Rh = dword(gr + 1);
+    for (; k < r; k += 4, --left, ++right) {
+        const uint32_t Ll = left[-1], Rh = right[1];
         const h2v a = as_h2(perm(Rh, Rl, r12) + perm(Lh, Ll, l12));
         const h2v b = as_h2(perm(Rh, Rl, r34) + perm(Lh, Ll, l34));
-        tap(ws[k], (float)a.x);
-        if (k + 1 < r) tap(ws[k + 1], (float)a.y);
-        if (k + 2 < r) tap(ws[k + 2], (float)b.x);
+        const float4 w = *reinterpret_cast<const float4*>(ws + k);  // taps past r are not used
+        tap(w.x, (float)a.x);
+        if (k + 1 < r) tap(w.y, (float)a.y);
+        if (k + 2 < r) tap(w.z, (float)b.x);
+        if (k + 3 < r) tap(w.w, (float)b.y);
+        Lh = Ll;
+        Rl = Rh;
     }
     return acc;
 }
@@ -304,13 +318,14 @@ __device__ __forceinline__ float fx_row_sum(const unsigned char* plane, int row,
 // bytes at o (rows osh, columns osw apart) and lists the undecided pixels; returns false if the
 // list has no room for them.
 template <int NK>
-__device__ __forceinline__ bool fx_channel(const unsigned char* plane, const v4i (&T)[NK][3], int F, int Q,
-                                           float bias, float lim, float e2, int bw, int bh, global_ptr<uint8_t> o,
-                                           int64_t osh, int64_t osw, int ch, int* count, uint16_t* list, int lane) {
+__device__ __forceinline__ bool fx_channel(const unsigned char* plane, const v4i (&T)[NK][3], FxHead& head,
+                                           float e2, int bw, int bh, global_ptr<uint8_t> o, int64_t osh, int64_t osw,
+                                           int ch, uint16_t* list, int lane) {
     const int l = lane & 31, h = lane >> 5;
     const unsigned char* lane_plane = plane + l * fx_pitch(NK) + 4 * h;
     v16i L4{}, L3{}, L2{};
-    const int cut = F - 8 - Q;
+    const int F = head.F, Q = min(16, F - 8), cut = F - 8 - Q;
+    const float bias = head.bias, lim = head.lim;
 #pragma unroll
     for (int b = 0; b < NK; ++b) {
         v4i P[NK];
@@ -318,7 +333,7 @@ __device__ __forceinline__ bool fx_channel(const unsigned char* plane, const v4i
         for (int j = 0; j < NK; ++j)
 #pragma unroll
             for (int q = 0; q < 4; ++q)
-                P[j][q] = *reinterpret_cast<const int*>(lane_plane + 32 * b * fx_pitch(NK) + 32 * j + 8 * q);
+                P[j][q] = *reinterpret_cast<const int*>(lane_plane + 32 * b * fx_pitch(NK) + 32 * j + 8 * q) ^ (int)0x80808080;
         v16i A{}, C{};
 #pragma unroll
         for (int j = 0; j < NK; ++j) A = __builtin_amdgcn_mfma_i32_32x32x32_i8(P[j], T[j][0], A, 0, 0, 0);
@@ -379,7 +394,7 @@ __device__ __forceinline__ bool fx_channel(const unsigned char* plane, const v4i
     const int mine = __popc(und);
     if (__ballot(mine != 0) == 0) return true;
     int at = 0;
-    if (mine) at = atomicAdd(count, mine);
+    if (mine) at = atomicAdd(&head.und, mine);
     const bool over = at + mine > kFxCap;
     if (__ballot(over)) return false;
     for (; und; und &= und - 1) {
@@ -442,11 +457,9 @@ struct FxJob {
     int r, xa, ya, bw, bh, c0, nc;
 };
 
-// Runs a tile with NK = fx_blocks(r); wg: the fragment's FP32 taps.  Returns whether the tile is left to
-// the FP32 passes (the same for every thread).  LDS is in use until every thread has returned.
+// Runs a tile with NK = fx_blocks(r).  Returns whether the tile is left to the FP32 passes (the same for every thread).  LDS is in use until every thread has returned.
 template <int NK>
-__device__ __forceinline__ bool fx_tile(const FrameDesc& d, const FxJob& t, const float* __restrict__ wg,
-                                        unsigned char* smem) {
+__device__ __forceinline__ bool fx_tile(const FrameDesc& d, const FxJob& t, double sigma, unsigned char* smem) {
     int tid = threadIdx.x;
     asm volatile("" : "+v"(tid));  // lane addresses computed per tile, not held across tiles
     const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -454,42 +467,61 @@ __device__ __forceinline__ bool fx_tile(const FrameDesc& d, const FxJob& t, cons
     constexpr FxLds at = fx_lds(NK, kFxChan);
     float* w = reinterpret_cast<float*>(smem);
     float* ws = reinterpret_cast<float*>(smem + at.ws);
-    int* misc = reinterpret_cast<int*>(smem + at.misc);  // tap sum, M 2^(F-8), undecided pixels, too many of them
+    FxHead* head = reinterpret_cast<FxHead*>(smem + at.misc);
     uint16_t* list = reinterpret_cast<uint16_t*>(smem + at.list);
     unsigned char* dig = smem + at.digits;
     unsigned char* tile = smem + at.tile;
-    const float w0 = wg[r];
-    float tap = 0.0f;
-    if (tid < N) tap = wg[tid];
     FxStager<NK> st;
     st.load(tile, d, t.xa - r, t.ya - r, t.c0, t.nc, TH, wave, lane);
-    // Tap digits, four byte-shifted copies each (so that a lane's four taps are one aligned word).
+    // The taps and their digits, four byte-shifted copies of each (so that a lane's four taps are one aligned
+    // word), by the wave that has no channel to compute: it rotates over the workgroups of a CU.
+    const int ch = (wave + (blockIdx.x >> 3)) & 3;
     constexpr int LEN = fx_digits(NK);
-    int F = 22 - ilogbf(w0);
-    if (ldexpf(w0, F) > 8355000.0f) --F;
-    const int Q = min(16, F - 8);
     for (int i = tid; i < 12 * LEN / 4; i += kThreads) reinterpret_cast<uint32_t*>(dig)[i] = 0;
-    if (tid < 4) misc[tid] = 0;
     __syncthreads();
-    if (tid < N) {
-        w[tid] = tap;
-        if (tid > r) ws[tid - r - 1] = tap * kSymScale;
-        const int W = (int)rintf(ldexpf(tap, F));
-        atomicAdd(&misc[0], W);
-        if (tid > r) atomicAdd(&misc[1], ((W >> 8) + 1) * (tid - r));  // rounded up
-        const uint32_t u = (uint32_t)(W + 0x8080);
-        const uint8_t b0 = (uint8_t)(u ^ 0x80u), b1 = (uint8_t)((u >> 8) ^ 0x80u), b2 = (uint8_t)(u >> 16);
+    if (ch == 3) {
+        asm volatile("" : "+s"(sigma));  // here, while the samples arrive, and not ahead of the tile loop
+        const Taps tp(sigma, r, lane);
+        const float w0 = (float)(1.0 / tp.sum);  // tap r
+        int F = 22 - ilogbf(w0);
+        if (ldexpf(w0, F) > 8355000.0f) --F;
+        int W = 0, M = 0;  // this lane's taps in units of 2^-F; its part of M in units of 2^(8-F), rounded up
+        const auto put_tap = [&](int i, double e) {
+            const float t = (float)(e / tp.sum);
+            w[i] = t;
+            const int v = (int)rintf(ldexpf(t, F));
+            W += v;
+            if (i > r) {
+                ws[i - r - 1] = t * kSymScale;
+                M += ((v >> 8) + 1) * (i - r);
+            }
+            const uint32_t u = (uint32_t)(v + 0x8080);
+            const uint8_t b0 = (uint8_t)(u ^ 0x80u), b1 = (uint8_t)((u >> 8) ^ 0x80u), b2 = (uint8_t)(u >> 16);
 #pragma unroll
-        for (int s = 0; s < 4; ++s) {
-            dig[(0 * 4 + s) * LEN + tid + 32 + s] = b0;
-            dig[(1 * 4 + s) * LEN + tid + 32 + s] = b1;
-            dig[(2 * 4 + s) * LEN + tid + 32 + s] = b2;
+            for (int s = 0; s < 4; ++s) {
+                dig[(0 * 4 + s) * LEN + i + 32 + s] = b0;
+                dig[(1 * 4 + s) * LEN + i + 32 + s] = b1;
+                dig[(2 * 4 + s) * LEN + i + 32 + s] = b2;
+            }
+        };
+        if (lane < N) put_tap(lane, tp.e0);
+        if (lane + 64 < N) put_tap(lane + 64, tp.e1);
+        const double both = wave_sum((double)W), m = wave_sum((double)M);
+        if (lane == 0) {
+            const int Q = min(16, F - 8);
+            const double sw = ldexp(both, -F);  // sum of the taps
+            const float fN = (float)N, u = 1.02f * 5.9604645e-8f;
+            const float e1 = 1.01f * 255.0f * ldexpf(fN, -F) + ldexpf(1.0f, -Q - 1) + ldexpf(1.0f, 8 - F) +
+                             1.01f * ldexpf(fN, 23 - F - Q) + 3.0517578e-5f;
+            const float eM = u * fminf(128.0f * (float)r, 255.0f * ldexpf((float)m, 8 - F));
+            head->F = F;
+            head->und = head->over = 0;
+            head->bias = (float)(128.0 * sw * sw) + ldexpf(1.0f, -Q - 1);
+            head->lim = 0.5f - e1 - eM;
         }
     }
     st.store(tile);
     __syncthreads();
-    // A wave's channel; the wave without one rotates over the workgroups of a CU.
-    const int ch = (wave + (blockIdx.x >> 3)) & 3;
     v4i T[NK][3];
     {
         const int l = lane & 31, h = lane >> 5, s = l & 3;
@@ -502,21 +534,16 @@ __device__ __forceinline__ bool fx_tile(const FrameDesc& d, const FxJob& t, cons
                     T[j][dg][q] = *reinterpret_cast<const int*>(dig + (dg * 4 + s) * LEN + 32 * j + 8 * q + 4 * h - l + s + 32);
     }
     if (ch < t.nc) {
-        const double sw = ldexp((double)misc[0], -F);  // sum of the taps
-        const float bias = (float)(128.0 * sw * sw) + ldexpf(1.0f, -Q - 1);
-        const float fN = (float)N, u = 1.02f * 5.9604645e-8f;
-        const float e1 = 1.01f * 255.0f * ldexpf(fN, -F) + ldexpf(1.0f, -Q - 1) + ldexpf(1.0f, 8 - F) +
-                         1.01f * ldexpf(fN, 23 - F - Q) + 3.0517578e-5f;
-        const float eM = u * fminf(128.0f * (float)r, 255.0f * ldexpf((float)misc[1], 8 - F));
         global_ptr<uint8_t> o = as_global(static_cast<uint8_t*>(d.out)) + (int64_t)(t.c0 + ch) * d.osc +
                                 (int64_t)t.ya * d.osh + (int64_t)t.xa * d.osw;
-        const bool ok = fx_channel<NK>(tile + ch * fx_plane(NK), T, F, Q, bias, 0.5f - e1 - eM, 2.0f * u * (float)(r + 1),
-                                       t.bw, t.bh, o, d.osh, d.osw, ch, &misc[2], list, lane);
-        if (!ok && lane == 0) misc[3] = 1;
+        const bool ok = fx_channel<NK>(tile + ch * fx_plane(NK), T, *head, 2.0f * 1.02f * 5.9604645e-8f * (float)(r + 1),
+                                       t.bw, t.bh, o, d.osh, d.osw, ch, list, lane);
+        if (!ok && lane == 0) head->over = 1;
     }
     __syncthreads();
-    if (misc[3]) return true;
-    if (misc[2]) fx_recompute<NK>(d, r, t.xa, t.ya, t.c0, tile, w, ws, reinterpret_cast<float*>(dig), list, misc[2], tid);
+    if (head->over) return true;
+    const int und = head->und;
+    if (und) fx_recompute<NK>(d, r, t.xa, t.ya, t.c0, tile, w, ws, reinterpret_cast<float*>(dig), list, und, tid);
     return false;
 }
 

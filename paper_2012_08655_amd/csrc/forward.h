@@ -18,34 +18,33 @@ struct FrameDesc {
 // batches pass a device table instead.
 constexpr int kArgFrames = 16;
 
-// Kernel arguments shared by the plan, order and main forward kernels.
-// Fragments of all frames are numbered consecutively: frame f owns fragments
-// [prefix[f], prefix[f+1]).  Work item i belongs to fragment i >> (2 split_log2).
+// Kernel arguments of the forward and adjoint kernels.  Fragments of all
+// frames are numbered consecutively: frame f owns fragments
+// [prefix[f], prefix[f+1]).  Work item i of the forward belongs to fragment
+// i >> (2 split_log2) of the launch order (see decode() in forward.hip).
 struct FwdLaunch {
     int32_t nframes, nfrag;
-    int32_t nslots;      // queue slots (work items plus empty padding slots)
+    int32_t nitems;      // work items of the forward
     int32_t split_log2;  // each fragment is cut into (2^split_log2)^2 work items (output tiles of
                          // ceil(B / 2^split_log2) pixels a side); 0 = one item per fragment
     int32_t r_cap;       // largest radius the LDS allocation was sized for
     int32_t strip_rows;  // padded-tile rows staged in LDS at once
-    int32_t wstride;     // weights per fragment in the plan workspace (multiple of 16)
-    int32_t from_args;   // 1: fr[]/kprefix[] hold the frames and the plan kernel
-                         // copies them to table/prefix; 0: table/prefix were uploaded
-    int32_t cs_rmax;     // >= 0: a fragment with r <= cs_rmax becomes one work item per channel,
-                         // its channels in consecutive slots of one XCD after the rest of the
-                         // queue, so these short, latency-bound items run their channels side by
-                         // side and share that XCD's L2; -1: off.  Needs split_log2 = 0, fewer
-                         // than 2^26 fragments and cmax <= 16
-    int32_t cmax;        // largest channel count of the frames (with cs_rmax >= 0)
+    int32_t from_args;   // 1: fr[]/kprefix[] hold the frames; 0: table/prefix were uploaded
+    int32_t chan;        // 1: one work item per fragment and channel (cmax per fragment), so that
+                         // small, latency-bound launches run their channels side by side;
+                         // split_log2 must be 0
+    int32_t cmax;        // largest channel count of the frames
+    int32_t even;        // 1: every frame has the same number of fragments (items take the frames in
+                         // turn)
     int32_t merge;       // 1: a fragment at an even row whose sigma and the sigma of the fragment
                          // below both equal the cap becomes one work item with it (equal taps, so
                          // the halo rows they share are computed once); split_log2 must be 0
     FrameDesc* table;    // device table of nframes entries (read by the main kernel)
     int32_t* prefix;     // device array of nframes+1 entries
-    const int32_t* hdr;  // optional device header {nframes, nfrag, nslots}: when set, the kernels
+    const int32_t* hdr;  // optional device header {nframes, nfrag, nitems}: when set, the kernels
                          // read the counts there and the fields above are capacities (a launch
                          // sequence that can be captured once and replayed for many batches; the
-                         // replayer sets the main kernel's grid to the batch's slot count)
+                         // replayer sets the main kernel's grid to the batch's item count)
     int32_t kprefix[kArgFrames + 1];
     FrameDesc fr[kArgFrames];
 };
@@ -53,41 +52,19 @@ static_assert(sizeof(FwdLaunch) <= 4000, "kernel arguments must fit the kernarg 
 
 // Device header of a replayable batch (see FwdLaunch::hdr).
 struct BatchHeader {
-    int32_t nframes, nfrag, nslots, pad;
+    int32_t nframes, nfrag, nitems, pad;
 };
 
-// Plan workspace of one launch.
-struct PlanBuffers {
-    int32_t* radius;   // [nfrag] radius of each fragment
-    int32_t* okey;     // [nfrag] (ring, angle bin) cell of each fragment for the queue order
-    int32_t* order;    // [nslots][2] queue: (work item id, radius word) per slot (id -1 = empty
-                       // slot), see the order kernel
-    void* weights;     // [nfrag][wstride] normalised taps, float (u8/f32) or double (f64)
-};
-
-// Queue slots for nitems work items.
-int queue_slots(int nitems, int r_cap);
-// Queue slots when fragments may be split by channel (cs_rmax >= 0): room for one slot per
-// channel of every fragment and ring padding.
-int queue_slots_by_channel(int nfrag, int r_cap, int cmax);
-// Order entries of a per-channel work item (cs_rmax >= 0): bit 30 set, channel in bits 26-29,
-// fragment in bits 0-25.
-constexpr int32_t kChanItem = 1 << 30;
-constexpr int kChanShift = 26;
-constexpr int32_t kChanItemMask = (1 << kChanShift) - 1;
-size_t plan_bytes(int nfrag, int nslots, int wstride, int wsize);
-PlanBuffers carve_plan(void* ws, int nfrag, int nslots);
-
-// Plan + order + main kernel for one launch.  persist selects the dispatch of
-// the main kernel: a persistent grid striding over the queue, or one
-// workgroup per fragment handed out by the hardware dispatcher.
+// The forward kernel of one launch.  persist selects its dispatch: a persistent
+// grid striding over the work items, or one workgroup per item handed out by
+// the hardware dispatcher.
 // ev_start/ev_stop, when not null, are recorded on `stream` right before and
 // right after the main kernel.
-fov_status launch_forward(const FwdLaunch& a, int in_dtype, int out_dtype, size_t lds, const PlanBuffers& plan,
-                          hipStream_t stream, size_t lds_limit, int cus, bool persist,
+fov_status launch_forward(const FwdLaunch& a, int in_dtype, int out_dtype, size_t lds, hipStream_t stream,
+                          size_t lds_limit, int cus, bool persist,
                           hipEvent_t ev_start = nullptr, hipEvent_t ev_stop = nullptr);
 
-// The main forward kernel of a batch table launched one workgroup per slot, for
+// The main forward kernel of a batch table launched one workgroup per item, for
 // a dtype pair (to find its node in a captured graph); NULL for an unsupported
 // pair.
 const void* forward_main_kernel(int in_dtype, int out_dtype, int r_cap);
@@ -108,7 +85,7 @@ size_t forward_lds_bytes(int in_dtype, int out_dtype, int r_cap, int tile_w, int
 // height above it cannot change).
 int forward_tile_rows(int r, int tile_h);
 
-// Workgroups of the main kernel (one workgroup per queue slot) that one CU
+// Workgroups of the main kernel (one workgroup per work item) that one CU
 // holds at once with `lds` bytes of dynamic LDS each.
 int forward_occupancy(int in_dtype, int out_dtype, int r_cap, size_t lds);
 

@@ -1,29 +1,23 @@
-// Forward block-wise foveation for gfx950.
+// Forward block-wise foveation for gfx950: one launch per batch of frames, one workgroup per work item
+// (Alg. 1).  A work item finds its fragment from its number (decode()), the fragment's sigma from its
+// midpoint's eccentricity (Sec. 2, Fig. 1) or the sigma map, the radius r = ceil(3 sigma) and the normalised
+// taps w_k = exp(-k^2/(2 sigma^2)) / sum (Eq. 1 cut at 3 sigma, Appendix "Methods"), the taps while its first
+// samples are on their way.  Earlier forms ran a plan kernel (taps of every fragment) and an order kernel (a
+// counting sort by radius) first; for small calls the three launches in series were the time (480p gray 17.7
+// us a call, now 10.7; 1080p RGB 57.1, now 49.0), for large ones the order kernel's single workgroup
+// (64 mixed frames 4280 us, now 3503).  Calls of more than kArgFrames frames upload their frame table.
 //
-// Three launches per batch of frames on the caller's stream:
-//
-//  1. fov_plan_weights_kernel — one wavefront per fragment: the fragment's
-//     sigma from its midpoint's eccentricity (Sec. 2, Fig. 1), radius
-//     r = ceil(3 sigma) and the normalised taps w_k = exp(-k^2/(2 sigma^2)) / sum
-//     (Eq. 1 cut at 3 sigma, Appendix "Methods"), summed with wavefront
-//     shuffles, written to the plan workspace.
-//
-//  2. fov_order_kernel — a counting sort of fragments by decreasing radius
-//     (costliest first), dealt within each radius in angular arcs to the
-//     eight XCDs: the dispatch order of the main kernel.
-//
-//  3. fov_fwd_kernel — one workgroup per work item (Alg. 1): the padded
-//     tile (fragment plus r on each side, clamp-to-edge) is staged into LDS
-//     with row-coalesced loads, 8-bit input as 16-bit integers; a horizontal
-//     pass writes the fp32 intermediate into LDS; a vertical pass produces the
-//     fragment (Appendix "Workload of the Block", "Shared Memory").  Each
-//     thread computes 8 (horizontal) or 4 (vertical) outputs and slides the
-//     filter window through registers (the register reuse of Appendix "Data
-//     Reuse"); the work item copies its weights to LDS and both passes read
-//     them as broadcast LDS loads.  For 8-bit input the horizontal pass adds
-//     the two samples that share a weight (the taps are symmetric) exactly,
-//     two sums per 32-bit integer add, before the FP32 multiply-add.  A
-//     fragment with r = 0 is copied.
+//  * fov_fwd_kernel: the padded tile (fragment plus r on each side, clamp-to-edge) is staged into LDS
+//    with row-coalesced loads, 8-bit input as 16-bit integers; a horizontal
+//    pass writes the fp32 intermediate into LDS; a vertical pass produces the
+//    fragment (Appendix "Workload of the Block", "Shared Memory").  Each
+//    thread computes 8 (horizontal) or 4 (vertical) outputs and slides the
+//    filter window through registers (the register reuse of Appendix "Data
+//    Reuse"); both passes read the weights as broadcast LDS loads.  For 8-bit input the horizontal
+//    pass adds the two samples that share a weight (the taps are symmetric) exactly,
+//    two sums per 32-bit integer add, before the FP32 multiply-add.  A
+//    fragment with r = 0 is copied.
+//  * fov_fwd_u8_kernel: 8-bit output with radii up to 48, the same bytes on the matrix cores (fixed.h).
 //
 // Every output sums its taps in the same order (k = -r .. r; for 8-bit input
 // the horizontal pass goes k = 0, then the pairs +-1 .. +-r) whatever the
@@ -293,8 +287,8 @@ __device__ __forceinline__ void copy_fragment(const Frag& F, int c_lo, int c_hi)
 // in flight while the current one is computed), horizontal pass into the
 // column-major intermediate, vertical pass into the output.
 template <typename TIn, typename TOut, typename TS, typename TC>
-__device__ __forceinline__ void process_fragment(int r_cap, int strip_rows, int r, const Frag& F, int c_lo, int c_hi,
-                                                 const TC* __restrict__ wg, unsigned char* smem) {
+__device__ __forceinline__ void process_fragment(int r_cap, int strip_rows, int r, double sigma, const Frag& F, int c_lo,
+                                                 int c_hi, unsigned char* smem) {
     const FrameDesc& d = *F.fd;
     if (r == 0) {
         copy_fragment<TIn, TOut>(F, c_lo, c_hi);
@@ -310,8 +304,8 @@ __device__ __forceinline__ void process_fragment(int r_cap, int strip_rows, int 
     const int TW = g.TW + sh;
     const int TP = tile_pitch(TW, sizeof(TS));
     const int IP = inter_pitch(g.TH, sizeof(TC));
-    // The fragment's taps are copied to LDS once (read by the passes as broadcast LDS loads, so
-    // the inner loops wait on LDS only): w[0 .. N-1] = w_{-r} .. w_r, then for the symmetric
+    // The fragment's taps go to LDS once (read by the passes as broadcast LDS loads, so the inner
+    // loops wait on LDS only): w[0 .. N-1] = w_{-r} .. w_r, then for the symmetric
     // pass ws[j] = 2^24 w_{j+1} (j = 0 .. r-1) at a 16-byte boundary (scaled for the 16-bit
     // integer samples, which it reads as fp16 subnormals; the scaling is exact).
     TC* w = reinterpret_cast<TC*>(smem + kTileLead);
@@ -319,13 +313,6 @@ __device__ __forceinline__ void process_fragment(int r_cap, int strip_rows, int 
     TS* tile = reinterpret_cast<TS*>(smem + kTileLead + tap_lds_bytes(r_cap, sizeof(TC)));
     TC* inter = reinterpret_cast<TC*>(reinterpret_cast<unsigned char*>(tile) +
                                       align16((size_t)SR * TP * sizeof(TS)));  // [column][row]
-    {
-        for (int i = tid; i < g.N; i += kThreads) {
-            const TC v = wg[i];
-            w[i] = v;
-            if (kSym && i > r) ws[i - r - 1] = v * kSymScale;
-        }
-    }
     const TIn* in = static_cast<const TIn*>(d.in);
     const int nst = (g.TH + SR - 1) / SR;
     const int nunits = (c_hi - c_lo) * nst;  // (channel, strip) units, channels c_lo .. c_hi - 1
@@ -339,6 +326,15 @@ __device__ __forceinline__ void process_fragment(int r_cap, int strip_rows, int 
     const int64_t span = (int64_t)(d.c - 1) * d.isc + (int64_t)(d.h - 1) * d.ish + (int64_t)(d.w - 1) * d.isw + 1;
     st.setup(F.xa - r - sh, TW, d.w, d.isw, d.ish, d.h, in, (uint32_t)span);
     st.issue(in + c_lo * d.isc, F.ya - r, SR);
+    // the taps, while the first strip's samples arrive
+    Taps tp(sigma, r, tid & 63);
+    for (int q = wave_id(); 64 * q < g.N; q += kThreads / 64) {
+        const int i = 64 * q + (tid & 63);
+        if (i >= g.N) continue;
+        const TC v = (TC)tp.tap(q, r, tid & 63);
+        w[i] = v;
+        if (kSym && i > r) ws[i - r - 1] = v * kSymScale;
+    }
     st.commit(tile, TP);
     __syncthreads();
     int cu = 0, sidx = 0;  // the current unit: channel c_lo + cu, strip sidx
@@ -428,78 +424,107 @@ __device__ __forceinline__ void process_fragment(int r_cap, int strip_rows, int 
 
 // Counts of a launch: from the arguments or (replayed launches) the device header.
 struct Counts {
-    int nslots, nframes;
+    int nitems, nframes;
 };
 
 template <bool ARGS>
 __device__ __forceinline__ Counts counts(const FwdLaunch& a) {
-    Counts n{a.nslots, a.nframes};
+    Counts n{a.nitems, a.nframes};
     if (!ARGS && a.hdr) {
-        n.nslots = __builtin_amdgcn_readfirstlane(a.hdr[2]);
+        n.nitems = __builtin_amdgcn_readfirstlane(a.hdr[2]);
         n.nframes = __builtin_amdgcn_readfirstlane(a.hdr[0]);
     }
     return n;
 }
 
-// A work item: fragment gid of radius r (a merged pair: the taller rectangle), its rectangle and its
-// channels c_lo .. c_hi - 1.
+// A work item: a rectangle (a fragment, a merged pair of them or an output tile of one) with the sigma and
+// radius of its fragment, and its channels c_lo .. c_hi - 1.
 struct Item {
-    int gid, r, c_lo, c_hi;
+    int r, c_lo, c_hi;
+    double sigma;
     Frag F;
 };
 
-// The work item in queue slot q; false if the slot holds none.
+// Work item i of the launch; false if it holds nothing.  Items are numbered so that the costliest tend to
+// come first (a launch does not end on a long tail) and neighbours, which share halo samples, meet in one
+// L2, without any pass over the plan before the launch:
+//  * workgroup b runs on XCD b mod 8, each with an L2 of its own: every 64 items are dealt so that an XCD
+//    gets eight consecutive ones;
+//  * a frame's fragments go along its longer axis, the lines farthest from the fixation first (sigma grows
+//    with the distance), and in turn within a line; frames of equal fragment counts take turns.
 template <bool ARGS>
-__device__ __forceinline__ bool decode(const FwdLaunch& a, const int32_t* __restrict__ order,
-                                       const FrameDesc* __restrict__ table, const int32_t* __restrict__ prefix,
-                                       int nframes, int q, Item* it) {
-    const int2 ent = reinterpret_cast<const int2*>(order)[q];  // (work item, radius word)
-    int item = __builtin_amdgcn_readfirstlane(ent.x);
-    if (item < 0) return false;  // empty slot
+__device__ __forceinline__ bool decode(const FwdLaunch& a, const FrameDesc* __restrict__ table,
+                                       const int32_t* __restrict__ prefix, const Counts& n, int i, Item* it) {
     const int L = a.split_log2;
-    int c_lo = 0, c_hi = 1 << 30;                    // clipped to the frame's below
-    if (a.cs_rmax >= 0 && (item & kChanItem)) {  // one channel of a fragment split by channel
-        c_lo = (item >> kChanShift) & 15;
-        c_hi = c_lo + 1;
-        item &= kChanItemMask;
+    if ((i | 63) < n.nitems) i = (i & ~63) | (i & 7) << 3 | (i >> 3 & 7);
+    const int sub = i & ((1 << (2 * L)) - 1);
+    int k = i >> (2 * L), ch = -1;
+    if (a.chan) {
+        const int q = k / a.cmax;
+        ch = k - q * a.cmax;
+        k = q;
     }
-    const int gid = item >> (2 * L);
-    const int rr = __builtin_amdgcn_readfirstlane(ent.y);
-    Frag F = frag_of<ARGS>(a, table, prefix, nframes, gid);
-    if (rr >> 16) {  // merged with the fragment below (same taps): one taller tile
-        const Frag F2 = describe_at(F.fd, F.f, gid - F.lb, gid + F.fd->p.nbx);
-        F.bh = F2.ya + F2.bh - F.ya;
+    int f, rank;
+    if (a.even) {
+        rank = k / n.nframes;
+        f = k - rank * n.nframes;
+    } else if constexpr (ARGS) {
+        f = 0;
+        while (f + 1 < n.nframes && k >= a.kprefix[f + 1]) ++f;
+        rank = k - a.kprefix[f];
+    } else {
+        f = frame_search(prefix, n.nframes, k);
+        rank = k - prefix[f];
     }
-    if (!narrow_to_tile(F, L, item & ((1 << (2 * L)) - 1))) return false;
-    it->gid = gid;
-    it->r = rr & 0xFFFF;
-    it->c_lo = c_lo;
-    it->c_hi = min(c_hi, F.fd->c);
+    const FrameDesc& d = frame_of<ARGS>(a, table, f);
+    const FrameParams& fp = d.p;
+    // lines along the longer axis: n1 of them, n2 fragments in each
+    const bool cols = fp.nbx >= d.nby;
+    const int n1 = cols ? fp.nbx : d.nby, n2 = cols ? d.nby : fp.nbx;
+    const int line = rank / n2, at = rank - line * n2;
+    // The first t lines are farther from the fixation than the last one: they go first, then the rest from
+    // both ends in turn.  (Any t in 0 .. n1 visits every line once.)
+    const float c1 = (float)((cols ? fp.fix_x - fp.origin_x : fp.fix_y - fp.origin_y) + 0.5) / (float)fp.block;
+    const int t = (int)fminf(fmaxf(2.0f * c1 - (float)n1, 0.0f), (float)n1);
+    const int m = line - t;
+    const int pos = m < 0 ? line : ((m & 1) ? t + (m >> 1) : n1 - 1 - (m >> 1));
+    const int bx = __builtin_amdgcn_readfirstlane(cols ? pos : at), by = __builtin_amdgcn_readfirstlane(cols ? at : pos);
+    Frag F = fragment_at(&d, f, bx, by);
+    const double sigma = uniform(fragment_sigma(fp, F.lb, bx, by));
+    int r = __builtin_amdgcn_readfirstlane(radius_of(sigma));
+    if (r > a.r_cap) r = a.r_cap;  // the host sized everything for r_cap; plans agree bit for bit
+    // Vertical pairs at the cap (rows 2k and 2k+1, both sigma == cap, hence equal taps): the upper
+    // fragment's item covers both, the lower one's is empty.
+    if (a.merge && r > 0 && sigma == fp.cap) {
+        const int by2 = by ^ 1;
+        if (by2 < d.nby && fragment_sigma(fp, F.lb + (by2 - by) * fp.nbx, bx, by2) == fp.cap) {
+            if (by & 1) return false;
+            const Frag F2 = fragment_at(&d, f, bx, by2);
+            F.bh = F2.ya + F2.bh - F.ya;
+        }
+    }
+    if (!narrow_to_tile(F, L, sub)) return false;
+    it->r = r;
+    it->sigma = sigma;
+    it->c_lo = max(ch, 0);
+    it->c_hi = ch < 0 ? d.c : min(ch + 1, d.c);
     it->F = F;
     return it->c_lo < it->c_hi;
 }
 
-// Work items are taken from the queue (by decreasing radius, so the costliest
-// start first); an item is a whole fragment or, with a split, one output tile
-// of it (same radius and taps, its own halo).  PERSIST = false: one workgroup per queue slot,
-// the hardware dispatcher hands slots out in order as workgroups retire.
-// PERSIST = true: a grid sized to what the chip holds at once; workgroup b
-// takes slots b, b + grid, b + 2 grid, ... (round-robin over the cost-sorted
-// queue balances the load without atomics).
+// One workgroup per work item, in turn (PERSIST = false: handed out by the hardware dispatcher as workgroups
+// retire; PERSIST = true: a grid sized to what the chip holds at once, workgroup b taking items b,
+// b + grid, ...).
 template <typename TIn, typename TOut, typename TS, typename TC, bool PERSIST, bool ARGS>
-__global__ __launch_bounds__(kThreads) void fov_fwd_kernel(const FwdLaunch a, const int32_t* __restrict__ radius,
-                                                           const TC* __restrict__ wts,
-                                                           const int32_t* __restrict__ order,
-                                                           const FrameDesc* __restrict__ table,
+__global__ __launch_bounds__(kThreads) void fov_fwd_kernel(const FwdLaunch a, const FrameDesc* __restrict__ table,
                                                            const int32_t* __restrict__ prefix) {
     extern __shared__ __align__(16) unsigned char smem[];
     const Counts n = counts<ARGS>(a);
-    for (int q = blockIdx.x; q < n.nslots; q += gridDim.x) {
+    for (int i = blockIdx.x; i < n.nitems; i += gridDim.x) {
         Item it;
-        if (decode<ARGS>(a, order, table, prefix, n.nframes, q, &it)) {
+        if (decode<ARGS>(a, table, prefix, n, i, &it)) {
             it.F.fd = &frame_of<ARGS>(a, table, it.F.f);
-            process_fragment<TIn, TOut, TS, TC>(a.r_cap, a.strip_rows, it.r, it.F, it.c_lo, it.c_hi,
-                                                wts + (size_t)it.gid * a.wstride, smem);
+            process_fragment<TIn, TOut, TS, TC>(a.r_cap, a.strip_rows, it.r, it.sigma, it.F, it.c_lo, it.c_hi, smem);
         }
         if (!PERSIST) break;
         __syncthreads();  // this fragment's LDS reads are done before the next one is staged
@@ -507,12 +532,12 @@ __global__ __launch_bounds__(kThreads) void fov_fwd_kernel(const FwdLaunch a, co
 }
 
 // ---- 8-bit main kernel ---------------------------------------------------------------------------
-// 8-bit frames to 8-bit frames in launches of radius up to kFxRadius: one workgroup per queue slot, its
+// 8-bit frames to 8-bit frames in launches of radius up to kFxRadius: one workgroup per work item, its
 // tiles on the matrix cores (fixed.h); r = 0 is copied.
 //
 // The FP32 passes for a tile that the matrix cores leave.  A function of its own: it is rare, and inlined
 // it would take registers from the common path.
-__device__ __attribute__((noinline)) void fp32_tile(FrameDesc fd, const float* wg, int r_cap, int strip_rows, int r,
+__device__ __attribute__((noinline)) void fp32_tile(FrameDesc fd, double sigma, int r_cap, int strip_rows, int r,
                                                     int xa, int ya, int bw, int bh, int c_lo, int c_hi) {
     extern __shared__ __align__(16) unsigned char smem[];
     Frag P;
@@ -522,26 +547,22 @@ __device__ __attribute__((noinline)) void fp32_tile(FrameDesc fd, const float* w
     P.ya = ya;
     P.bw = bw;
     P.bh = bh;
-    process_fragment<uint8_t, uint8_t, _Float16, float>(r_cap, strip_rows, r, P, c_lo, c_hi, wg, smem);
+    process_fragment<uint8_t, uint8_t, _Float16, float>(r_cap, strip_rows, r, sigma, P, c_lo, c_hi, smem);
 }
 
 template <bool ARGS>
-__global__ __launch_bounds__(kThreads, 3) void fov_fwd_u8_kernel(const FwdLaunch a, const float* __restrict__ wts,
-                                                                 const int32_t* __restrict__ order,
-                                                                 const FrameDesc* __restrict__ table,
+__global__ __launch_bounds__(kThreads, 3) void fov_fwd_u8_kernel(const FwdLaunch a, const FrameDesc* __restrict__ table,
                                                                  const int32_t* __restrict__ prefix) {
     extern __shared__ __align__(16) unsigned char smem[];
     const Counts n = counts<ARGS>(a);
-    if ((int)blockIdx.x >= n.nslots) return;
     Item it;
-    if (!decode<ARGS>(a, order, table, prefix, n.nframes, blockIdx.x, &it)) return;
+    if ((int)blockIdx.x >= n.nitems || !decode<ARGS>(a, table, prefix, n, blockIdx.x, &it)) return;
     const FrameDesc& d = frame_of<ARGS>(a, table, it.F.f);
     it.F.fd = &d;
     if (it.r == 0) {
         copy_fragment<uint8_t, uint8_t>(it.F, it.c_lo, it.c_hi);
         return;
     }
-    const float* wg = wts + (size_t)it.gid * a.wstride;
     const int r = it.r, nk = fx_blocks(r);
     for (int c0 = it.c_lo; c0 < it.c_hi; c0 += kFxChan)
         for (int ty = 0; ty < it.F.bh; ty += kFxTile)
@@ -550,234 +571,14 @@ __global__ __launch_bounds__(kThreads, 3) void fov_fwd_u8_kernel(const FwdLaunch
                 const FxJob t{r, it.F.xa + tx, it.F.ya + ty, min(it.F.bw - tx, kFxTile), min(it.F.bh - ty, kFxTile), c0,
                               min(it.c_hi - c0, kFxChan)};
                 bool left;
-                if (nk == 2) left = fx_tile<2>(d, t, wg, smem);
-                else if (nk == 3) left = fx_tile<3>(d, t, wg, smem);
-                else left = fx_tile<4>(d, t, wg, smem);
+                if (nk == 2) left = fx_tile<2>(d, t, it.sigma, smem);
+                else if (nk == 3) left = fx_tile<3>(d, t, it.sigma, smem);
+                else left = fx_tile<4>(d, t, it.sigma, smem);
                 if (left) {
                     __syncthreads();
-                    fp32_tile(d, wg, a.r_cap, a.strip_rows, r, t.xa, t.ya, t.bw, t.bh, c0, c0 + t.nc);
+                    fp32_tile(d, it.sigma, a.r_cap, a.strip_rows, r, t.xa, t.ya, t.bw, t.bh, c0, c0 + t.nc);
                 }
             }
-}
-
-constexpr int kOrderThreads = 1024;
-constexpr int kOrderMaxRings = 1024;
-constexpr int kOrderCells = 12288;
-constexpr int kOrderHeld = 4096;  // items whose (key, radius word) the order kernel holds in LDS
-constexpr int kOrderBins = 16;  // angle bins per ring: one 16-lane segment of a wave scans a ring
-constexpr int kXcds = 8;
-
-// Rings (distinct radii) and angle bins of the order histogram.
-int order_rings(int r_cap) { return std::min(r_cap + 1, kOrderMaxRings); }
-int order_angle_bins(int nrings) { return std::max(1, std::min(kOrderBins, kOrderCells / nrings)); }
-
-__device__ __forceinline__ int angle_bin(const Frag& F, int nang) {
-    const FrameParams& fp = F.fd->p;
-    const float half = 0.5f * (float)(fp.block - 1);
-    const float cx = (float)(fp.origin_x + F.bx * fp.block) + half;
-    const float cy = (float)(fp.origin_y + F.by * fp.block) + half;
-    const float th = atan2f(cy - (float)fp.fix_y, cx - (float)fp.fix_x);  // (-pi, pi]
-    int b = (int)((th + 3.14159265f) * (float)nang * 0.159154943f);
-    return b < 0 ? 0 : (b >= nang ? nang - 1 : b);
-}
-
-// ---- plan kernels --------------------------------------------------------------------------------
-// Fragment plan: radius and normalised taps, one wavefront per fragment.
-template <typename TC>
-__global__ __launch_bounds__(64) void fov_plan_weights_kernel(const FwdLaunch a, int32_t* __restrict__ radius,
-                                                              int32_t* __restrict__ okey, int nrings, int nang,
-                                                              TC* __restrict__ wts) {
-    const int lane = threadIdx.x;
-    int nframes = a.nframes, nfrag = a.nfrag;
-    if (a.hdr) {
-        nframes = __builtin_amdgcn_readfirstlane(a.hdr[0]);
-        nfrag = __builtin_amdgcn_readfirstlane(a.hdr[1]);
-    }
-    for (int gid = blockIdx.x; gid < nfrag; gid += gridDim.x) {
-    Frag F;
-    if (a.from_args) F = frag_of<true>(a, a.table, a.prefix, nframes, gid);
-    else F = frag_of<false>(a, a.table, a.prefix, nframes, gid);
-    const FrameParams& fp = F.fd->p;
-    const double sigma = fp.sigma_map ? clip_map_sigma((double)fp.sigma_map[F.lb], fp.cap)
-                                      : fragment_sigma_ramp(fp, F.bx, F.by);
-    int r = radius_of(sigma);
-    if (r > a.r_cap) r = a.r_cap;  // the host sized everything for r_cap; plans agree bit for bit
-    // Vertical pairs at the cap (rows 2k and 2k+1, both sigma == cap, hence equal taps): the upper
-    // fragment's item covers both, the lower one gets no item.
-    int pair = 0;  // 1: upper of a merged pair, -1: lower
-    if (a.merge && r > 0 && sigma == fp.cap) {
-        const int by2 = F.by ^ 1;
-        if (by2 < F.fd->nby) {
-            const double s2 = fp.sigma_map ? clip_map_sigma((double)fp.sigma_map[F.lb + (by2 - F.by) * fp.nbx], fp.cap)
-                                           : fragment_sigma_ramp(fp, F.bx, by2);
-            if (s2 == fp.cap) pair = (F.by & 1) ? -1 : 1;
-        }
-    }
-    if (lane == 0) {
-        radius[gid] = r | (pair == 1 ? 0x10000 : 0);
-        okey[gid] = pair == -1 ? -1  // no queue slot
-                               : (nrings - 1 - min(r, nrings - 1)) * nang + angle_bin(F, nang);  // (ring, angle bin)
-    }
-    const int N = 2 * r + 1;
-    const double inv = r > 0 ? 1.0 / (2.0 * sigma * sigma) : 0.0;
-    constexpr int kHeld = 4;  // taps per lane kept in registers
-    double gv[kHeld];
-    double part = 0.0;
-#pragma unroll
-    for (int q = 0; q < kHeld; ++q) {
-        const int j = lane + 64 * q;
-        const double k = (double)(j - r);
-        gv[q] = j < N ? exp(-(k * k) * inv) : 0.0;
-        part += gv[q];
-    }
-    for (int j = lane + 64 * kHeld; j < N; j += 64) {
-        const double k = (double)(j - r);
-        part += exp(-(k * k) * inv);
-    }
-    for (int off = 32; off > 0; off >>= 1) part += __shfl_xor(part, off, 64);
-    TC* wr = wts + (size_t)gid * a.wstride;
-#pragma unroll
-    for (int q = 0; q < kHeld; ++q) {
-        const int j = lane + 64 * q;
-        if (j < a.wstride) wr[j] = (TC)(gv[q] / part);
-    }
-    for (int j = lane + 64 * kHeld; j < a.wstride; j += 64) {
-        double v = 0.0;
-        if (j < N) {
-            const double k = (double)(j - r);
-            v = exp(-(k * k) * inv) / part;
-        }
-        wr[j] = (TC)v;
-    }
-    }
-}
-
-// Queue order.  Work items go by decreasing radius (their cost grows with r),
-// so the costliest start first and the launch does not end on a long tail.
-// The items of a split fragment share its (ring, angle bin) cell.
-// Workgroup q runs on XCD q mod 8 (the dispatcher deals workgroups to the
-// eight XCDs in turn), and each XCD has its own L2: neighbouring fragments
-// share halo rows, so within every radius ring the fragments are sorted by
-// angle around their frame's fixation and cut into eight contiguous arcs, arc
-// a going to slots congruent to a mod 8.  Each XCD thus works through one
-// angular sector ring by ring, with an equal share of every ring.  Rings are
-// padded to a multiple of 8 slots with empty slots (-1).  With per-channel
-// items (cs_rmax >= 0) the rings of radius <= cs_rmax follow the rest of the
-// queue, each of their fragments in cmax consecutive slots of its arc's XCD
-// (one per channel).
-// One workgroup: LDS histogram over (ring, angle bin), scans, scatter; the
-// order inside one (ring, angle bin) cell is arbitrary and results do not
-// depend on it.  Up to kOrderHeld items keep their key and radius word in LDS
-// from the histogram pass to the scatter, so memory is read once.
-
-__global__ __launch_bounds__(kOrderThreads) void fov_order_kernel(const int32_t* __restrict__ okey,
-                                                                  const int32_t* __restrict__ radius, int n_arg,
-                                                                  int L, int nrings, int nang, int nslots_arg,
-                                                                  const int32_t* __restrict__ hdr,
-                                                                  int32_t* __restrict__ order, int cs_rmax,
-                                                                  int cmax) {
-    const int n = (hdr ? hdr[1] : n_arg) << (2 * L);  // work items
-    const int nslots = hdr ? hdr[2] : nslots_arg;
-    __shared__ int cells[kOrderCells];        // [ring][angle bin], ring 0 = largest radius
-    __shared__ int ring_n[kOrderMaxRings];    // fragments per ring
-    __shared__ int ring_base[kOrderMaxRings]; // first slot of each ring (multiple of 8)
-    __shared__ int chan_base[kOrderMaxRings]; // split rings: first slot of each after the queue
-    __shared__ int total_slots, total_extra;
-    __shared__ int2 held[kOrderHeld];         // (key, radius word) per item when n <= kOrderHeld
-    // rings whose fragments (r <= cs_rmax) are split by channel: ring >= small0
-    const int small0 = (cs_rmax >= 0 && cmax > 1) ? max(nrings - 1 - cs_rmax, 0) : nrings;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int ncell = nrings * nang;
-    for (int i = tid; i < ncell; i += kOrderThreads) cells[i] = 0;
-    __syncthreads();
-    const bool hold = n <= kOrderHeld;
-    for (int i = tid; i < n; i += kOrderThreads) {
-        const int key = okey[i >> (2 * L)];
-        if (hold) held[i] = make_int2(key, radius[i >> (2 * L)]);
-        if (key >= 0) atomicAdd(&cells[key], 1);  // -1: the lower fragment of a merged pair
-    }
-    __syncthreads();
-    // exclusive scan of the angle bins inside each ring: 16-lane segments, four rings per wave
-    // (nang <= kOrderBins)
-    for (int ring = wave * 4 + (lane >> 4); ring < nrings; ring += kOrderThreads / 16) {
-        const int b = lane & 15;
-        const bool live = ring < nrings && b < nang;
-        const int v = live ? cells[ring * nang + b] : 0;
-        int incl = v;
-        for (int off = 1; off < 16; off <<= 1) {
-            const int t = __shfl_up(incl, off, 16);
-            if (b >= off) incl += t;
-        }
-        if (live) cells[ring * nang + b] = incl - v;
-        if (ring < nrings && b == 15) ring_n[ring] = incl;
-    }
-    __syncthreads();
-    if (wave == 0) {
-        // ring bases: each ring takes 8 * ceil(n_ring / 8) slots (split rings go after the queue)
-        int carry = 0;
-        for (int r0 = 0; r0 < nrings; r0 += 64) {
-            const int ring = r0 + lane;
-            const int v = ring < small0 ? round_up(ring_n[ring], kXcds) : 0;
-            int incl = v;
-            for (int off = 1; off < 64; off <<= 1) {
-                const int t = __shfl_up(incl, off, 64);
-                if (lane >= off) incl += t;
-            }
-            if (ring < nrings) ring_base[ring] = carry + incl - v;
-            carry += __shfl(incl, 63, 64);
-        }
-        if (lane == 0) total_slots = carry;
-    } else if (wave == 1) {
-        // split rings after the queue, ring by ring: cmax slots per fragment
-        int carry = 0;
-        for (int r0 = small0; r0 < nrings; r0 += 64) {
-            const int ring = r0 + lane;
-            const int v = ring < nrings ? round_up(ring_n[ring], kXcds) * cmax : 0;
-            int incl = v;
-            for (int off = 1; off < 64; off <<= 1) {
-                const int t = __shfl_up(incl, off, 64);
-                if (lane >= off) incl += t;
-            }
-            if (ring < nrings) chan_base[ring] = carry + incl - v;
-            carry += __shfl(incl, 63, 64);
-        }
-        if (lane == 0) total_extra = carry;
-    }
-    __syncthreads();
-    int2* ord = reinterpret_cast<int2*>(order);
-    for (int i = tid; i < n; i += kOrderThreads) {
-        const int2 kr = hold ? held[i] : make_int2(okey[i >> (2 * L)], radius[i >> (2 * L)]);
-        const int key = kr.x;
-        if (key < 0) continue;
-        const int rr = kr.y;
-        const int ring = key / nang;
-        const int j = atomicAdd(&cells[key], 1);  // rank in the ring
-        const int m = ring_n[ring];
-        const int arc = (j * kXcds) / m;                  // arc a holds ranks [ceil(a m/8), ceil((a+1) m/8))
-        const int k = j - (arc * m + kXcds - 1) / kXcds;  // rank inside the arc
-        if (ring < small0) {
-            ord[ring_base[ring] + kXcds * k + arc] = make_int2(i, rr);
-        } else {  // one slot per channel, consecutive slots of the same XCD
-            const int e = total_slots + chan_base[ring] + kXcds * k * cmax + arc;
-            for (int ch = 0; ch < cmax; ++ch) ord[e + kXcds * ch] = make_int2(i | kChanItem | (ch << kChanShift), rr);
-        }
-    }
-    // empty slots: arc a of a ring of m holds ceil((a+1)m/8) - ceil(a m/8) fragments, ceil(m/8)
-    // or one fewer, so each arc leaves at most its last slot empty (eight lanes per ring)
-    for (int ring = tid >> 3; ring < nrings; ring += kOrderThreads / kXcds) {
-        const int arc = tid & (kXcds - 1);
-        const int m = ring_n[ring], per = (m + kXcds - 1) / kXcds;
-        const int sz = ((arc + 1) * m + kXcds - 1) / kXcds - (arc * m + kXcds - 1) / kXcds;
-        if (sz == per) continue;
-        const int k = per - 1;
-        if (ring < small0) {
-            ord[ring_base[ring] + kXcds * k + arc] = make_int2(-1, 0);
-        } else {
-            const int e = total_slots + chan_base[ring] + kXcds * k * cmax + arc;
-            for (int ch = 0; ch < cmax; ++ch) ord[e + kXcds * ch] = make_int2(-1, 0);
-        }
-    }
-    for (int q = total_slots + total_extra + tid; q < nslots; q += kOrderThreads) ord[q] = make_int2(-1, 0);
 }
 
 // Device plan for foveate_plan(): sigma and radius only.
@@ -791,22 +592,20 @@ __global__ void fov_plan_kernel(FrameParams fp, int n, double* sigma_out, int32_
 }
 
 template <typename TIn, typename TOut, typename TS, typename TC, bool PERSIST, bool ARGS>
-fov_status launch_main(const FwdLaunch& a, size_t lds, const PlanBuffers& plan, hipStream_t stream,
+fov_status launch_main(const FwdLaunch& a, size_t lds, hipStream_t stream,
                        size_t lds_limit, int cus, hipEvent_t ev_start, hipEvent_t ev_stop) {
     auto kern = fov_fwd_kernel<TIn, TOut, TS, TC, PERSIST, ARGS>;
     fov_status st = allow_dyn_lds((const void*)kern, lds_limit);
     if (st != FOV_OK) return st;
-    int grid = a.nslots;
-    if (PERSIST) grid = std::max(1, std::min(a.nslots, std::max(occupancy_of((const void*)kern, lds), 1) * cus));
+    int grid = a.nitems;
+    if (PERSIST) grid = std::max(1, std::min(a.nitems, std::max(occupancy_of((const void*)kern, lds), 1) * cus));
     if (ev_start || ev_stop) {
         // The dispatch itself stamps the events: no separate event packets (each would leave a
         // gap of several microseconds between the kernels of the stream).
         hipExtLaunchKernelGGL(kern, dim3(grid), dim3(kThreads), lds, stream, ev_start, ev_stop, 0, a,
-                              (const int32_t*)plan.radius, (const TC*)plan.weights, (const int32_t*)plan.order,
                               (const FrameDesc*)a.table, (const int32_t*)a.prefix);
     } else {
-        hipLaunchKernelGGL(kern, dim3(grid), dim3(kThreads), lds, stream, a, (const int32_t*)plan.radius,
-                           (const TC*)plan.weights, (const int32_t*)plan.order, (const FrameDesc*)a.table,
+        hipLaunchKernelGGL(kern, dim3(grid), dim3(kThreads), lds, stream, a, (const FrameDesc*)a.table,
                            (const int32_t*)a.prefix);
     }
     const hipError_t e = hipGetLastError();
@@ -815,70 +614,37 @@ fov_status launch_main(const FwdLaunch& a, size_t lds, const PlanBuffers& plan, 
 }
 
 template <bool ARGS>
-fov_status launch_u8(const FwdLaunch& a, size_t lds, const PlanBuffers& plan, hipStream_t stream, size_t lds_limit,
-                     hipEvent_t ev_start, hipEvent_t ev_stop) {
+fov_status launch_u8(const FwdLaunch& a, size_t lds, hipStream_t stream, size_t lds_limit, hipEvent_t ev_start,
+                     hipEvent_t ev_stop) {
     auto kern = fov_fwd_u8_kernel<ARGS>;
     fov_status st = allow_dyn_lds((const void*)kern, lds_limit);
     if (st != FOV_OK) return st;
-    const dim3 grid(a.nslots);
-    const auto args = [&](auto&& launch) {
-        launch(a, (const float*)plan.weights, (const int32_t*)plan.order, (const FrameDesc*)a.table, (const int32_t*)a.prefix);
-    };
     if (ev_start || ev_stop)
-        args([&](auto... x) { hipExtLaunchKernelGGL(kern, grid, dim3(kThreads), lds, stream, ev_start, ev_stop, 0, x...); });
+        hipExtLaunchKernelGGL(kern, dim3(a.nitems), dim3(kThreads), lds, stream, ev_start, ev_stop, 0, a,
+                              (const FrameDesc*)a.table, (const int32_t*)a.prefix);
     else
-        args([&](auto... x) { hipLaunchKernelGGL(kern, grid, dim3(kThreads), lds, stream, x...); });
+        hipLaunchKernelGGL(kern, dim3(a.nitems), dim3(kThreads), lds, stream, a, (const FrameDesc*)a.table,
+                           (const int32_t*)a.prefix);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_error(e, "forward kernel launch");
     return FOV_OK;
 }
 
 template <typename TIn, typename TOut, typename TS, typename TC>
-fov_status launch_typed(const FwdLaunch& a, size_t lds, const PlanBuffers& plan, hipStream_t stream,
-                        size_t lds_limit, int cus, bool persist, hipEvent_t ev_start, hipEvent_t ev_stop) {
-    TC* wts = static_cast<TC*>(plan.weights);
-    const int nrings = order_rings(a.r_cap), nang = order_angle_bins(nrings);
-    const int plan_grid = a.hdr ? std::min(a.nfrag, 8192) : a.nfrag;
-    hipLaunchKernelGGL(fov_plan_weights_kernel<TC>, dim3(plan_grid), dim3(64), 0, stream, a, plan.radius, plan.okey,
-                       nrings, nang, wts);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return hip_error(e, "plan kernel launch");
-    hipLaunchKernelGGL(fov_order_kernel, dim3(1), dim3(kOrderThreads), 0, stream, (const int32_t*)plan.okey,
-                       (const int32_t*)plan.radius, a.nfrag,
-                       a.split_log2, nrings, nang, a.nslots, a.hdr, plan.order, a.cs_rmax, a.cmax);
-    e = hipGetLastError();
-    if (e != hipSuccess) return hip_error(e, "order kernel launch");
+fov_status launch_typed(const FwdLaunch& a, size_t lds, hipStream_t stream, size_t lds_limit, int cus, bool persist,
+                        hipEvent_t ev_start, hipEvent_t ev_stop) {
     if constexpr (std::is_same<TOut, uint8_t>::value)
         if (forward_fixed(FOV_U8, FOV_U8, a.r_cap))
-            return (a.from_args ? launch_u8<true> : launch_u8<false>)(a, lds, plan, stream, lds_limit, ev_start, ev_stop);
+            return (a.from_args ? launch_u8<true> : launch_u8<false>)(a, lds, stream, lds_limit, ev_start, ev_stop);
     const auto main = a.from_args ? (persist ? launch_main<TIn, TOut, TS, TC, true, true> : launch_main<TIn, TOut, TS, TC, false, true>)
                                   : (persist ? launch_main<TIn, TOut, TS, TC, true, false> : launch_main<TIn, TOut, TS, TC, false, false>);
-    return main(a, lds, plan, stream, lds_limit, cus, ev_start, ev_stop);
+    return main(a, lds, stream, lds_limit, cus, ev_start, ev_stop);
 }
 
 int stage_size(int in_dtype) { return in_dtype == FOV_U8 ? 2 : (in_dtype == FOV_F32 ? 4 : 8); }
 int compute_size(int in_dtype) { return in_dtype == FOV_F64 ? 8 : 4; }
 
 }  // namespace
-
-int queue_slots(int nitems, int r_cap) { return nitems + kXcds * order_rings(r_cap); }
-
-int queue_slots_by_channel(int nfrag, int r_cap, int cmax) { return cmax * queue_slots(nfrag, r_cap); }
-
-size_t plan_bytes(int nfrag, int nslots, int wstride, int wsize) {
-    return 2 * align16((size_t)nfrag * 4) + align16((size_t)nslots * 8) + 256 + (size_t)nfrag * wstride * wsize;
-}
-
-PlanBuffers carve_plan(void* ws, int nfrag, int nslots) {
-    PlanBuffers p;
-    char* base = static_cast<char*>(ws);
-    const size_t f4 = align16((size_t)nfrag * 4);
-    p.radius = reinterpret_cast<int32_t*>(base);
-    p.okey = reinterpret_cast<int32_t*>(base + f4);
-    p.order = reinterpret_cast<int32_t*>(base + 2 * f4);
-    p.weights = base + 2 * f4 + align16((size_t)nslots * 8) + 256;
-    return p;
-}
 
 int forward_strip_max() { return kStripMax; }
 
@@ -902,18 +668,18 @@ size_t forward_lds_bytes(int in_dtype, int out_dtype, int r_cap, int tile_w, int
     return std::max(fp32, (size_t)fx_lds(fx_blocks(r_cap), kFxChan).total);
 }
 
-fov_status launch_forward(const FwdLaunch& a, int in_dtype, int out_dtype, size_t lds, const PlanBuffers& plan,
-                          hipStream_t stream, size_t lds_limit, int cus, bool persist, hipEvent_t ev_start,
+fov_status launch_forward(const FwdLaunch& a, int in_dtype, int out_dtype, size_t lds, hipStream_t stream,
+                          size_t lds_limit, int cus, bool persist, hipEvent_t ev_start,
                           hipEvent_t ev_stop) {
     if (a.nfrag <= 0) return FOV_OK;
     if (in_dtype == FOV_U8 && out_dtype == FOV_U8)
-        return launch_typed<uint8_t, uint8_t, _Float16, float>(a, lds, plan, stream, lds_limit, cus, persist, ev_start, ev_stop);
+        return launch_typed<uint8_t, uint8_t, _Float16, float>(a, lds, stream, lds_limit, cus, persist, ev_start, ev_stop);
     if (in_dtype == FOV_U8 && out_dtype == FOV_F32)
-        return launch_typed<uint8_t, float, _Float16, float>(a, lds, plan, stream, lds_limit, cus, persist, ev_start, ev_stop);
+        return launch_typed<uint8_t, float, _Float16, float>(a, lds, stream, lds_limit, cus, persist, ev_start, ev_stop);
     if (in_dtype == FOV_F32 && out_dtype == FOV_F32)
-        return launch_typed<float, float, float, float>(a, lds, plan, stream, lds_limit, cus, persist, ev_start, ev_stop);
+        return launch_typed<float, float, float, float>(a, lds, stream, lds_limit, cus, persist, ev_start, ev_stop);
     if (in_dtype == FOV_F64 && out_dtype == FOV_F64)
-        return launch_typed<double, double, double, double>(a, lds, plan, stream, lds_limit, cus, persist, ev_start, ev_stop);
+        return launch_typed<double, double, double, double>(a, lds, stream, lds_limit, cus, persist, ev_start, ev_stop);
     return set_error(FOV_EDTYPE, "unsupported dtype pair");
 }
 

@@ -20,7 +20,7 @@ struct DeviceInfo {
 };
 fov_status device_info(const DeviceInfo** out);
 
-// Per-(device, stream) workspace: device buffer for plans and frame tables,
+// Per-(device, stream) workspace: device buffer for frame tables and adjoint windows,
 // pinned host buffer for table uploads (see abi.cpp).
 struct Workspace {
     std::mutex mu;  // held by a call from lookup (and any growth) until its launches are enqueued
@@ -57,7 +57,7 @@ struct LaunchCfg {
     int strip_rows = 64;
     bool persistent = false;
     int merge = -1;  // vertical pairs at the cap as one item: 1 on, 0 off, -1 on unless it lowers occupancy
-    int chan_split = -1;  // small radii one item per channel: 1 on, 0 off, -1 on (several channels)
+    int chan_split = -1;  // one item per channel: 1 on, 0 off, -1 by kernel
 };
 
 // What a forward call launches: largest radius and fragment side, fragments.
@@ -82,22 +82,21 @@ fov_status collect_single(const fov_tensor* in, const fov_tensor* out, const fov
                           std::vector<FrameDesc>* frames, int* dt_in, int* dt_out);
 fov_status collect_batch(const fov_tensor* ins, const fov_tensor* outs, const fov_params* ps, int32_t nframes,
                          std::vector<FrameDesc>* frames, int* dt_in, int* dt_out);
-// Plan, order and main kernels for a list of frames on `stream`, with the
-// given configuration (NULL: select_cfg).  profile: take the thread's
-// profiler events, if any, for the main kernel.
+// The forward kernel for a list of frames on `stream`, with the given
+// configuration (NULL: select_cfg).  profile: take the thread's profiler
+// events, if any.
 fov_status run_forward(const std::vector<FrameDesc>& frames, int in_dtype, int out_dtype, hipStream_t stream,
                        const LaunchCfg* cfg = nullptr, bool profile = true);
 
-// The launch shape of one forward call (run_forward in two steps, for callers
-// that bring their own plan workspace).
+// The launch shape of one forward call (run_forward in two steps).
 struct ForwardPlan {
     FwdLaunch a;                        // counts and sizes; the frame table is placed by launch_planned
     std::vector<int32_t> prefix_table;  // first fragment of each frame (nframes + 1 entries) when
                                         // nframes > kArgFrames; otherwise they are in a.kprefix
     const int32_t* prefix() const { return a.nframes > kArgFrames ? prefix_table.data() : a.kprefix; }
     size_t lds = 0;               // dynamic LDS per workgroup
-    size_t pbytes = 0;            // plan workspace bytes (radii, order keys, queue, taps)
-    size_t tbytes = 0;            // frame table bytes, placed after the plan workspace
+    size_t tbytes = 0;            // frame table bytes to upload (0: the frames travel in a.fr)
+    size_t plan_bytes = 0;        // size of the fragments' plans written out (noalloc's limit)
     size_t lds_limit = 0;
     int cus = 0;
     bool persistent = false;
@@ -105,6 +104,6 @@ struct ForwardPlan {
 fov_status plan_forward(const FrameDesc* frames, int nf, int in_dtype, int out_dtype, const LaunchCfg* cfg,
                         ForwardPlan* fp);
 fov_status launch_planned(const FrameDesc* frames, int nf, int in_dtype, int out_dtype, ForwardPlan& fp,
-                          void* scratch, Workspace* ws, hipStream_t stream, bool profile);
+                          Workspace* ws, hipStream_t stream, bool profile);
 
 }  // namespace fov

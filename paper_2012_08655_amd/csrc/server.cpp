@@ -57,7 +57,7 @@ struct Slot {
     // graph replay
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
-    void* dev = nullptr;    // plan workspace + staged batch table
+    void* dev = nullptr;    // staged batch table
     void* host = nullptr;   // pinned copy of the staged batch table
     size_t stage_bytes = 0;
     hipGraphNode_t main_node = nullptr;  // the main kernel's node: its grid is set per batch
@@ -151,21 +151,16 @@ void fake_device_loop(ServerImpl* s) {
 }
 
 // Capacity launch of the replayable batch step of one slot.
-FwdLaunch capacity_launch(const ServerImpl* s, const Slot& sl, PlanBuffers* plan, bool merge) {
+FwdLaunch capacity_launch(const ServerImpl* s, const Slot& sl, bool merge) {
     FwdLaunch a;
     std::memset(&a, 0, sizeof(a));
-    a.merge = merge ? 1 : 0;
-    a.cs_rmax = -1;  // whole fragments: batch sizes vary per replay
+    a.merge = merge ? 1 : 0;  // whole fragments: batch sizes vary per replay
     a.nframes = s->cfg.max_batch_frames;
     a.nfrag = s->cfg.max_fragments;
-    a.nslots = queue_slots(a.nfrag, s->r_cap);
+    a.nitems = a.nfrag;
     a.r_cap = s->r_cap;
     a.strip_rows = choose_strip_rows();
-    a.wstride = round_up(2 * s->r_cap + 1, 16);
-    const int wsize = s->cfg.in_dtype == FOV_F64 ? 8 : 4;
-    const size_t pbytes = (plan_bytes(a.nfrag, a.nslots, a.wstride, wsize) + 255) / 256 * 256;
-    *plan = carve_plan(sl.dev, a.nfrag, a.nslots);
-    char* stage = static_cast<char*>(sl.dev) + pbytes;
+    char* stage = static_cast<char*>(sl.dev);
     a.hdr = reinterpret_cast<const int32_t*>(stage);
     a.table = reinterpret_cast<FrameDesc*>(stage + sizeof(BatchHeader));
     a.prefix = reinterpret_cast<int32_t*>(stage + sizeof(BatchHeader) + (size_t)a.nframes * sizeof(FrameDesc));
@@ -180,12 +175,8 @@ fov_status build_graph(ServerImpl* s, Slot& sl) {
     const DeviceInfo* dev = nullptr;
     fov_status st = device_info(&dev);
     if (st != FOV_OK) return st;
-    const int wsize = s->cfg.in_dtype == FOV_F64 ? 8 : 4;
-    const int nslots = queue_slots(s->cfg.max_fragments, s->r_cap);
-    const int wstride = round_up(2 * s->r_cap + 1, 16);
-    const size_t pbytes = (plan_bytes(s->cfg.max_fragments, nslots, wstride, wsize) + 255) / 256 * 256;
     sl.stage_bytes = stage_bytes_of(s->cfg);
-    hipError_t e = hipMalloc(&sl.dev, pbytes + sl.stage_bytes);
+    hipError_t e = hipMalloc(&sl.dev, sl.stage_bytes);
     if (e != hipSuccess) return set_error(FOV_ENOMEM, "server workspace allocation failed");
     e = hipHostMalloc(&sl.host, sl.stage_bytes, hipHostMallocDefault);
     if (e != hipSuccess) return set_error(FOV_ENOMEM, "server staging allocation failed");
@@ -200,14 +191,13 @@ fov_status build_graph(ServerImpl* s, Slot& sl) {
                        forward_occupancy(s->cfg.in_dtype, s->cfg.out_dtype, s->r_cap, lds2) >=
                            forward_occupancy(s->cfg.in_dtype, s->cfg.out_dtype, s->r_cap, lds);
     if (merge) lds = lds2;
-    PlanBuffers plan;
-    const FwdLaunch a = capacity_launch(s, sl, &plan, merge);
+    const FwdLaunch a = capacity_launch(s, sl, merge);
     e = hipStreamBeginCapture(sl.stream, hipStreamCaptureModeThreadLocal);
     if (e != hipSuccess) return hip_error(e, "hipStreamBeginCapture");
     e = hipMemcpyAsync(const_cast<int32_t*>(a.hdr), sl.host, sl.stage_bytes, hipMemcpyHostToDevice, sl.stream);
     st = e == hipSuccess ? FOV_OK : hip_error(e, "hipMemcpyAsync(batch table)");
     if (st == FOV_OK)
-        st = launch_forward(a, s->cfg.in_dtype, s->cfg.out_dtype, lds, plan, sl.stream, dev->lds_limit, dev->cus, false);
+        st = launch_forward(a, s->cfg.in_dtype, s->cfg.out_dtype, lds, sl.stream, dev->lds_limit, dev->cus, false);
     if (st == FOV_OK) {
         e = hipLaunchHostFunc(sl.stream, on_batch_done, &sl);
         if (e != hipSuccess) st = hip_error(e, "hipLaunchHostFunc");
@@ -220,8 +210,8 @@ fov_status build_graph(ServerImpl* s, Slot& sl) {
     }
     if (e2 != hipSuccess) return hip_error(e2, "hipStreamEndCapture");
     sl.graph = g;
-    // The main kernel was captured with one workgroup per slot of the largest
-    // batch; each replay sets its grid to the batch's own slot count.
+    // The main kernel was captured with one workgroup per item of the largest
+    // batch; each replay sets its grid to the batch's own item count.
     const void* main_fn = forward_main_kernel(s->cfg.in_dtype, s->cfg.out_dtype, s->r_cap);
     size_t nnodes = 0;
     e = hipGraphGetNodes(g, nullptr, &nnodes);
@@ -262,7 +252,7 @@ fov_status launch_batch(ServerImpl* s, Slot& sl, const std::vector<FrameDesc>& f
     }
     if (s->cfg.use_graph) {
         char* h = static_cast<char*>(sl.host);
-        BatchHeader hdr{(int32_t)frames.size(), nfrag, queue_slots(nfrag, s->r_cap), 0};
+        BatchHeader hdr{(int32_t)frames.size(), nfrag, nfrag, 0};
         std::memcpy(h, &hdr, sizeof(hdr));
         std::memcpy(h + sizeof(BatchHeader), frames.data(), frames.size() * sizeof(FrameDesc));
         int32_t* pre = reinterpret_cast<int32_t*>(h + sizeof(BatchHeader) + (size_t)s->cfg.max_batch_frames * sizeof(FrameDesc));
@@ -272,7 +262,7 @@ fov_status launch_batch(ServerImpl* s, Slot& sl, const std::vector<FrameDesc>& f
             acc += frames[i].p.nbx * frames[i].nby;
         }
         pre[frames.size()] = acc;
-        sl.main_params.gridDim = dim3((unsigned)hdr.nslots);
+        sl.main_params.gridDim = dim3((unsigned)hdr.nitems);
         hipError_t e = hipGraphExecKernelNodeSetParams(sl.exec, sl.main_node, &sl.main_params);
         if (e != hipSuccess) return hip_error(e, "hipGraphExecKernelNodeSetParams");
         e = hipGraphLaunch(sl.exec, sl.run);

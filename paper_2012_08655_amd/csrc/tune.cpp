@@ -110,26 +110,29 @@ fov_tuning to_public(const LaunchCfg& c, float us) {
 // Every configuration that fits the device's LDS for this call.  Strip heights
 // at or above the tallest padded tile behave alike; only the smallest such is
 // kept.  Splits stop at tiles of 8 pixels, and calls with enough fragments to
-// fill the chip several times over are not split (more halo work for nothing;
-// their work-item counts also make the single-workgroup order pass slow).
+// fill the chip several times over are not split (more halo work for
+// nothing).  The matrix-core kernel of 8-bit output has the split alone.
 constexpr int64_t kSplitMaxFragments = 4096;
 std::vector<LaunchCfg> candidates(const DeviceInfo& dev, int in_dtype, int out_dtype, const CallShape& cs) {
     std::vector<LaunchCfg> out;
+    const bool fixed = forward_fixed(in_dtype, out_dtype, cs.r_cap);
     for (int L = 0; L <= 2; ++L) {
         const int tile = (cs.bmax + (1 << L) - 1) >> L;
         if (L > 0 && (tile < 8 || tile == cs.bmax || cs.nfrag >= kSplitMaxFragments)) break;
         for (int merge : {0, 1}) {
-            if (merge && (L > 0 || cs.r_cap == 0)) continue;
+            if (merge && (fixed || L > 0 || cs.r_cap == 0)) continue;
             const int th = merge ? 2 * tile : tile;
             const int rows = forward_tile_rows(cs.r_cap, th);
             int prev = -1;
             for (int sr : {16, 32, 64}) {
+                if (fixed && sr != 64) continue;
                 const int eff = std::min(sr, rows);
                 if (eff == prev) continue;
                 prev = eff;
                 if (forward_lds_bytes(in_dtype, out_dtype, cs.r_cap, tile, th, sr) + 64 > dev.lds_limit) continue;
                 for (bool persist : {false, true})
                     for (int chan : {0, 1}) {
+                        if (fixed && (persist || chan)) continue;
                         if (chan && (L > 0 || cs.c < 2 || cs.c > 16)) continue;
                         LaunchCfg c;
                         c.split_log2 = L;
