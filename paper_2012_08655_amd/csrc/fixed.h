@@ -22,7 +22,7 @@
 //
 // Bound.  Let V be the exact value for the FP32 taps, N = 2r + 1.
 //  * |v - V| <= e1 =
-//      1.01 * 255 N 2^-F              taps, each off by at most 2^-(F+1), in both passes
+//      1.01 * 255 * 2 sum |w - W 2^-F|  taps, in both passes
 //    + 2^-(Q+1) + 2^-(F-8)            the intermediate is cut (not rounded) to 2^-Q; half of
 //                                     that is added back in v
 //    + 1.01 * N 2^(23-F-Q)            products left out, digits at most 128 in size
@@ -35,8 +35,7 @@
 //    the centre tap on by u 2^m each; the r before the centre by u 2^m each or,
 //    as their partial sums are at most 255 times the sum of the taps so far,
 //    by 255 M in total, M = sum_{j > 0} j w_j (symmetric taps).  Together
-//    (2^m <= v, 2^m <= 128)
-//      e2 = 1.02 u (2 (r + 1) min(v, 128) + min(128 r, 255 M)).
+//      e2 = 1.02 u ((r + 1) (min(v, 128) + 2^m) + min(128 r, 255 M)).
 // |v - rint(v)| <= 1/2 - e1 - e2 then decides the byte.  For frames of random
 // content about 2 (e1 + e2) of the pixels are left: 1.6 in a thousand at r = 48.
 //
@@ -68,7 +67,9 @@ constexpr int kFxChan = 3;     // channels staged together
 // of them (an image of many exact half-integer means, such as a one-pixel
 // checkerboard) is handed to the FP32 passes as a whole.
 constexpr int kFxCap = 32;
-constexpr int kFxBatch = 5;  // undecided pixels recomputed together (three workgroups' LDS fit a CU)
+// Undecided pixels recomputed together: what the LDS beside the planes holds when three workgroups share a
+// CU (four-block windows), else more than a tile usually has.
+__host__ __device__ constexpr int fx_batch(int nk) { return nk == 4 ? 5 : 16; }
 
 typedef int v4i __attribute__((ext_vector_type(4)));
 typedef int v16i __attribute__((ext_vector_type(16)));
@@ -105,7 +106,7 @@ __host__ __device__ constexpr FxLds fx_lds(int nk, int nchan) {
     l.misc = l.ws + (16 * (nk - 1) + 4) * 4;
     l.list = l.misc + 32;
     l.digits = l.list + kFxCap * 2;
-    const int dig = 12 * fx_digits(nk), cols = kFxBatch * fx_col(nk) * 4;
+    const int dig = 12 * fx_digits(nk), cols = fx_batch(nk) * fx_col(nk) * 4;
     l.tile = l.digits + ((dig > cols ? dig : cols) + 15) / 16 * 16;
     l.total = l.tile + nchan * fx_plane(nk) + 32;  // the recomputation reads up to two words past a row
     return l;
@@ -373,7 +374,9 @@ __device__ __forceinline__ bool fx_channel(const unsigned char* plane, const v4i
     const auto byte = [&](int i) {
         const float v = fmaf((float)(L3[i] * 256 + L2[i]), s3, fmaf((float)L4[i], s4, bias));
         const float n = v + kRound;
-        und = und + und + (fmaf(e2, fminf(v, 128.0f), fabsf(v - (n - kRound))) <= lim ? 0u : 1u);
+        const float t = n - kRound, p2 = __uint_as_float(__float_as_uint(t) & 0x7f800000u);  // 2^m, or the next one
+        const float off_by = fmaf(e2, p2, fmaf(e2, fminf(v, 128.0f), fabsf(v - t)));
+        und = und + und + (off_by <= lim ? 0u : 1u);
         return (uint8_t)__float_as_uint(n);
     };
     if (full) {
@@ -411,8 +414,8 @@ __device__ __forceinline__ void fx_recompute(const FrameDesc& d, int r, int xa, 
                                              const uint16_t* list, int count, int tid) {
     const int N = 2 * r + 1;
     const float w0s = w[r] * kSymScale;
-    for (int p0 = 0; p0 < count; p0 += kFxBatch) {
-        const int np = min(kFxBatch, count - p0);
+    for (int p0 = 0; p0 < count; p0 += fx_batch(NK)) {
+        const int np = min(fx_batch(NK), count - p0);
         const float rnp = 1.0f / (float)np;
         for (int t = tid; t < np * N; t += kThreads) {
             const int k = (int)(((float)t + 0.5f) * rnp), p = t - k * np;  // lanes of a row apart: fewer bank conflicts
@@ -447,7 +450,7 @@ __device__ __forceinline__ void fx_recompute(const FrameDesc& d, int r, int xa, 
                                                     (int64_t)(xa + (px & 31)) * d.osw] =
                 (uint8_t)__float_as_uint(acc + 12582912.0f);  // 0 <= acc < 255.5
         }
-        if (p0 + kFxBatch < count) __syncthreads();  // the columns are read
+        if (p0 + fx_batch(NK) < count) __syncthreads();  // the columns are read
     }
 }
 
@@ -485,11 +488,14 @@ __device__ __forceinline__ bool fx_tile(const FrameDesc& d, const FxJob& t, doub
         const float w0 = (float)(1.0 / tp.sum);  // tap r
         int F = 22 - ilogbf(w0);
         if (ldexpf(w0, F) > 8355000.0f) --F;
+        float off = 0.0f;  // |w 2^F - W|, summed over this lane's taps
         int W = 0, M = 0;  // this lane's taps in units of 2^-F; its part of M in units of 2^(8-F), rounded up
         const auto put_tap = [&](int i, double e) {
             const float t = (float)(e / tp.sum);
             w[i] = t;
-            const int v = (int)rintf(ldexpf(t, F));
+            const float tf = ldexpf(t, F);
+            const int v = (int)rintf(tf);
+            off += fabsf(tf - (float)v);
             W += v;
             if (i > r) {
                 ws[i - r - 1] = t * kSymScale;
@@ -506,12 +512,12 @@ __device__ __forceinline__ bool fx_tile(const FrameDesc& d, const FxJob& t, doub
         };
         if (lane < N) put_tap(lane, tp.e0);
         if (lane + 64 < N) put_tap(lane + 64, tp.e1);
-        const double both = wave_sum((double)W), m = wave_sum((double)M);
+        const double both = wave_sum((double)W), m = wave_sum((double)M), offs = wave_sum((double)off);
         if (lane == 0) {
             const int Q = min(16, F - 8);
             const double sw = ldexp(both, -F);  // sum of the taps
             const float fN = (float)N, u = 1.02f * 5.9604645e-8f;
-            const float e1 = 1.01f * 255.0f * ldexpf(fN, -F) + ldexpf(1.0f, -Q - 1) + ldexpf(1.0f, 8 - F) +
+            const float e1 = 1.01f * 510.0f * ldexpf((float)offs, -F) + ldexpf(1.0f, -Q - 1) + ldexpf(1.0f, 8 - F) +
                              1.01f * ldexpf(fN, 23 - F - Q) + 3.0517578e-5f;
             const float eM = u * fminf(128.0f * (float)r, 255.0f * ldexpf((float)m, 8 - F));
             head->F = F;
@@ -536,7 +542,7 @@ __device__ __forceinline__ bool fx_tile(const FrameDesc& d, const FxJob& t, doub
     if (ch < t.nc) {
         global_ptr<uint8_t> o = as_global(static_cast<uint8_t*>(d.out)) + (int64_t)(t.c0 + ch) * d.osc +
                                 (int64_t)t.ya * d.osh + (int64_t)t.xa * d.osw;
-        const bool ok = fx_channel<NK>(tile + ch * fx_plane(NK), T, *head, 2.0f * 1.02f * 5.9604645e-8f * (float)(r + 1),
+        const bool ok = fx_channel<NK>(tile + ch * fx_plane(NK), T, *head, 1.02f * 5.9604645e-8f * (float)(r + 1),
                                        t.bw, t.bh, o, d.osh, d.osw, ch, list, lane);
         if (!ok && lane == 0) head->over = 1;
     }
