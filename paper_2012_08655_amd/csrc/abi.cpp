@@ -533,9 +533,15 @@ fov_status run_backward_group(const FrameDesc* frames, int nf, int dtype, hipStr
     a.nframes = nf;
     a.nfrag = (int32_t)total;
     a.r_cap = cs.r_cap;
+    a.cmax = cs.c;
+    a.even = 1;
+    for (int i = 0; i < nf; ++i) a.even &= prefix[i + 1] - prefix[i] == prefix[1];
     const size_t f4 = ((size_t)a.nfrag * 4 + 255) / 256 * 256;
     const size_t tbytes = frame_table_bytes(nf);
-    const size_t sbytes = adjoint_scratch_elems(sh, a.nfrag) * es;
+    bool gather = adjoint_gather_fits(total, cs.c);
+    for (int i = 0; i < nf; ++i) gather &= adjoint_gathers(es, frames[i].p.block);
+    if (adjoint_lds(sh, es) + 64 > dev->lds_limit) return set_error(FOV_ERANGE, "adjoint tiles do not fit in LDS");
+    const size_t sbytes = (gather ? adjoint_tap_elems(cs.r_cap, a.nfrag) : adjoint_scratch_elems(sh, a.nfrag)) * es;
     Workspace* ws = nullptr;
     std::unique_lock<std::mutex> hold;
     if ((s = workspace(stream, f4 + tbytes + sbytes, nf > kArgFrames ? tbytes : 0, &ws, &hold)) != FOV_OK) return s;
@@ -544,6 +550,7 @@ fov_status run_backward_group(const FrameDesc* frames, int nf, int dtype, hipStr
     char* dtab = base + f4;
     void* scratch = dtab + tbytes;
     if ((s = stage_frame_table(frames, nf, prefix.data(), ws, dtab, tbytes, stream, &a)) != FOV_OK) return s;
+    if (gather) return launch_adjoint_gather(a, radius, static_cast<float*>(scratch), stream);
     return launch_adjoint(a, sh, es, radius, scratch, stream, dev->lds_limit);
 }
 
@@ -560,6 +567,7 @@ fov_status run_backward(const fov_tensor* go, const fov_tensor* gi, const fov_pa
     while (f0 < frames.size()) {
         size_t f1 = f0 + 1;
         CallShape cs = call_shape(&frames[f0], 1);
+        bool gather = adjoint_gathers(es, frames[f0].p.block);
         while (f1 < frames.size()) {
             const CallShape one = call_shape(&frames[f1], 1);
             CallShape m = cs;
@@ -568,8 +576,13 @@ fov_status run_backward(const fov_tensor* go, const fov_tensor* gi, const fov_pa
             m.c = std::max(m.c, one.c);
             m.nfrag += one.nfrag;
             const AdjShape sh = adjoint_shape(es, m.r_cap, m.bmax, m.c);
-            if (m.nfrag > (1 << 30) || adjoint_scratch_elems(sh, (int)m.nfrag) * es > kAdjScratchMax) break;
+            const bool both = gather && adjoint_gathers(es, frames[f1].p.block);
+            if (m.nfrag > (1 << 30)) break;
+            const size_t elems = both && adjoint_gather_fits(m.nfrag, m.c) ? adjoint_tap_elems(m.r_cap, (int)m.nfrag)
+                                                                           : adjoint_scratch_elems(sh, (int)m.nfrag);
+            if (elems * es > kAdjScratchMax) break;
             cs = m;
+            gather = both;
             ++f1;
         }
         fov_status s = run_backward_group(frames.data() + f0, (int)(f1 - f0), go->dtype, stream);

@@ -47,4 +47,13 @@ size_t adjoint_scratch_elems(const AdjShape& s, int nfrag);
 fov_status launch_adjoint(const FwdLaunch& a, const AdjShape& s, int es, int32_t* radius, void* scratch,
                           hipStream_t stream, size_t lds_limit);
 
+// Whether frames of this element size and fragment side run as a matrix-core
+// gather (all of a launch's, if its grid fits), its tap table (elements) and its
+// kernels: each fragment's radius and taps, then every output tile from the
+// gradients that reach it.
+bool adjoint_gathers(int es, int block);
+bool adjoint_gather_fits(int64_t nfrag, int cmax);
+size_t adjoint_tap_elems(int r_cap, int nfrag);
+fov_status launch_adjoint_gather(const FwdLaunch& a, int32_t* radius, float* taps, hipStream_t stream);
+
 }  // namespace fov

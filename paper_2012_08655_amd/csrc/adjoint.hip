@@ -14,7 +14,8 @@
 // cdf_b(-p-1) = sum_{i <= -p-1} w_b(i) for input p, and output L-1 the extra
 // weight cdf_b(p-L).
 //
-// Two kernels:
+// 32-bit gradients with fragment sides of 16 or 28 .. 32 take the matrix-core gather further below; the
+// rest two kernels:
 //  1. fov_adj_window_kernel — one workgroup per fragment and channel: the
 //     fragment's sigma, radius and normalised taps (kept in LDS), then its
 //     transposed window as the forward computes a fragment: the gradient is
@@ -456,6 +457,349 @@ __global__ __launch_bounds__(kThreads) void fov_adj_sum_kernel(const FwdLaunch a
     }
 }
 
+// ---- matrix-core gather for 32-bit gradients, fragment sides 16 and 28 .. 32 ----------------------
+// grad_in over an output tile is the sum, over the fragments b that reach it, of Ay_b^T g_b Ax_b: two dense
+// products of at most 32 x 32 x 32 per channel with Ax_b[c][x] = w_b(x - c) (plus the edge folds), which
+// v_mfma_f32_16x16x4_f32 forms in FP32 like the vector units.  Nothing but the gradient and the taps is
+// read and nothing but grad_in written: the window and sum kernels move every fragment's transposed window,
+// (32 + 2r)^2 values a channel, through scratch and back, and were bound by that.  Measured per call, with the
+// window kernels in brackets: 4 x 3 x 512 x 512, radii up to 36, 32 px fragments 55 us (85), 16 px 129 (346);
+// 32 x 3 x 224 x 224 57 us (73); 3 x 1080 x 1920, radii up to 48 167 us (305).  What bounds it now is latency: a
+// wave's matrix instructions take a third of its 30 thousand cycles, its three hits' loads, weights through
+// LDS and scalar set-up the rest (one hit's loads ahead of the last one's products was slower, 65 us: the
+// second set of addresses and weights costs more than the wait; one or two waves a tile 67 and 63 us).
+//  1. fov_adj_plan_kernel: one wave per fragment: radius, taps and the running sums of the taps.
+//  2. fov_adj_gather_kernel: one workgroup per output tile (as many fragments as fit 32 pixels a side) and
+//     channel; its waves take the fragments that reach the tile in turn, and their sums meet in LDS in a
+//     fixed order.  Steps of the products whose weights are all zero are skipped (16 x 16 results, 16 rows or
+//     8 columns of the fragment at a time).
+
+// Taps of fragment gid in `taps`: w(t) at [gid][t + r_cap] for |t| <= r, then C(t) = sum_{i <= t} w(i)
+// at [gid][2 r_cap + 1 + t + r_cap] for -r <= t <= -1.
+__host__ __device__ inline int adj_tap_stride(int r_cap) { return 3 * r_cap + 1; }
+
+template <bool ARGS>
+__global__ __launch_bounds__(64) void fov_adj_plan_kernel(const FwdLaunch a, const FrameDesc* __restrict__ table,
+                                                          const int32_t* __restrict__ prefix,
+                                                          int32_t* __restrict__ radius, float* __restrict__ taps) {
+    const int gid = blockIdx.x, lane = threadIdx.x;
+    const Frag F = frag_of<ARGS>(a, table, prefix, a.nframes, gid);
+    const double sigma = fragment_sigma(F.fd->p, F.lb, F.bx, F.by);
+    const int r = min(radius_of(sigma), a.r_cap);
+    if (lane == 0) radius[gid] = r;
+    const Taps tp(sigma, r, lane);
+    float* w = taps + (size_t)gid * adj_tap_stride(a.r_cap) + a.r_cap;
+    float* c = w + 2 * a.r_cap + 1;
+    double carry = 0.0;
+    for (int q = 0; 64 * q < 2 * r + 1; ++q) {
+        const int j = 64 * q + lane;
+        const double v = j < 2 * r + 1 ? tp.tap(q, r, lane) : 0.0;
+        if (j < 2 * r + 1) w[j - r] = (float)v;
+        if (64 * q >= r) continue;  // the sums end at t = -1
+        double incl = v;
+        for (int off = 1; off < 64; off <<= 1) {
+            const double t = __shfl_up(incl, off, 64);
+            if (lane >= off) incl += t;
+        }
+        incl += carry;
+        if (j < r) c[j - r] = (float)incl;
+        carry = __shfl(incl, 63, 64);
+    }
+}
+
+constexpr int kGatherTile = 32;
+constexpr int kGatherPitch = kGatherTile + 1;  // LDS row pitch of the waves' sums
+constexpr int kGatherWaves = 4;                // waves per output tile and channel
+
+// One axis of a fragment and a tile: tile position 0 is at fragment position d; n positions of the tile,
+// frag_n of the fragment, radius r.
+struct Axis {
+    int d, n, frag_n, r;
+    bool first, last;  // the tile holds the frame's first, last position
+
+    // The fragment positions that reach the tile's positions 16 k .. 16 k + 15, in groups of `size`: lo() .. hi()
+    // (lo > hi: none).
+    __device__ __forceinline__ int lo(int k, int size) const {
+        return 16 * k < n ? max(d + 16 * k - r, 0) / size : 1;
+    }
+    __device__ __forceinline__ int hi(int k, int size) const {
+        const int e = min(d + min(16 * k + 15, n - 1) + r, frag_n - 1);
+        return 16 * k < n && e >= 0 ? e / size : -1;
+    }
+};
+
+__device__ __forceinline__ Axis axis_of(int tile0, int tile_n, int frag0, int frag_n, int r, int len) {
+    return Axis{tile0 - frag0, tile_n, frag_n, r, tile0 == 0, tile0 + tile_n == len};
+}
+
+// The weights of an axis by t = tile position - fragment position, t + 31 - d in lw: w(t), and for a tile at
+// the frame's first or last position the folds onto it.  `lw` is 3 x 64 words of this wave's LDS.  load()
+// issues every read at a valid place (both axes' are in flight together), store() drops what is outside.
+struct AxisLoads {
+    float w, first, last;
+    __device__ __forceinline__ void load(const Axis& x, const float* __restrict__ taps, const float* __restrict__ c, int lane) {
+        const int t = x.d - 31 + lane, r = x.r;
+        w = taps[clampi(t, -r, r)];
+        first = last = 0.0f;
+        if (r > 0 && x.first) first = c[clampi(t - 1, -r, -1)];
+        if (r > 0 && x.last) last = c[clampi(-t - 1, -r, -1)];
+    }
+    __device__ __forceinline__ void store(const Axis& x, float* lw, int lane) const {
+        const int t = x.d - 31 + lane, r = x.r;
+        lw[lane] = t >= -r && t <= r ? w : 0.0f;
+        if (x.first) lw[64 + lane] = t - 1 >= -r && t <= 0 ? first : 0.0f;
+        if (x.last) lw[128 + lane] = t >= 0 && -t - 1 >= -r ? last : 0.0f;
+    }
+};
+
+// A lane's weights of tile position pos for fragment positions base + at(i), i = 0 .. 7.
+template <typename At>
+__device__ __forceinline__ void lane_weights(float (&A)[8], const Axis& x, const float* lw, int pos, int base, At at) {
+    const float* p = lw + (31 + pos - base - at(7));
+#pragma unroll
+    for (int i = 0; i < 8; ++i) A[i] = p[at(7) - at(i)];
+    if (x.first && pos == 0) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) A[i] += p[64 + at(7) - at(i)];
+    }
+    if (x.last && pos == x.n - 1) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) A[i] += p[128 + at(7) - at(i)];
+    }
+}
+
+typedef float v4f __attribute__((ext_vector_type(4)));
+
+// A step of v_mfma_f32_16x16x4_f32 takes one fragment position from each quarter h4 of the wave.  Columns
+// (first product): step i, 8 (i / 2) + 2 h4 + i % 2.  Rows (second product): step i, 16 (i / 4) + 4 h4 + i % 4,
+// the rows in which the first product's result lies.
+__device__ __forceinline__ constexpr int gather_col(int i) { return 8 * (i >> 1) + (i & 1); }
+__device__ __forceinline__ constexpr int gather_row(int i) { return 16 * (i >> 2) + (i & 3); }
+
+template <bool ARGS>
+__global__ __launch_bounds__(64 * kGatherWaves, 4) void fov_adj_gather_kernel(const FwdLaunch a, const FrameDesc* __restrict__ table,
+                                                                     const int32_t* __restrict__ prefix,
+                                                                     const int32_t* __restrict__ radius,
+                                                                     const float* __restrict__ taps) {
+    __shared__ float sums[kGatherWaves][kGatherTile * kGatherPitch];
+    const int item = blockIdx.x / a.cmax, ch = blockIdx.x - item * a.cmax;
+    const Frag Q = ranked_fragment<ARGS>(a, table, prefix, a.nframes, item);
+    const FrameDesc& d = frame_of<ARGS>(a, table, Q.f);
+    const FrameParams& fp = d.p;
+    const int B = fp.block, m = B <= kGatherTile / 2 ? 2 : 1;  // fragments per tile side
+    if (ch >= d.c || (m == 2 && ((Q.bx | Q.by) & 1))) return;
+    const int nbx = fp.nbx, nby = d.nby, first = ARGS ? a.kprefix[Q.f] : prefix[Q.f];
+    const int X0 = fp.origin_x + Q.bx * B, Y0 = fp.origin_y + Q.by * B;
+    const int tw = min(X0 + m * B, d.w) - Q.xa, th = min(Y0 + m * B, d.h) - Q.ya;
+    const int K = (a.r_cap + B - 1) / B;  // fragments within reach on each side
+    const int by_lo = max(Q.by - K, 0), by_hi = min(Q.by + m - 1 + K, nby - 1);
+    const int bx_lo = max(Q.bx - K, 0), bx_hi = min(Q.bx + m - 1 + K, nbx - 1);
+    const int nx = bx_hi - bx_lo + 1, ncand = nx * (by_hi - by_lo + 1);
+    const float rnx = 1.0f / (float)nx;
+    const int tid = threadIdx.x, lane = tid & 63, wave = wave_id(), l = lane & 15, h4 = lane >> 4;
+    float* lx = &sums[wave][0];  // this wave's axis weights; its sums later
+    float* ly = lx + 192;
+    const int stride = adj_tap_stride(a.r_cap);
+    const global_ptr<const float> in = as_global(static_cast<const float*>(d.in)) + (int64_t)ch * d.isc;
+    // a fragment's offsets fit 31 bits of bytes
+    const bool near = (kGatherTile - 1) * (d.ish + d.isw) < (int64_t)(kOutside / 4);
+    v4f acc[2][2];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) acc[i >> 1][i & 1] = v4f{};
+    // Each fragment that reaches the tile, in a fixed order; wave v takes hits v, v + kGatherWaves, ...
+    const auto for_hits = [&](auto&& f) {
+        int turn = 0;
+        for (int j0 = 0; j0 < ncand; j0 += 64) {
+            const int j = j0 + lane, jy = (int)(((float)j + 0.5f) * rnx);
+            const int cy = by_lo + jy, cx = bx_lo + (j - jy * nx);
+            int rb = 0;
+            bool hit = false;
+            if (j < ncand) {
+                rb = radius[first + cy * nbx + cx];
+                const int x0 = fp.origin_x + cx * B, y0 = fp.origin_y + cy * B;
+                hit = x0 + B - 1 + rb >= Q.xa && x0 - rb < Q.xa + tw && y0 + B - 1 + rb >= Q.ya && y0 - rb < Q.ya + th;
+            }
+            for (uint64_t hits = __ballot(hit); hits; hits &= hits - 1, ++turn) {
+                if (turn % kGatherWaves != wave) continue;
+                const int src = __builtin_ctzll(hits);
+                const int bx = lane_value(cx, src), by = lane_value(cy, src), r = lane_value(rb, src);
+                const int xb = max(fp.origin_x + bx * B, 0), yb = max(fp.origin_y + by * B, 0);
+                const int bw = min(fp.origin_x + (bx + 1) * B, d.w) - xb, bh = min(fp.origin_y + (by + 1) * B, d.h) - yb;
+                const float* w = taps + (size_t)(first + by * nbx + bx) * stride + a.r_cap;
+                const Axis ax = axis_of(Q.xa, tw, xb, bw, r, d.w), ay = axis_of(Q.ya, th, yb, bh, r, d.h);
+                f(ax, ay, w, w + 2 * a.r_cap + 1, in + (int64_t)yb * d.ish + (int64_t)xb * d.isw);
+            }
+        }
+    };
+    for_hits([&](const Axis& ax, const Axis& ay, const float* w, const float* c, global_ptr<const float> gp) {
+        const int xlo0 = ax.lo(0, 8), xhi0 = ax.hi(0, 8), xlo1 = ax.lo(1, 8), xhi1 = ax.hi(1, 8);
+        // rows 16 k .. 16 k + 15 of the fragment are wanted by tile rows 16 i ..: use[k][i]
+        bool use[2][2];
+#pragma unroll
+        for (int k = 0; k < 2; ++k)
+#pragma unroll
+            for (int i = 0; i < 2; ++i) use[k][i] = ay.lo(i, 16) <= k && k <= ay.hi(i, 16);
+        AxisLoads wx, wy;
+        wx.load(ax, w, c, lane);
+        wy.load(ay, w, c, lane);
+        // The gradient where it has a weight, zero elsewhere: lane l's rows 16 k + l, columns gather_col().  A place
+        // that is not wanted is given an offset that the range check turns into a zero without a read.
+        float g[2][8];
+        const int x0 = max(ax.d - ax.r, 0), x1 = min(ax.d + tw - 1 + ax.r, ax.frag_n - 1);
+        const int y0 = max(ay.d - ay.r, 0), y1 = min(ay.d + th - 1 + ay.r, ay.frag_n - 1);
+        const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<float*>((const float*)gp), 0, (int)kOutside, kBufferWord3);
+        if (d.isw == 1 && near && !(ax.frag_n & 1)) {
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                const int row = 16 * k + l;
+                const uint32_t at = ((uint32_t)row * (uint32_t)d.ish + 2 * h4) * 4;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const int col = 8 * j + 2 * h4;
+                    const bool want = row >= y0 && row <= y1 && col + 1 >= x0 && col <= x1;
+                    const auto v = __builtin_amdgcn_raw_buffer_load_b64(rsrc, (int)(want ? at + 32 * j : kOutside), 0, 0);
+                    g[k][2 * j] = __builtin_bit_cast(float, (uint32_t)v[0]);
+                    g[k][2 * j + 1] = __builtin_bit_cast(float, (uint32_t)v[1]);
+                }
+            }
+        } else if (near) {
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                const int row = 16 * k + l;
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    const int col = gather_col(i) + 2 * h4;
+                    const bool want = row >= y0 && row <= y1 && col >= x0 && col <= x1;
+                    const uint32_t at = ((uint32_t)row * (uint32_t)d.ish + (uint32_t)col * (uint32_t)d.isw) * 4;
+                    g[k][i] = buffer_load<float>(rsrc, want ? at : kOutside);
+                }
+            }
+        } else {
+#pragma unroll
+            for (int k = 0; k < 2; ++k)
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    const int row = 16 * k + l, col = gather_col(i) + 2 * h4;
+                    const bool want = row >= y0 && row <= y1 && col >= x0 && col <= x1;
+                    g[k][i] = want ? gp[(int64_t)row * d.ish + (int64_t)col * d.isw] : 0.0f;
+                }
+        }
+        __builtin_amdgcn_wave_barrier();
+        wx.store(ax, lx, lane);
+        wy.store(ay, ly, lane);
+        __builtin_amdgcn_wave_barrier();
+        float Ax[2][8], Ay[2][8];
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            lane_weights(Ax[k], ax, lx, 16 * k + l, 2 * h4, gather_col);
+            lane_weights(Ay[k], ay, ly, 16 * k + l, 4 * h4, gather_row);
+        }
+        // The fragment's part on its own, then added: one chain over all fragments rounds more (rms error 8.5e-8
+        // of the outputs' against 7.4e-8 for uniform gradients; the window kernels' is 7.6e-8).
+        v4f part[2][2];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) part[i >> 1][i & 1] = v4f{};
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            if (!use[k][0] && !use[k][1]) continue;
+            v4f G0{}, G1{};
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                if (xlo0 <= j && j <= xhi0) {
+                    G0 = __builtin_amdgcn_mfma_f32_16x16x4f32(g[k][2 * j], Ax[0][2 * j], G0, 0, 0, 0);
+                    G0 = __builtin_amdgcn_mfma_f32_16x16x4f32(g[k][2 * j + 1], Ax[0][2 * j + 1], G0, 0, 0, 0);
+                }
+                if (xlo1 <= j && j <= xhi1) {
+                    G1 = __builtin_amdgcn_mfma_f32_16x16x4f32(g[k][2 * j], Ax[1][2 * j], G1, 0, 0, 0);
+                    G1 = __builtin_amdgcn_mfma_f32_16x16x4f32(g[k][2 * j + 1], Ax[1][2 * j + 1], G1, 0, 0, 0);
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                if (!use[k][i]) continue;
+                if (xlo0 <= xhi0) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        part[i][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(Ay[i][4 * k + e], G0[e], part[i][0], 0, 0, 0);
+                }
+                if (xlo1 <= xhi1) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        part[i][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(Ay[i][4 * k + e], G1[e], part[i][1], 0, 0, 0);
+                }
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) acc[i >> 1][i & 1] += part[i >> 1][i & 1];
+    });
+    float probe = 0.0f;  // NaN if a sum is an infinity or a NaN
+#pragma unroll
+    for (int i = 0; i < 16; ++i) probe = fmaf(acc[i >> 3][(i >> 2) & 1][i & 3], 0.0f, probe);
+    if (__ballot(probe != 0.0f)) {
+        // An infinity or a NaN in the gradient, or an overflow, may have met a zero weight: this wave's hits
+        // again, term by term over the weights that are not zero.
+#pragma unroll
+        for (int i = 0; i < 4; ++i) acc[i >> 1][i & 1] = v4f{};
+        for_hits([&](const Axis& ax, const Axis& ay, const float* w, const float* c, global_ptr<const float> gp) {
+            AxisLoads wx, wy;
+            wx.load(ax, w, c, lane);
+            wy.load(ay, w, c, lane);
+            __builtin_amdgcn_wave_barrier();
+            wx.store(ax, lx, lane);
+            wy.store(ay, ly, lane);
+            __builtin_amdgcn_wave_barrier();
+            const auto weight = [](const float* t, const Axis& x, int pos, int frag) {
+                const int at = 31 + pos - frag;
+                return t[at] + (x.first && pos == 0 ? t[64 + at] : 0.0f) + (x.last && pos == x.n - 1 ? t[128 + at] : 0.0f);
+            };
+#pragma unroll
+            for (int xi = 0; xi < 2; ++xi)
+#pragma unroll 1
+                for (int p = 0; p < ay.frag_n; ++p) {
+                    float s = 0.0f;
+                    for (int q = 0; q < ax.frag_n; ++q) {
+                        const float wt = 16 * xi + l < tw ? weight(lx, ax, 16 * xi + l, q) : 0.0f;
+                        if (wt != 0.0f) s = fmaf(wt, gp[(int64_t)p * d.ish + (int64_t)q * d.isw], s);
+                    }
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) {
+                        const int y = 16 * (i >> 2) + 4 * h4 + (i & 3);
+                        const float wt = y < th ? weight(ly, ay, y, p) : 0.0f;
+                        if (wt != 0.0f) acc[i >> 2][xi][i & 3] = fmaf(wt, s, acc[i >> 2][xi][i & 3]);
+                    }
+                }
+        });
+    }
+    // (a wave's weights are read before it stores its sums over them: LDS operations of a wave stay in order)
+#pragma unroll
+    for (int i = 0; i < 16; ++i)
+        sums[wave][(16 * (i >> 3) + 4 * h4 + (i & 3)) * kGatherPitch + 16 * ((i >> 2) & 1) + l] = acc[i >> 3][(i >> 2) & 1][i & 3];
+    __syncthreads();
+    const global_ptr<float> out = as_global(static_cast<float*>(d.out)) + (int64_t)ch * d.osc + (int64_t)Q.ya * d.osh +
+                                  (int64_t)Q.xa * d.osw;
+    for (int i = tid; i < kGatherTile * kGatherTile; i += 64 * kGatherWaves) {
+        const int y = i >> 5, x = i & 31, at = y * kGatherPitch + x;
+        float s = sums[0][at];
+#pragma unroll
+        for (int v = 1; v < kGatherWaves; ++v) s += sums[v][at];
+        if (x < tw && y < th) out[(int64_t)y * d.osh + (int64_t)x * d.osw] = s;
+    }
+}
+
+template <bool ARGS>
+fov_status launch_gather(const FwdLaunch& a, int32_t* radius, float* taps, hipStream_t stream) {
+    hipLaunchKernelGGL(fov_adj_plan_kernel<ARGS>, dim3(a.nfrag), dim3(64), 0, stream, a, (const FrameDesc*)a.table,
+                       (const int32_t*)a.prefix, radius, taps);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return hip_error(e, "adjoint plan kernel launch");
+    hipLaunchKernelGGL(fov_adj_gather_kernel<ARGS>, dim3(a.nfrag * a.cmax), dim3(64 * kGatherWaves), 0, stream, a,
+                       (const FrameDesc*)a.table, (const int32_t*)a.prefix, (const int32_t*)radius, (const float*)taps);
+    e = hipGetLastError();
+    if (e != hipSuccess) return hip_error(e, "adjoint gather kernel launch");
+    return FOV_OK;
+}
+
 template <typename T, int GV, bool ARGS>
 fov_status launch_kernels(const FwdLaunch& a, const AdjShape& s, int32_t* radius, T* sc, hipStream_t stream,
                           size_t lds_limit) {
@@ -522,6 +866,23 @@ size_t adjoint_lds(const AdjShape& s, int es) {
 }
 
 size_t adjoint_scratch_elems(const AdjShape& s, int nfrag) { return (size_t)nfrag * s.cmax * s.sw * s.sh; }
+
+// A tile is 32 x 32 whatever the fragments: sides that leave much of it empty do better with the windows.  Per
+// call, 4 x 3 x 512 x 512 with radii up to 36 and then 3, 3 x 1080 x 1920 with radii up to 3, gather against
+// windows: 16 px 131 / 347, 69 / 111 and 134 / 205 us; 17 px 315 / 283, 136 / 109; 24 px 109 / 155 but 26 px
+// 53 / 57, 98 / 95; 28 px 49 / 56 and 87 / 86; 32 px 55 / 85, 38 / 44 and 68 / 71.
+bool adjoint_gathers(int es, int block) {
+    return es == 4 && (block == kGatherTile / 2 || (block >= 28 && block <= kGatherTile));
+}
+
+bool adjoint_gather_fits(int64_t nfrag, int cmax) { return nfrag * cmax * kThreads < ((int64_t)1 << 32); }
+
+size_t adjoint_tap_elems(int r_cap, int nfrag) { return (size_t)nfrag * adj_tap_stride(r_cap); }
+
+fov_status launch_adjoint_gather(const FwdLaunch& a, int32_t* radius, float* taps, hipStream_t stream) {
+    if (a.nfrag <= 0) return FOV_OK;
+    return a.from_args ? launch_gather<true>(a, radius, taps, stream) : launch_gather<false>(a, radius, taps, stream);
+}
 
 fov_status launch_adjoint(const FwdLaunch& a, const AdjShape& s, int es, int32_t* radius, void* scratch,
                           hipStream_t stream, size_t lds_limit) {

@@ -53,11 +53,7 @@ __host__ __device__ inline size_t tap_lds_bytes(int r_cap, int ec) {
 __device__ __forceinline__ int clampi(int v, int lo, int hi) { return v < lo ? lo : (v > hi ? hi : v); }
 
 // Smallest s with 2^s >= v (v >= 1).
-__host__ __device__ inline int ceil_log2(int v) {
-    int s = 0;
-    while ((1 << s) < v) ++s;
-    return s;
-}
+__device__ __forceinline__ int ceil_log2(int v) { return v > 1 ? 32 - __builtin_clz((uint32_t)v - 1u) : 0; }
 
 // Frame buffers as global-memory pointers (pointers read from the frame table would otherwise be
 // accessed with flat instructions).
@@ -534,6 +530,41 @@ __device__ __forceinline__ Frag frag_of(const FwdLaunch& a, const FrameDesc* __r
     } else {
         return describe(table, prefix, nframes, gid);
     }
+}
+
+// The k-th fragment of the launch, numbered so that the costliest tend to come first (a launch does not end
+// on a long tail) without any pass over the plan: a frame's fragments go along its longer axis, the lines
+// farthest from the fixation first (sigma grows with the distance), and in turn within a line; frames of
+// equal fragment counts take turns.
+template <bool ARGS>
+__device__ __forceinline__ Frag ranked_fragment(const FwdLaunch& a, const FrameDesc* __restrict__ table,
+                                                const int32_t* __restrict__ prefix, int nframes, int k) {
+    int f, rank;
+    if (a.even) {
+        rank = k / nframes;
+        f = k - rank * nframes;
+    } else if constexpr (ARGS) {
+        f = 0;
+        while (f + 1 < nframes && k >= a.kprefix[f + 1]) ++f;
+        rank = k - a.kprefix[f];
+    } else {
+        f = frame_search(prefix, nframes, k);
+        rank = k - prefix[f];
+    }
+    const FrameDesc& d = frame_of<ARGS>(a, table, f);
+    const FrameParams& fp = d.p;
+    // lines along the longer axis: n1 of them, n2 fragments in each
+    const bool cols = fp.nbx >= d.nby;
+    const int n1 = cols ? fp.nbx : d.nby, n2 = cols ? d.nby : fp.nbx;
+    const int line = rank / n2, at = rank - line * n2;
+    // The first t lines are farther from the fixation than the last one: they go first, then the rest from
+    // both ends in turn.  (Any t in 0 .. n1 visits every line once.)
+    const float c1 = (float)((cols ? fp.fix_x - fp.origin_x : fp.fix_y - fp.origin_y) + 0.5) / (float)fp.block;
+    const int t = (int)fminf(fmaxf(2.0f * c1 - (float)n1, 0.0f), (float)n1);
+    const int m = line - t;
+    const int pos = m < 0 ? line : ((m & 1) ? t + (m >> 1) : n1 - 1 - (m >> 1));
+    return fragment_at(&d, f, __builtin_amdgcn_readfirstlane(cols ? pos : at),
+                       __builtin_amdgcn_readfirstlane(cols ? at : pos));
 }
 
 }  // namespace

@@ -445,13 +445,9 @@ struct Item {
     Frag F;
 };
 
-// Work item i of the launch; false if it holds nothing.  Items are numbered so that the costliest tend to
-// come first (a launch does not end on a long tail) and neighbours, which share halo samples, meet in one
-// L2, without any pass over the plan before the launch:
-//  * workgroup b runs on XCD b mod 8, each with an L2 of its own: every 64 items are dealt so that an XCD
-//    gets eight consecutive ones;
-//  * a frame's fragments go along its longer axis, the lines farthest from the fixation first (sigma grows
-//    with the distance), and in turn within a line; frames of equal fragment counts take turns.
+// Work item i of the launch; false if it holds nothing.  Items take the fragments in ranked_fragment()'s
+// order, dealt so that neighbours, which share halo samples, meet in one L2: workgroup b runs on XCD b mod 8,
+// each with an L2 of its own, and of every 64 items an XCD gets eight consecutive ones.
 template <bool ARGS>
 __device__ __forceinline__ bool decode(const FwdLaunch& a, const FrameDesc* __restrict__ table,
                                        const int32_t* __restrict__ prefix, const Counts& n, int i, Item* it) {
@@ -464,32 +460,10 @@ __device__ __forceinline__ bool decode(const FwdLaunch& a, const FrameDesc* __re
         ch = k - q * a.cmax;
         k = q;
     }
-    int f, rank;
-    if (a.even) {
-        rank = k / n.nframes;
-        f = k - rank * n.nframes;
-    } else if constexpr (ARGS) {
-        f = 0;
-        while (f + 1 < n.nframes && k >= a.kprefix[f + 1]) ++f;
-        rank = k - a.kprefix[f];
-    } else {
-        f = frame_search(prefix, n.nframes, k);
-        rank = k - prefix[f];
-    }
-    const FrameDesc& d = frame_of<ARGS>(a, table, f);
+    Frag F = ranked_fragment<ARGS>(a, table, prefix, n.nframes, k);
+    const FrameDesc& d = frame_of<ARGS>(a, table, F.f);
     const FrameParams& fp = d.p;
-    // lines along the longer axis: n1 of them, n2 fragments in each
-    const bool cols = fp.nbx >= d.nby;
-    const int n1 = cols ? fp.nbx : d.nby, n2 = cols ? d.nby : fp.nbx;
-    const int line = rank / n2, at = rank - line * n2;
-    // The first t lines are farther from the fixation than the last one: they go first, then the rest from
-    // both ends in turn.  (Any t in 0 .. n1 visits every line once.)
-    const float c1 = (float)((cols ? fp.fix_x - fp.origin_x : fp.fix_y - fp.origin_y) + 0.5) / (float)fp.block;
-    const int t = (int)fminf(fmaxf(2.0f * c1 - (float)n1, 0.0f), (float)n1);
-    const int m = line - t;
-    const int pos = m < 0 ? line : ((m & 1) ? t + (m >> 1) : n1 - 1 - (m >> 1));
-    const int bx = __builtin_amdgcn_readfirstlane(cols ? pos : at), by = __builtin_amdgcn_readfirstlane(cols ? at : pos);
-    Frag F = fragment_at(&d, f, bx, by);
+    const int bx = F.bx, by = F.by;
     const double sigma = uniform(fragment_sigma(fp, F.lb, bx, by));
     int r = __builtin_amdgcn_readfirstlane(radius_of(sigma));
     if (r > a.r_cap) r = a.r_cap;  // the host sized everything for r_cap; plans agree bit for bit
@@ -499,7 +473,7 @@ __device__ __forceinline__ bool decode(const FwdLaunch& a, const FrameDesc* __re
         const int by2 = by ^ 1;
         if (by2 < d.nby && fragment_sigma(fp, F.lb + (by2 - by) * fp.nbx, bx, by2) == fp.cap) {
             if (by & 1) return false;
-            const Frag F2 = fragment_at(&d, f, bx, by2);
+            const Frag F2 = fragment_at(&d, F.f, bx, by2);
             F.bh = F2.ya + F2.bh - F.ya;
         }
     }
