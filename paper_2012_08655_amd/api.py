@@ -11,6 +11,9 @@ float32 tensor of nby*nbx per-fragment sigmas replacing the ramp).
 from __future__ import annotations
 
 import ctypes
+import functools
+import operator
+import struct
 from typing import Mapping, Sequence
 
 import numpy as np
@@ -22,10 +25,16 @@ _DTYPES = {torch.uint8: N.FOV_U8, torch.float32: N.FOV_F32, torch.float64: N.FOV
 LAYOUTS = ("NCHW", "NHWC", "CHW", "HWC", "HW")
 
 
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream_handle(stream=None):
+    # The handle without a Stream object around it: 0.2 us against 2.9.
+    if stream is None and _raw_stream is not None and torch.cuda.is_initialized():
+        return _raw_stream(torch._C._cuda_getDevice())
     if stream is None:
         stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+    return stream.cuda_stream
 
 
 def tensor_desc(t: torch.Tensor, layout: str, host: bool = False) -> N.FovTensor:
@@ -68,9 +77,32 @@ def _params_array(params, n: int):
         plist = list(params)
         if len(plist) not in (1, n):
             raise ValueError("need one params dict per frame (or one shared)")
-    arr = (N.FovParams * max(len(plist), 1))()
     keep = []
-    for i, p in enumerate(plist):
+    return _pack_params(plist, keep), len(plist), keep
+
+
+_ALL = operator.itemgetter("fix_x", "fix_y", "e0", "slope", "cap", "block", "origin_x", "origin_y")
+
+
+def _with_defaults(p):
+    return (p["fix_x"], p["fix_y"], p["e0"], p["slope"], p["cap"], p.get("block", 32), p.get("origin_x", 0),
+            p.get("origin_y", 0))
+
+
+@functools.lru_cache(maxsize=64)
+def _packer(n: int) -> struct.Struct:
+    return struct.Struct("@" + "5d4iP" * n)  # n FovParams
+
+
+assert _packer(2).size == 2 * ctypes.sizeof(N.FovParams)
+
+
+def _pack_params(plist, keep: list):
+    """The dicts of ``plist`` in their C form, packed by one call: 0.4 us a frame against 1.0 through a FovParams
+    object each (a training batch converts its parameters twice per step).  What struct does not take as it
+    is, such as a float for ``block``, goes through make_params' conversions."""
+    vals, ptrs = [], []
+    for p in plist:
         sm = p.get("sigma_map")
         ptr = None
         if sm is not None:
@@ -78,8 +110,31 @@ def _params_array(params, n: int):
                 raise TypeError("sigma_map must be a contiguous CUDA float32 tensor")
             ptr = sm.data_ptr()
             keep.append(sm)
-        arr[i] = N.make_params(p, ptr)
-    return arr, len(plist), keep
+        try:
+            vals += _ALL(p) if type(p) is dict else _with_defaults(p)
+        except KeyError:  # one of the last three, or raised again here
+            vals += _with_defaults(p)
+        vals += 0, ptr or 0
+        ptrs.append(ptr)
+    arr = (N.FovParams * max(len(plist), 1))()
+    try:
+        _packer(len(plist)).pack_into(arr, 0, *vals)
+    except (struct.error, TypeError, OverflowError):
+        for i, p in enumerate(plist):
+            arr[i] = N.make_params(p, ptrs[i])
+    return arr
+
+
+def _frame_params(params, keep: list):
+    """One C form per entry of ``params`` (dicts, or lists of one dict)."""
+    return _pack_params([p if isinstance(p, Mapping) else _one(p) for p in params], keep)
+
+
+def _one(p):
+    p = list(p)
+    if len(p) != 1:
+        raise ValueError("need one params dict per frame (or one shared)")
+    return p[0]
 
 
 def _n_of(desc: N.FovTensor) -> int:
@@ -121,12 +176,8 @@ def forward_batch(frames, params, outs=None, layout: str = "HWC", out_dtype: tor
         outs = [torch.empty_like(f, dtype=out_dtype or f.dtype) for f in frames]
     di = (N.FovTensor * max(n, 1))(*[tensor_desc(f, layout) for f in frames])
     do = (N.FovTensor * max(n, 1))(*[tensor_desc(o, layout) for o in outs])
-    arr = (N.FovParams * max(n, 1))()
     keep = []
-    for i, p in enumerate(params):
-        a, _, k = _params_array(p, 1)
-        arr[i] = a[0]
-        keep.append(k)
+    arr = _frame_params(params, keep)
     N.check(N.lib().foveate_forward_batch(di, do, arr, n, _stream_handle(stream)))
     return outs
 
@@ -156,12 +207,8 @@ def autotune_batch(frames, params, outs, layout: str = "HWC", reps: int = 5, str
     n = len(frames)
     di = (N.FovTensor * max(n, 1))(*[tensor_desc(f, layout) for f in frames])
     do = (N.FovTensor * max(n, 1))(*[tensor_desc(o, layout) for o in outs])
-    arr = (N.FovParams * max(n, 1))()
     keep = []
-    for i, p in enumerate(params):
-        a, _, k = _params_array(p, 1)
-        arr[i] = a[0]
-        keep.append(k)
+    arr = _frame_params(params, keep)
     t = N.FovTuning()
     N.check(N.lib().foveate_autotune_batch(di, do, arr, n, int(reps), _stream_handle(stream), ctypes.byref(t)))
     return _tuning_dict(t)
