@@ -583,7 +583,9 @@ __global__ __launch_bounds__(64 * kGatherWaves, 4) void fov_adj_gather_kernel(co
                                                                      const float* __restrict__ taps) {
     __shared__ float sums[kGatherWaves][kGatherTile * kGatherPitch];
     const int item = blockIdx.x / a.cmax, ch = blockIdx.x - item * a.cmax;
-    const Frag Q = ranked_fragment<ARGS>(a, table, prefix, a.nframes, item);
+    int frame, rank;
+    ranked_frame<ARGS>(a, prefix, a.nframes, item, &frame, &rank);
+    const Frag Q = ranked_at(frame_of<ARGS>(a, table, frame), frame, rank);
     const FrameDesc& d = frame_of<ARGS>(a, table, Q.f);
     const FrameParams& fp = d.p;
     const int B = fp.block, m = B <= kGatherTile / 2 ? 2 : 1;  // fragments per tile side

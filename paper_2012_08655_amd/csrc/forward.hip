@@ -274,14 +274,15 @@ struct Stager<uint8_t, _Float16> {
 // Narrow a fragment to output tile `sub` of its L-level split: tiles of
 // T = ceil(B / 2^L) pixels a side, row-major, clipped to the fragment and the
 // frame.  Returns false for a tile that holds no pixel (ragged splits).
-__device__ __forceinline__ bool narrow_to_tile(Frag& F, int L, int sub) {
+template <typename D>
+__device__ __forceinline__ bool narrow_to_tile(Frag& F, const D& d, int L, int sub) {
     if (L == 0) return true;
-    const FrameParams& fp = F.fd->p;
+    const FrameParams& fp = d.p;
     const int B = fp.block, T = (B + (1 << L) - 1) >> L;
     const int sx = sub & ((1 << L) - 1), sy = sub >> L;
     const int X0 = fp.origin_x + F.bx * B, Y0 = fp.origin_y + F.by * B;
     const int x0 = X0 + sx * T, y0 = Y0 + sy * T;
-    const int x1 = min(min(x0 + T, X0 + B), F.fd->w), y1 = min(min(y0 + T, Y0 + B), F.fd->h);
+    const int x1 = min(min(x0 + T, X0 + B), d.w), y1 = min(min(y0 + T, Y0 + B), d.h);
     F.xa = max(x0, 0);
     F.ya = max(y0, 0);
     F.bw = x1 - F.xa;
@@ -467,45 +468,51 @@ struct Item {
     Frag F;
 };
 
-// Work item i of the launch; false if it holds nothing.  Items take the fragments in ranked_fragment()'s
-// order, dealt so that neighbours, which share halo samples, meet in one L2: workgroup b runs on XCD b mod 8,
-// each with an L2 of its own, and of every 64 items an XCD gets eight consecutive ones.
-template <bool ARGS>
+// Work item i of the launch; false if it holds nothing.  Items take the fragments in the order of
+// ranked_frame(), dealt so that neighbours, which share halo samples, meet in one L2: workgroup b runs on XCD
+// b mod 8, each with an L2 of its own, and of every 64 items an XCD gets eight consecutive ones.
+// FIXED: a launch of the 8-bit kernel, which has neither channel items nor pairs.
+template <bool ARGS, bool FIXED = false>
 __device__ __forceinline__ bool decode(const FwdLaunch& a, const FrameDesc* __restrict__ table,
                                        const int32_t* __restrict__ prefix, const Counts& n, int i, Item* it) {
     const int L = a.split_log2;
     if ((i | 63) < n.nitems) i = (i & ~63) | (i & 7) << 3 | (i >> 3 & 7);
     const int sub = i & ((1 << (2 * L)) - 1);
     int k = i >> (2 * L), ch = -1;
-    if (a.chan) {
+    if (!FIXED && a.chan) {
         const int q = k / a.cmax;
         ch = k - q * a.cmax;
         k = q;
     }
-    Frag F = ranked_fragment<ARGS>(a, table, prefix, n.nframes, k);
-    const FrameDesc& d = frame_of<ARGS>(a, table, F.f);
-    const FrameParams& fp = d.p;
-    const int bx = F.bx, by = F.by;
-    const double sigma = uniform(fragment_sigma(fp, F.lb, bx, by));
-    int r = __builtin_amdgcn_readfirstlane(radius_of(sigma));
-    if (r > a.r_cap) r = a.r_cap;  // the host sized everything for r_cap; plans agree bit for bit
-    // Vertical pairs at the cap (rows 2k and 2k+1, both sigma == cap, hence equal taps): the upper
-    // fragment's item covers both, the lower one's is empty.
-    if (a.merge && r > 0 && sigma == fp.cap) {
-        const int by2 = by ^ 1;
-        if (by2 < d.nby && fragment_sigma(fp, F.lb + (by2 - by) * fp.nbx, bx, by2) == fp.cap) {
-            if (by & 1) return false;
-            const Frag F2 = fragment_at(&d, F.f, bx, by2);
-            F.bh = F2.ya + F2.bh - F.ya;
+    int f, rank;
+    ranked_frame<ARGS>(a, prefix, n.nframes, k, &f, &rank);
+    const auto describe = [&](const auto& d) {
+        const FrameParams& fp = d.p;
+        Frag F = ranked_at(d, f, rank);
+        const int bx = F.bx, by = F.by;
+        const double sigma = uniform(fragment_sigma(fp, F.lb, bx, by));
+        int r = __builtin_amdgcn_readfirstlane(radius_of(sigma));
+        if (r > a.r_cap) r = a.r_cap;  // the host sized everything for r_cap; plans agree bit for bit
+        // Vertical pairs at the cap (rows 2k and 2k+1, both sigma == cap, hence equal taps): the upper
+        // fragment's item covers both, the lower one's is empty.
+        if (!FIXED && a.merge && r > 0 && sigma == fp.cap) {
+            const int by2 = by ^ 1;
+            if (by2 < d.nby && fragment_sigma(fp, F.lb + (by2 - by) * fp.nbx, bx, by2) == fp.cap) {
+                if (by & 1) return false;
+                const Frag F2 = fragment_at(d, f, bx, by2);
+                F.bh = F2.ya + F2.bh - F.ya;
+            }
         }
-    }
-    if (!narrow_to_tile(F, L, sub)) return false;
-    it->r = r;
-    it->sigma = sigma;
-    it->c_lo = max(ch, 0);
-    it->c_hi = ch < 0 ? d.c : min(ch + 1, d.c);
-    it->F = F;
-    return it->c_lo < it->c_hi;
+        if (!narrow_to_tile(F, d, L, sub)) return false;
+        it->r = r;
+        it->sigma = sigma;
+        it->c_lo = max(ch, 0);
+        it->c_hi = ch < 0 ? d.c : min(ch + 1, d.c);
+        it->F = F;
+        return it->c_lo < it->c_hi;
+    };
+    if constexpr (FIXED) return describe(geo_of<ARGS>(a, table, f));
+    else return describe(frame_of<ARGS>(a, table, f));
 }
 
 // One workgroup per work item, in turn (PERSIST = false: handed out by the hardware dispatcher as workgroups
@@ -552,7 +559,7 @@ __global__ __launch_bounds__(kThreads, 3) void fov_fwd_u8_kernel(const FwdLaunch
     extern __shared__ __align__(16) unsigned char smem[];
     const Counts n = counts<ARGS>(a);
     Item it;
-    if ((int)blockIdx.x >= n.nitems || !decode<ARGS>(a, table, prefix, n, blockIdx.x, &it)) return;
+    if ((int)blockIdx.x >= n.nitems || !decode<ARGS, true>(a, table, prefix, n, blockIdx.x, &it)) return;
     const FrameDesc& d = frame_of<ARGS>(a, table, it.F.f);
     it.F.fd = &d;
     if (it.r == 0) {
