@@ -225,7 +225,8 @@ fov_status foveate_backward(const fov_tensor* grad_out, const fov_tensor* grad_i
  *   chan_split : 1 = a fragment is one work item per channel (short, latency
  *                bound items: its channels then run side by side); needs split
  *                1 and at most 16 channels.  By default on for frames of
- *                several channels.
+ *                several channels in calls of fewer fragments than nine per
+ *                compute unit.
  * 8-bit output of radii up to 48 runs on a kernel of its own that takes a
  * fragment's channels together and follows `split` alone.
  *   time_us    : (output of foveate_autotune) median time of one call.

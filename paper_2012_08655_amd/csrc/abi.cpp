@@ -460,8 +460,14 @@ fov_status plan_forward(const FrameDesc* frames, int nf, int in_dtype, int out_d
     a.cmax = cs.c;
     a.even = 1;
     for (int i = 0; i < nf; ++i) a.even &= prefix[i + 1] - prefix[i] == prefix[1];
-    // one work item per channel, unless a configuration says otherwise
-    a.chan = !fixed && cfg.chan_split != 0 && L == 0 && cs.c > 1 && cs.c <= 16 &&
+    // One work item per channel where the fragments alone would not fill the chip several times over; above
+    // that an item's sigma, taps and geometry are worked out once for its channels, and a channel is loaded while
+    // the last one is computed.  A configuration may say otherwise.  Kernel time, items of one channel against
+    // items of three: 1024 fragments (4 x 3 x 512 x 512 f32) 45 / 54 us, 1568 (32 x 3 x 224 x 224 f32) 34 / 32, 2048 (8 x 3 x
+    // 512 x 512) 73 / 77, 2400 (16 x 3 x 317 x 451 u8 to f32) 54 / 54, 2888 (2 x 3 x 600 x 600, 16 px) f32 54 / 42 and f64
+    // 157 / 144, 4640 (8 x 3 x 317 x 451 u8 to f32, 16 px) 73 / 64.
+    const bool chan = cfg.chan_split > 0 || (cfg.chan_split < 0 && cs.nfrag < (int64_t)9 * dev->cus);
+    a.chan = !fixed && chan && L == 0 && cs.c > 1 && cs.c <= 16 &&
              cs.nfrag * cs.c <= ((int64_t)1 << 30);
     a.nitems = a.chan ? a.nfrag * cs.c : a.nfrag << (2 * L);
     fp->lds = lds;
