@@ -463,11 +463,11 @@ __global__ __launch_bounds__(kThreads) void fov_adj_sum_kernel(const FwdLaunch a
 // v_mfma_f32_16x16x4_f32 forms in FP32 like the vector units.  Nothing but the gradient and the taps is
 // read and nothing but grad_in written: the window and sum kernels move every fragment's transposed window,
 // (32 + 2r)^2 values a channel, through scratch and back, and were bound by that.  Measured per call, with the
-// window kernels in brackets: 4 x 3 x 512 x 512, radii up to 36, 32 px fragments 55 us (85), 16 px 129 (346);
-// 32 x 3 x 224 x 224 57 us (73); 3 x 1080 x 1920, radii up to 48 167 us (305).  What bounds it now is latency: a
-// wave's matrix instructions take a third of its 30 thousand cycles, its three hits' loads, weights through
-// LDS and scalar set-up the rest (one hit's loads ahead of the last one's products was slower, 65 us: the
-// second set of addresses and weights costs more than the wait; one or two waves a tile 67 and 63 us).
+// window kernels in brackets: 4 x 3 x 512 x 512, radii up to 36, 32 px fragments 57 us (85), 16 px 125 (347);
+// 32 x 3 x 224 x 224 56 us (73); 3 x 1080 x 1920, radii up to 48 165 us (301).  Of a SIMD's time the matrix
+// instructions take 36 %, scalar instructions (a tile's and a hit's set-up, the skips) 40 %, vector ones 29 %; a
+// wave waits 40 % of its own.  Slower were: the next hit's loads ahead of this one's products (65 us: a second set of
+// addresses and weights costs more than the wait), and one or two waves a tile (67 and 63 us).
 //  1. fov_adj_plan_kernel: one wave per fragment: radius, taps and the running sums of the taps.
 //  2. fov_adj_gather_kernel: one workgroup per output tile (as many fragments as fit 32 pixels a side) and
 //     channel; its waves take the fragments that reach the tile in turn, and their sums meet in LDS in a
@@ -517,14 +517,11 @@ struct Axis {
     int d, n, frag_n, r;
     bool first, last;  // the tile holds the frame's first, last position
 
-    // The fragment positions that reach the tile's positions 16 k .. 16 k + 15, in groups of `size`: lo() .. hi()
-    // (lo > hi: none).
-    __device__ __forceinline__ int lo(int k, int size) const {
-        return 16 * k < n ? max(d + 16 * k - r, 0) / size : 1;
-    }
-    __device__ __forceinline__ int hi(int k, int size) const {
-        const int e = min(d + min(16 * k + 15, n - 1) + r, frag_n - 1);
-        return 16 * k < n && e >= 0 ? e / size : -1;
+    // The fragment positions that reach the tile's positions 16 k .. 16 k + 15: bit g for those of the g-th
+    // group of 2^size.
+    __device__ __forceinline__ uint32_t band(int k, int size) const {
+        const int lo = max(d + 16 * k - r, 0), hi = min(d + min(16 * k + 15, n - 1) + r, frag_n - 1);
+        return 16 * k < n && lo <= hi ? (2u << ((uint32_t)hi >> size)) - (1u << ((uint32_t)lo >> size)) : 0u;
     }
 };
 
@@ -558,6 +555,7 @@ __device__ __forceinline__ void lane_weights(float (&A)[8], const Axis& x, const
     const float* p = lw + (31 + pos - base - at(7));
 #pragma unroll
     for (int i = 0; i < 8; ++i) A[i] = p[at(7) - at(i)];
+    if (!x.first && !x.last) return;
     if (x.first && pos == 0) {
 #pragma unroll
         for (int i = 0; i < 8; ++i) A[i] += p[64 + at(7) - at(i)];
@@ -634,13 +632,10 @@ __global__ __launch_bounds__(64 * kGatherWaves, 4) void fov_adj_gather_kernel(co
         }
     };
     for_hits([&](const Axis& ax, const Axis& ay, const float* w, const float* c, global_ptr<const float> gp) {
-        const int xlo0 = ax.lo(0, 8), xhi0 = ax.hi(0, 8), xlo1 = ax.lo(1, 8), xhi1 = ax.hi(1, 8);
-        // rows 16 k .. 16 k + 15 of the fragment are wanted by tile rows 16 i ..: use[k][i]
-        bool use[2][2];
-#pragma unroll
-        for (int k = 0; k < 2; ++k)
-#pragma unroll
-            for (int i = 0; i < 2; ++i) use[k][i] = ay.lo(i, 16) <= k && k <= ay.hi(i, 16);
+        // Columns 8 j .. of the fragment that tile columns 0 .. 15 and 16 .. want, and rows 16 k .. that tile rows
+        // 0 .. 15 and 16 .. want, as bits j and k: a test of one is two scalar instructions (the scalar unit was
+        // busier here than the matrix cores).
+        const uint32_t x_0 = ax.band(0, 3), x_1 = ax.band(1, 3), y_0 = ay.band(0, 4), y_1 = ay.band(1, 4);
         AxisLoads wx, wy;
         wx.load(ax, w, c, lane);
         wy.load(ay, w, c, lane);
@@ -704,28 +699,28 @@ __global__ __launch_bounds__(64 * kGatherWaves, 4) void fov_adj_gather_kernel(co
         for (int i = 0; i < 4; ++i) part[i >> 1][i & 1] = v4f{};
 #pragma unroll
         for (int k = 0; k < 2; ++k) {
-            if (!use[k][0] && !use[k][1]) continue;
+            if (!((y_0 | y_1) >> k & 1)) continue;
             v4f G0{}, G1{};
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                if (xlo0 <= j && j <= xhi0) {
+                if (x_0 >> j & 1) {
                     G0 = __builtin_amdgcn_mfma_f32_16x16x4f32(g[k][2 * j], Ax[0][2 * j], G0, 0, 0, 0);
                     G0 = __builtin_amdgcn_mfma_f32_16x16x4f32(g[k][2 * j + 1], Ax[0][2 * j + 1], G0, 0, 0, 0);
                 }
-                if (xlo1 <= j && j <= xhi1) {
+                if (x_1 >> j & 1) {
                     G1 = __builtin_amdgcn_mfma_f32_16x16x4f32(g[k][2 * j], Ax[1][2 * j], G1, 0, 0, 0);
                     G1 = __builtin_amdgcn_mfma_f32_16x16x4f32(g[k][2 * j + 1], Ax[1][2 * j + 1], G1, 0, 0, 0);
                 }
             }
 #pragma unroll
             for (int i = 0; i < 2; ++i) {
-                if (!use[k][i]) continue;
-                if (xlo0 <= xhi0) {
+                if (!((i ? y_1 : y_0) >> k & 1)) continue;
+                if (x_0) {
 #pragma unroll
                     for (int e = 0; e < 4; ++e)
                         part[i][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(Ay[i][4 * k + e], G0[e], part[i][0], 0, 0, 0);
                 }
-                if (xlo1 <= xhi1) {
+                if (x_1) {
 #pragma unroll
                     for (int e = 0; e < 4; ++e)
                         part[i][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(Ay[i][4 * k + e], G1[e], part[i][1], 0, 0, 0);
@@ -870,9 +865,9 @@ size_t adjoint_lds(const AdjShape& s, int es) {
 size_t adjoint_scratch_elems(const AdjShape& s, int nfrag) { return (size_t)nfrag * s.cmax * s.sw * s.sh; }
 
 // A tile is 32 x 32 whatever the fragments: sides that leave much of it empty do better with the windows.  Per
-// call, 4 x 3 x 512 x 512 with radii up to 36 and then 3, 3 x 1080 x 1920 with radii up to 3, gather against
-// windows: 16 px 131 / 347, 69 / 111 and 134 / 205 us; 17 px 315 / 283, 136 / 109; 24 px 109 / 155 but 26 px
-// 53 / 57, 98 / 95; 28 px 49 / 56 and 87 / 86; 32 px 55 / 85, 38 / 44 and 68 / 71.
+// call, gather / windows, 4 x 3 x 512 x 512 with radii up to 36 and then 3, 3 x 1080 x 1920 with radii up to 3: 16 px
+// 128 / 347, 66 / 111 and 128 / 205 us; 17 px 303 / 282, 129 / 109 and 241 / 191; 24 px 106 / 155 but 59 / 64 and 107 / 104;
+// 26 px 90 / 114, 51 / 58 and 95 / 95; 28 px 78 / 104, 47 / 56 and 84 / 86; 32 px 57 / 85, 37 / 44 and 67 / 71.
 bool adjoint_gathers(int es, int block) {
     return es == 4 && (block == kGatherTile / 2 || (block >= 28 && block <= kGatherTile));
 }
