@@ -182,13 +182,18 @@ struct FxStager {
         };
         if (later) {
             const uint32_t off = rgb ? (uint32_t)x * 3u : (uint32_t)x + coff;
-            const uint32_t d1 = rgb ? 16u : (nc > 1 ? isc : 0u), d2 = rgb ? 32u : (nc > 2 ? 2u * isc : d1);
+            const uint32_t d1 = rgb ? 16u : isc, d2 = rgb ? 32u : (nc > 2 ? 2u * isc : d1);
+            if (!rgb && nc == 1) {
 #pragma unroll
-            for (int i = 0; i < kTasks; ++i) {
-                const uint32_t o = row(i) + off;
-                load_words<4>(v[i], in + o);
-                load_words<4>(v[i] + 4, in + (o + d1));
-                load_words<4>(v[i] + 8, in + (o + d2));
+                for (int i = 0; i < kTasks; ++i) load_words<4>(v[i], in + (row(i) + off));
+            } else {
+#pragma unroll
+                for (int i = 0; i < kTasks; ++i) {
+                    const uint32_t o = row(i) + off;
+                    load_words<4>(v[i], in + o);
+                    load_words<4>(v[i] + 4, in + (o + d1));
+                    load_words<4>(v[i] + 8, in + (o + d2));
+                }
             }
         } else if (mode == kRgb) {
 #pragma unroll
