@@ -59,7 +59,8 @@ def algorithmic_fma(h, w, c, p, plan_r):
 
 
 KERNEL_SOURCES = ("paper_2012_08655_amd/csrc/forward.hip", "paper_2012_08655_amd/csrc/forward.h",
-                  "paper_2012_08655_amd/csrc/conv.h", "paper_2012_08655_amd/csrc/common.h")
+                  "paper_2012_08655_amd/csrc/conv.h", "paper_2012_08655_amd/csrc/common.h",
+                  "paper_2012_08655_amd/csrc/fixed.h")
 TRAFFIC_SUMMARY = os.path.join(ROOT, "profiles", "fov_fwd_u8_1080p_rgb_traffic.md")
 
 
@@ -504,7 +505,7 @@ def main():
         "frame_latency_ms": {"p50": round(float(np.percentile(call_ms, 50)), 5),
                              "p99": round(float(np.percentile(call_ms, 99)), 5),
                              "kind": "plain per-frame launch: device time of one call, HIP events"},
-        "roofline": {"bound": "alu", "kernel": "fov_fwd_kernel<u8,u8,f32>",
+        "roofline": {"bound": "alu", "kernel": "fov_fwd_u8_kernel",
                      "achieved": round(achieved_tflops, 3), "peak": PEAK_FP32_TFLOPS, "unit": "TFLOP/s",
                      "frac": round(achieved_tflops / PEAK_FP32_TFLOPS, 4), "traffic": traffic,
                      "algorithmic_flops_per_launch": float(np.mean(flops)),

@@ -4,8 +4,8 @@
 // taps w_k = exp(-k^2/(2 sigma^2)) / sum (Eq. 1 cut at 3 sigma, Appendix "Methods"), the taps while its first
 // samples are on their way.  Earlier forms ran a plan kernel (taps of every fragment) and an order kernel (a
 // counting sort by radius) first; for small calls the three launches in series were the time (480p gray 17.7
-// us a call, now 10.7; 1080p RGB 57.1, now 49.0), for large ones the order kernel's single workgroup
-// (64 mixed frames 4280 us, now 3503).  Calls of more than kArgFrames frames upload their frame table.
+// us a call, 10.7 without them; 1080p RGB 57.1 and 49.0), for large ones the order kernel's single workgroup
+// (64 mixed frames 4280 us and 3503).  Calls of more than kArgFrames frames upload their frame table.
 //
 //  * fov_fwd_kernel: the padded tile (fragment plus r on each side, clamp-to-edge) is staged into LDS
 //    with row-coalesced loads, 8-bit input as 16-bit integers; a horizontal
