@@ -62,10 +62,11 @@ def test_rows_far_apart(fov, orc, dev):
     check(got, orc.adjoint(g.astype(np.float64), p), "far")
 
 
-def test_frame_table_of_mixed_blocks(fov, orc, dev):
-    # more frames than travel in the kernel arguments, one or two fragments per tile side
+@pytest.mark.parametrize("n", [5, 18])
+def test_frame_table_of_mixed_blocks(fov, orc, dev, n):
+    # frames that travel in the kernel arguments and more than do, one or two fragments per tile side
     rng = np.random.default_rng(5)
-    n, c, h, w = 18, 2, 60, 75
+    c, h, w = 2, 60, 75
     ps = [synth.params_dict(rng.uniform(0, w - 1), rng.uniform(0, h - 1), 2.0, 0.3, rng.uniform(1, 12),
                             (16, 32, 29)[i % 3], -int(rng.integers(0, 16)), -int(rng.integers(0, 16))) for i in range(n)]
     g = rng.random((n, c, h, w)).astype(np.float32)
