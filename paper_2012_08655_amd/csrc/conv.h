@@ -544,6 +544,8 @@ template <bool ARGS>
 __device__ __forceinline__ void ranked_frame(const FwdLaunch& a, const int32_t* __restrict__ prefix, int nframes, int k,
                                              int* f, int* rank) {
     *f = 0;
+    *rank = k;
+    if (nframes == 1) return;
     if (a.even) {
         *rank = k / nframes;
         *f = k - *rank * nframes;
@@ -566,7 +568,7 @@ __device__ __forceinline__ Frag ranked_at(const D& d, int f, int rank) {
     const int line = rank / n2, at = rank - line * n2;
     // The first t lines are farther from the fixation than the last one: they go first, then the rest from
     // both ends in turn.  (Any t in 0 .. n1 visits every line once.)
-    const float c1 = (float)((cols ? fp.fix_x - fp.origin_x : fp.fix_y - fp.origin_y) + 0.5) / (float)fp.block;
+    const float c1 = (float)((cols ? fp.fix_x - fp.origin_x : fp.fix_y - fp.origin_y) + 0.5) * __builtin_amdgcn_rcpf((float)fp.block);
     const int t = (int)fminf(fmaxf(2.0f * c1 - (float)n1, 0.0f), (float)n1);
     const int m = line - t;
     const int pos = m < 0 ? line : ((m & 1) ? t + (m >> 1) : n1 - 1 - (m >> 1));
