@@ -463,8 +463,8 @@ __global__ __launch_bounds__(kThreads) void fov_adj_sum_kernel(const FwdLaunch a
 // v_mfma_f32_16x16x4_f32 forms in FP32 like the vector units.  Nothing but the gradient and the taps is
 // read and nothing but grad_in written: the window and sum kernels move every fragment's transposed window,
 // (32 + 2r)^2 values a channel, through scratch and back, and were bound by that.  Measured per call, with the
-// window kernels in brackets: 4 x 3 x 512 x 512, radii up to 36, 32 px fragments 57 us (85), 16 px 125 (347);
-// 32 x 3 x 224 x 224 56 us (73); 3 x 1080 x 1920, radii up to 48 165 us (301).  Of a SIMD's time the matrix
+// window kernels in brackets: 4 x 3 x 512 x 512, radii up to 36, 32 px fragments 57 us (85), 16 px 122 (347);
+// 32 x 3 x 224 x 224 55.5 us (73); 3 x 1080 x 1920, radii up to 48 165 us (301).  Of a SIMD's time the matrix
 // instructions take 36 %, scalar instructions (a tile's and a hit's set-up, the skips) 40 %, vector ones 29 %; a
 // wave waits 40 % of its own.  Slower were: the next hit's loads ahead of this one's products (65 us: a second set of
 // addresses and weights costs more than the wait), and one or two waves a tile (67 and 63 us).
@@ -580,6 +580,9 @@ __global__ __launch_bounds__(64 * kGatherWaves, 4) void fov_adj_gather_kernel(co
                                                                      const int32_t* __restrict__ radius,
                                                                      const float* __restrict__ taps) {
     __shared__ float sums[kGatherWaves][kGatherTile * kGatherPitch];
+    // The way to a hit's loads runs at a raised wave priority: other waves' products can wait for it (57.6 -> 56.7, 16 px
+    // 124.3 -> 121.8 us; the products raised instead, no change).
+    __builtin_amdgcn_s_setprio(2);
     const int item = blockIdx.x / a.cmax, ch = blockIdx.x - item * a.cmax;
     int frame, rank;
     ranked_frame<ARGS>(a, prefix, a.nframes, item, &frame, &rank);
@@ -636,6 +639,7 @@ __global__ __launch_bounds__(64 * kGatherWaves, 4) void fov_adj_gather_kernel(co
         // 0 .. 15 and 16 .. want, as bits j and k: a test of one is two scalar instructions (the scalar unit was
         // busier here than the matrix cores).
         const uint32_t x_0 = ax.band(0, 3), x_1 = ax.band(1, 3), y_0 = ay.band(0, 4), y_1 = ay.band(1, 4);
+        __builtin_amdgcn_s_setprio(2);
         AxisLoads wx, wy;
         wx.load(ax, w, c, lane);
         wy.load(ay, w, c, lane);
@@ -682,6 +686,7 @@ __global__ __launch_bounds__(64 * kGatherWaves, 4) void fov_adj_gather_kernel(co
                     g[k][i] = want ? gp[(int64_t)row * d.ish + (int64_t)col * d.isw] : 0.0f;
                 }
         }
+        __builtin_amdgcn_s_setprio(0);
         __builtin_amdgcn_wave_barrier();
         wx.store(ax, lx, lane);
         wy.store(ay, ly, lane);
