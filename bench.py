@@ -506,6 +506,8 @@ def main():
                              "p99": round(float(np.percentile(call_ms, 99)), 5),
                              "kind": "plain per-frame launch: device time of one call, HIP events"},
         "roofline": {"bound": "alu", "kernel": "fov_fwd_u8_kernel",
+                     "note": "8-bit output in fixed point on the integer matrix cores, byte for byte the FP32 sums; "
+                             "algorithmic FP32 operations against the FP32 vector peak",
                      "achieved": round(achieved_tflops, 3), "peak": PEAK_FP32_TFLOPS, "unit": "TFLOP/s",
                      "frac": round(achieved_tflops / PEAK_FP32_TFLOPS, 4), "traffic": traffic,
                      "algorithmic_flops_per_launch": float(np.mean(flops)),

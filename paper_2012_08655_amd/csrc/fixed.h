@@ -53,8 +53,8 @@
 // the samples are read from LDS in the same order.
 //
 // Measured, kernel time with the FP32 kernel (and the two kernels it needed before it) in brackets: 1080 x 1920
-// x 3, radii up to 48, 42 us (67 + 12), 1080 x 1920 gray 28 us; whole calls: 2160 x 3840 x 3 172 us (272), 64 mixed
-// frames 3285 us (5744).  A tile takes 31 thousand cycles: 4 to find the item, 3 to issue its loads, 8
+// x 3, radii up to 48, 41.5 us (67 + 12), 1080 x 1920 gray 27 us; whole calls: 2160 x 3840 x 3 169 us (271), 64 mixed
+// frames 3272 us (5740).  A tile takes 31 thousand cycles: 4 to find the item, 3 to issue its loads, 8
 // until the samples are in LDS, 1 for the tap digits, 7 for the products and 6 for the undecided
 // pixels; vector units 50 % busy, matrix cores 11 %, waves wait 49 % of their time.  53 KB of LDS and 168 registers
 // allow three workgroups a CU.
