@@ -89,7 +89,10 @@ def _with_defaults(p):
             p.get("origin_y", 0))
 
 
-@functools.lru_cache(maxsize=64)
+_PACK_FRAMES = 64  # frames packed by one call (bounds the formats kept)
+
+
+@functools.lru_cache(maxsize=_PACK_FRAMES + 1)
 def _packer(n: int) -> struct.Struct:
     return struct.Struct("@" + "5d4iP" * n)  # n FovParams
 
@@ -118,7 +121,12 @@ def _pack_params(plist, keep: list):
         ptrs.append(ptr)
     arr = (N.FovParams * max(len(plist), 1))()
     try:
-        _packer(len(plist)).pack_into(arr, 0, *vals)
+        if len(plist) <= _PACK_FRAMES:
+            _packer(len(plist)).pack_into(arr, 0, *vals)
+        else:
+            for i in range(0, len(plist), _PACK_FRAMES):
+                part = vals[10 * i:10 * (i + _PACK_FRAMES)]  # ten values a frame
+                _packer(len(part) // 10).pack_into(arr, i * ctypes.sizeof(N.FovParams), *part)
     except (struct.error, TypeError, OverflowError):
         for i, p in enumerate(plist):
             arr[i] = N.make_params(p, ptrs[i])

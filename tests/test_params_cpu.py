@@ -25,6 +25,13 @@ def test_bytes(n):
         assert bytes(api._frame_params([[p] for p in plist], [])) == bytes(arr)
 
 
+@pytest.mark.parametrize("n", [63, 64, 65, 128, 150])
+@pytest.mark.parametrize("forms", [FORMS[:2], FORMS])  # packed; one frame of them through make_params
+def test_many(n, forms):
+    plist = [dict(forms[i % len(forms)], e0=float(i)) for i in range(n)]
+    assert bytes(api._params_array(plist, n)[0]) == b"".join(bytes(N.make_params(p)) for p in plist)
+
+
 @pytest.mark.parametrize("bad", [{}, dict(BASE, block="x"), dict(BASE, fix_x=None), dict(BASE, origin_x=float("nan"))])
 def test_refusals(bad):
     with pytest.raises(Exception) as want:
