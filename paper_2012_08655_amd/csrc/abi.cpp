@@ -398,10 +398,10 @@ CallShape call_shape(const FrameDesc* frames, int nf) {
 
 // Bytes that the plans of a call's fragments (radius, taps and queue slots of every fragment) take when
 // written out; foveate_forward_noalloc's size limit is stated in them.
-size_t plan_bytes(const FwdLaunch& a, bool by_channel, int tap_size) {
+size_t plan_bytes(const FwdLaunch& a, int split_log2, bool by_channel, int tap_size) {
     const auto up = [](size_t v, size_t m) { return (v + m - 1) / m * m; };
     const size_t nfrag = a.nfrag, pad = 8 * (size_t)std::min(a.r_cap + 1, 1024);
-    const size_t slots = by_channel && nfrag < ((size_t)1 << 26) ? a.cmax * (nfrag + pad) : (nfrag << (2 * a.split_log2)) + pad;
+    const size_t slots = by_channel && nfrag < ((size_t)1 << 26) ? a.cmax * (nfrag + pad) : (nfrag << (2 * split_log2)) + pad;
     return up(2 * up(nfrag * 4, 16) + up(slots * 8, 16) + 256 + nfrag * up(2 * (size_t)a.r_cap + 1, 16) * tap_size, 256);
 }
 
@@ -417,7 +417,10 @@ fov_status plan_forward(const FrameDesc* frames, int nf, int in_dtype, int out_d
     const DeviceInfo* dev = nullptr;
     if ((s = device_info(&dev)) != FOV_OK) return s;
     const LaunchCfg cfg = cfg_in ? *cfg_in : select_cfg(nf, in_dtype, out_dtype, cs);
-    const int L = cfg.split_log2;
+    // the 8-bit kernel's fragments of several tiles: an item each, unless a configuration says otherwise
+    bool tiled = cfg.chan_split < 0 && cfg.split_log2 == 0 && cs.nfrag <= kTiledMax;
+    for (int i = 0; i < nf && tiled; ++i) tiled = forward_tiled(in_dtype, out_dtype, cs.r_cap, frames[i].p.block);
+    const int L = tiled ? 1 : cfg.split_log2;
     if ((cs.nfrag << (2 * L)) > ((int64_t)1 << 30)) return set_error(FOV_EINVAL, "too many fragments in one call");
     const int r_cap = cs.r_cap;
     const int tile = (cs.bmax + (1 << L) - 1) >> L;
@@ -473,7 +476,7 @@ fov_status plan_forward(const FrameDesc* frames, int nf, int in_dtype, int out_d
     fp->lds = lds;
     fp->persistent = cfg.persistent;
     fp->tbytes = nf > kArgFrames ? frame_table_bytes(nf) : 0;
-    fp->plan_bytes = plan_bytes(a, cfg.chan_split != 0 && L == 0 && cs.c > 1 && cs.c <= 16, in_dtype == FOV_F64 ? 8 : 4) +
+    fp->plan_bytes = plan_bytes(a, cfg.split_log2, cfg.chan_split != 0 && cfg.split_log2 == 0 && cs.c > 1 && cs.c <= 16, in_dtype == FOV_F64 ? 8 : 4) +
                      frame_table_bytes(nf);
     fp->lds_limit = dev->lds_limit;
     fp->cus = dev->cus;

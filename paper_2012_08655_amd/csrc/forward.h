@@ -41,8 +41,8 @@ struct FwdLaunch {
                          // the halo rows they share are computed once); split_log2 must be 0
     FrameDesc* table;    // device table of nframes entries (read by the main kernel)
     int32_t* prefix;     // device array of nframes+1 entries
-    const int32_t* hdr;  // optional device header {nframes, nfrag, nitems}: when set, the kernels
-                         // read the counts there and the fields above are capacities (a launch
+    const int32_t* hdr;  // optional device header (BatchHeader): when set, the kernels read the
+                         // counts and the split there and the fields above are capacities (a launch
                          // sequence that can be captured once and replayed for many batches; the
                          // replayer sets the main kernel's grid to the batch's item count)
     int32_t kprefix[kArgFrames + 1];
@@ -52,7 +52,7 @@ static_assert(sizeof(FwdLaunch) <= 4000, "kernel arguments must fit the kernarg 
 
 // Device header of a replayable batch (see FwdLaunch::hdr).
 struct BatchHeader {
-    int32_t nframes, nfrag, nitems, pad;
+    int32_t nframes, nfrag, nitems, split_log2;
 };
 
 // The forward kernel of one launch.  persist selects its dispatch: a persistent
@@ -72,6 +72,11 @@ const void* forward_main_kernel(int in_dtype, int out_dtype, int r_cap);
 // Whether launches of this dtype pair with radii up to r_cap run on the matrix
 // cores (8-bit output; see fixed.h).
 bool forward_fixed(int in_dtype, int out_dtype, int r_cap);
+
+// Whether fragments of this side are split into a work item per tile there.  Each tile is staged and
+// filtered by itself, so an item for each costs nothing more and fills the chip sooner.
+bool forward_tiled(int in_dtype, int out_dtype, int r_cap, int block);
+constexpr int64_t kTiledMax = (int64_t)1 << 26;  // fragments of a call up to which that is done
 
 // Device plan for foveate_plan(): sigma and radius of every fragment.
 fov_status launch_plan(const FrameParams& fp, int nblk, double* sigma_out, int32_t* r_out, hipStream_t stream);

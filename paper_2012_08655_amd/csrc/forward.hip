@@ -452,15 +452,16 @@ __device__ __forceinline__ void process_fragment(int r_cap, int strip_rows, int 
 
 // Counts of a launch: from the arguments or (replayed launches) the device header.
 struct Counts {
-    int nitems, nframes;
+    int nitems, nframes, split_log2;
 };
 
 template <bool ARGS>
 __device__ __forceinline__ Counts counts(const FwdLaunch& a) {
-    Counts n{a.nitems, a.nframes};
+    Counts n{a.nitems, a.nframes, a.split_log2};
     if (!ARGS && a.hdr) {
         n.nitems = __builtin_amdgcn_readfirstlane(a.hdr[2]);
         n.nframes = __builtin_amdgcn_readfirstlane(a.hdr[0]);
+        n.split_log2 = __builtin_amdgcn_readfirstlane(a.hdr[3]);
     }
     return n;
 }
@@ -480,7 +481,7 @@ struct Item {
 template <bool ARGS, bool FIXED = false>
 __device__ __forceinline__ bool decode(const FwdLaunch& a, const FrameDesc* __restrict__ table,
                                        const int32_t* __restrict__ prefix, const Counts& n, int i, Item* it) {
-    const int L = a.split_log2;
+    const int L = n.split_log2;
     if ((i | 63) < n.nitems) i = (i & ~63) | (i & 7) << 3 | (i >> 3 & 7);
     const int sub = i & ((1 << (2 * L)) - 1);
     int k = i >> (2 * L), ch = -1;
@@ -660,6 +661,11 @@ int forward_tile_rows(int r, int tile_h) { return geom(r, 1, tile_h).TH; }
 
 bool forward_fixed(int in_dtype, int out_dtype, int r_cap) {
     return in_dtype == FOV_U8 && out_dtype == FOV_U8 && r_cap >= 1 && r_cap <= kFxRadius;
+}
+
+// Per call: 354 x 563 gray, 64 px fragments, 24.1 -> 9.8 us; 1080 x 1920 x 3, 64 px, 63 -> 46; 400 x 600 x 3, 48 px, 33 -> 11.5.
+bool forward_tiled(int in_dtype, int out_dtype, int r_cap, int block) {
+    return forward_fixed(in_dtype, out_dtype, r_cap) && block > kFxTile;
 }
 
 size_t forward_lds_bytes(int in_dtype, int out_dtype, int r_cap, int tile_w, int tile_h, int strip_rows) {

@@ -252,7 +252,10 @@ fov_status launch_batch(ServerImpl* s, Slot& sl, const std::vector<FrameDesc>& f
     }
     if (s->cfg.use_graph) {
         char* h = static_cast<char*>(sl.host);
-        BatchHeader hdr{(int32_t)frames.size(), nfrag, nfrag, 0};
+        bool tiled = nfrag <= kTiledMax;
+        for (const FrameDesc& f : frames) tiled &= forward_tiled(s->cfg.in_dtype, s->cfg.out_dtype, s->r_cap, f.p.block);
+        const int L = tiled ? 1 : 0;
+        BatchHeader hdr{(int32_t)frames.size(), nfrag, nfrag << (2 * L), L};
         std::memcpy(h, &hdr, sizeof(hdr));
         std::memcpy(h + sizeof(BatchHeader), frames.data(), frames.size() * sizeof(FrameDesc));
         int32_t* pre = reinterpret_cast<int32_t*>(h + sizeof(BatchHeader) + (size_t)s->cfg.max_batch_frames * sizeof(FrameDesc));
