@@ -425,16 +425,21 @@ fov_status plan_forward(const FrameDesc* frames, int nf, int in_dtype, int out_d
     const int r_cap = cs.r_cap;
     const int tile = (cs.bmax + (1 << L) - 1) >> L;
     const int sr = cfg.strip_rows;
-    size_t lds = forward_lds_bytes(in_dtype, out_dtype, r_cap, tile, tile, sr);
+    // One channel of fragments of at most 16 px leaves most of the 8-bit kernel's tile and two of its waves
+    // empty: the FP32 kernel, with the same bytes.  Per call, 8-bit kernel / FP32 kernel, gray, 16 px, radii up to 24 and
+    // 48: 600 x 900 22 / 17 and 23 / 17 us, 1080 x 1920 75 / 63 and 87 / 79, 2160 x 3840 273 / 155 and 347 / 239; 24 px at
+    // 2160 x 3840 135 / 147 and 176 / 267; three channels, 16 px, 1080 x 1920 95 / 147 and 120 / 201.
+    const bool fp32 = forward_fixed(in_dtype, out_dtype, r_cap) && cfg.chan_split < 0 && cs.c == 1 && cs.bmax <= 16;
+    size_t lds = forward_lds_bytes(in_dtype, out_dtype, r_cap, tile, tile, sr, fp32);
     // vertical pairs at the cap need tiles twice as tall; by default only when the CU holds as
     // many workgroups with them
-    const bool fixed = forward_fixed(in_dtype, out_dtype, r_cap);
+    const bool fixed = !fp32 && forward_fixed(in_dtype, out_dtype, r_cap);
     bool merge = !fixed && cfg.merge != 0 && L == 0 && r_cap > 0;
     if (merge) {
-        const size_t lds2 = forward_lds_bytes(in_dtype, out_dtype, r_cap, tile, 2 * tile, sr);
+        const size_t lds2 = forward_lds_bytes(in_dtype, out_dtype, r_cap, tile, 2 * tile, sr, fp32);
         if (lds2 + 64 > dev->lds_limit ||
-            (cfg.merge < 0 && forward_occupancy(in_dtype, out_dtype, r_cap, lds2) <
-                                  forward_occupancy(in_dtype, out_dtype, r_cap, lds)))
+            (cfg.merge < 0 && forward_occupancy(in_dtype, out_dtype, r_cap, lds2, fp32) <
+                                  forward_occupancy(in_dtype, out_dtype, r_cap, lds, fp32)))
             merge = false;
         else
             lds = lds2;
@@ -458,6 +463,7 @@ fov_status plan_forward(const FrameDesc* frames, int nf, int in_dtype, int out_d
     a.nfrag = (int32_t)total;
     a.split_log2 = L;
     a.merge = merge ? 1 : 0;
+    a.fp32 = fp32 ? 1 : 0;
     a.r_cap = r_cap;
     a.strip_rows = sr;
     a.cmax = cs.c;

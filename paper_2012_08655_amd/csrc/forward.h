@@ -39,6 +39,7 @@ struct FwdLaunch {
     int32_t merge;       // 1: a fragment at an even row whose sigma and the sigma of the fragment
                          // below both equal the cap becomes one work item with it (equal taps, so
                          // the halo rows they share are computed once); split_log2 must be 0
+    int32_t fp32;        // 1: 8-bit output on the FP32 kernel whatever the radius (see forward_fixed())
     FrameDesc* table;    // device table of nframes entries (read by the main kernel)
     int32_t* prefix;     // device array of nframes+1 entries
     const int32_t* hdr;  // optional device header (BatchHeader): when set, the kernels read the
@@ -67,7 +68,7 @@ fov_status launch_forward(const FwdLaunch& a, int in_dtype, int out_dtype, size_
 // The main forward kernel of a batch table launched one workgroup per item, for
 // a dtype pair (to find its node in a captured graph); NULL for an unsupported
 // pair.
-const void* forward_main_kernel(int in_dtype, int out_dtype, int r_cap);
+const void* forward_main_kernel(int in_dtype, int out_dtype, int r_cap, bool fp32 = false);
 
 // Whether launches of this dtype pair with radii up to r_cap run on the matrix
 // cores (8-bit output; see fixed.h).
@@ -84,7 +85,7 @@ fov_status launch_plan(const FrameParams& fp, int nblk, double* sigma_out, int32
 // LDS bytes a forward workgroup needs for radius r_cap and output tiles of
 // tile_w x tile_h pixels (the fragment side B divided by the split, rounded
 // up; tile_h = 2B when vertical pairs are merged).
-size_t forward_lds_bytes(int in_dtype, int out_dtype, int r_cap, int tile_w, int tile_h, int strip_rows);
+size_t forward_lds_bytes(int in_dtype, int out_dtype, int r_cap, int tile_w, int tile_h, int strip_rows, bool fp32 = false);
 
 // Padded-tile rows of a tile tile_h pixels tall at radius r (what a strip
 // height above it cannot change).
@@ -92,7 +93,7 @@ int forward_tile_rows(int r, int tile_h);
 
 // Workgroups of the main kernel (one workgroup per work item) that one CU
 // holds at once with `lds` bytes of dynamic LDS each.
-int forward_occupancy(int in_dtype, int out_dtype, int r_cap, size_t lds);
+int forward_occupancy(int in_dtype, int out_dtype, int r_cap, size_t lds, bool fp32 = false);
 
 // Largest strip height the kernel stages at once.
 int forward_strip_max();

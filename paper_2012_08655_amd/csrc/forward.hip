@@ -643,7 +643,7 @@ template <typename TIn, typename TOut, typename TS, typename TC>
 fov_status launch_typed(const FwdLaunch& a, size_t lds, hipStream_t stream, size_t lds_limit, int cus, bool persist,
                         hipEvent_t ev_start, hipEvent_t ev_stop) {
     if constexpr (std::is_same<TOut, uint8_t>::value)
-        if (forward_fixed(FOV_U8, FOV_U8, a.r_cap))
+        if (!a.fp32 && forward_fixed(FOV_U8, FOV_U8, a.r_cap))
             return (a.from_args ? launch_u8<true> : launch_u8<false>)(a, lds, stream, lds_limit, ev_start, ev_stop);
     const auto main = a.from_args ? (persist ? launch_main<TIn, TOut, TS, TC, true, true> : launch_main<TIn, TOut, TS, TC, false, true>)
                                   : (persist ? launch_main<TIn, TOut, TS, TC, true, false> : launch_main<TIn, TOut, TS, TC, false, false>);
@@ -668,7 +668,7 @@ bool forward_tiled(int in_dtype, int out_dtype, int r_cap, int block) {
     return forward_fixed(in_dtype, out_dtype, r_cap) && block > kFxTile;
 }
 
-size_t forward_lds_bytes(int in_dtype, int out_dtype, int r_cap, int tile_w, int tile_h, int strip_rows) {
+size_t forward_lds_bytes(int in_dtype, int out_dtype, int r_cap, int tile_w, int tile_h, int strip_rows, bool only_fp32) {
     const Geom g = geom(r_cap, tile_w, tile_h);
     int rows = strip_rows < g.TH ? strip_rows : g.TH;
     if (rows > kStripMax) rows = kStripMax;
@@ -677,7 +677,7 @@ size_t forward_lds_bytes(int in_dtype, int out_dtype, int r_cap, int tile_w, int
     const int TW = g.TW + (in_dtype == FOV_U8 ? ((-r_cap) & 3) : 0);
     const size_t fp32 = kTileLead + tap_lds_bytes(r_cap, ec) + align16((size_t)rows * tile_pitch(TW, es) * es) +
                         (size_t)g.G * kPH * inter_pitch(g.TH, ec) * ec + 64;
-    if (!forward_fixed(in_dtype, out_dtype, r_cap)) return fp32;
+    if (only_fp32 || !forward_fixed(in_dtype, out_dtype, r_cap)) return fp32;
     // the matrix-core tiles and the FP32 passes take turns in one allocation
     return std::max(fp32, (size_t)fx_lds(fx_blocks(r_cap), kFxChan).total);
 }
@@ -697,13 +697,13 @@ fov_status launch_forward(const FwdLaunch& a, int in_dtype, int out_dtype, size_
     return set_error(FOV_EDTYPE, "unsupported dtype pair");
 }
 
-int forward_occupancy(int in_dtype, int out_dtype, int r_cap, size_t lds) {
-    const void* k = forward_main_kernel(in_dtype, out_dtype, r_cap);
+int forward_occupancy(int in_dtype, int out_dtype, int r_cap, size_t lds, bool fp32) {
+    const void* k = forward_main_kernel(in_dtype, out_dtype, r_cap, fp32);
     return k ? occupancy_of(k, lds) : 0;
 }
 
-const void* forward_main_kernel(int in_dtype, int out_dtype, int r_cap) {
-    if (forward_fixed(in_dtype, out_dtype, r_cap)) return (const void*)fov_fwd_u8_kernel<false>;
+const void* forward_main_kernel(int in_dtype, int out_dtype, int r_cap, bool fp32) {
+    if (!fp32 && forward_fixed(in_dtype, out_dtype, r_cap)) return (const void*)fov_fwd_u8_kernel<false>;
     if (in_dtype == FOV_U8 && out_dtype == FOV_U8) return (const void*)fov_fwd_kernel<uint8_t, uint8_t, _Float16, float, false, false>;
     if (in_dtype == FOV_U8 && out_dtype == FOV_F32) return (const void*)fov_fwd_kernel<uint8_t, float, _Float16, float, false, false>;
     if (in_dtype == FOV_F32 && out_dtype == FOV_F32) return (const void*)fov_fwd_kernel<float, float, float, float, false, false>;

@@ -41,3 +41,12 @@ def test_served(fov, dev, blocks):
     torch.cuda.synchronize()
     for x, p, y in zip(xs, ps, outs):
         assert torch.equal(y, expect(fov, x, p)), p["block"]
+
+
+@pytest.mark.parametrize("c", [1, 3])  # one channel of at most 16 px: the FP32 kernel
+@pytest.mark.parametrize("block", [1, 5, 15, 16, 17])
+def test_small_sides(fov, dev, block, c):
+    g = torch.Generator(device=dev).manual_seed(block)
+    x = torch.randint(0, 256, (61, 83, c), dtype=torch.uint8, device=dev, generator=g)
+    p = synth.params_dict(30.0, 20.0, 5.0, 0.2, 16.0, block, -(block // 3), -(block // 2))
+    assert torch.equal(fov.forward(x, p, layout="HWC"), expect(fov, x, p))
