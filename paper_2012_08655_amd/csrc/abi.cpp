@@ -417,19 +417,25 @@ fov_status plan_forward(const FrameDesc* frames, int nf, int in_dtype, int out_d
     const DeviceInfo* dev = nullptr;
     if ((s = device_info(&dev)) != FOV_OK) return s;
     const LaunchCfg cfg = cfg_in ? *cfg_in : select_cfg(nf, in_dtype, out_dtype, cs);
+    // One channel leaves two of the 8-bit kernel's three product waves empty, and fragments of at most 16 px most
+    // of its tile: the FP32 kernel then, with the same bytes, unless a configuration says otherwise; so too
+    // for large fragments with small radii, whose windows it stages once where the 8-bit kernel stages one per
+    // tile, if there are enough of them.  Per call, 8-bit kernel / FP32 kernel, gray, radii up to 24 and 48: 16 px, 600 x
+    // 900 22 / 17 and 23 / 17 us, 1080 x 1920 75 / 63 and 87 / 79, 2160 x 3840 273 / 155 and 347 / 239; 24 px, 2160 x 3840
+    // 135 / 147 and 176 / 267; 32 px 81 / 96 and 107 / 166; 64 px 81 / 50 and 108 / 121, 1080 x 1920 24 / 19 and 30 / 34, 720 x 1000
+    // 12 / 16 and 12 / 24; three channels, 16 px, 1080 x 1920 95 / 147 and 120 / 201.
+    int bmin = cs.bmax;
+    for (int i = 0; i < nf; ++i) bmin = std::min(bmin, frames[i].p.block);
+    const bool fp32 = forward_fixed(in_dtype, out_dtype, cs.r_cap) && cfg.chan_split < 0 && cs.c == 1 &&
+                      (cs.bmax <= 16 || (bmin > 32 && cs.r_cap <= 32 && cs.nfrag >= dev->cus));
     // the 8-bit kernel's fragments of several tiles: an item each, unless a configuration says otherwise
-    bool tiled = cfg.chan_split < 0 && cfg.split_log2 == 0 && cs.nfrag <= kTiledMax;
+    bool tiled = !fp32 && cfg.chan_split < 0 && cfg.split_log2 == 0 && cs.nfrag <= kTiledMax;
     for (int i = 0; i < nf && tiled; ++i) tiled = forward_tiled(in_dtype, out_dtype, cs.r_cap, frames[i].p.block);
     const int L = tiled ? 1 : cfg.split_log2;
     if ((cs.nfrag << (2 * L)) > ((int64_t)1 << 30)) return set_error(FOV_EINVAL, "too many fragments in one call");
     const int r_cap = cs.r_cap;
     const int tile = (cs.bmax + (1 << L) - 1) >> L;
     const int sr = cfg.strip_rows;
-    // One channel of fragments of at most 16 px leaves most of the 8-bit kernel's tile and two of its waves
-    // empty: the FP32 kernel, with the same bytes.  Per call, 8-bit kernel / FP32 kernel, gray, 16 px, radii up to 24 and
-    // 48: 600 x 900 22 / 17 and 23 / 17 us, 1080 x 1920 75 / 63 and 87 / 79, 2160 x 3840 273 / 155 and 347 / 239; 24 px at
-    // 2160 x 3840 135 / 147 and 176 / 267; three channels, 16 px, 1080 x 1920 95 / 147 and 120 / 201.
-    const bool fp32 = forward_fixed(in_dtype, out_dtype, r_cap) && cfg.chan_split < 0 && cs.c == 1 && cs.bmax <= 16;
     size_t lds = forward_lds_bytes(in_dtype, out_dtype, r_cap, tile, tile, sr, fp32);
     // vertical pairs at the cap need tiles twice as tall; by default only when the CU holds as
     // many workgroups with them

@@ -50,3 +50,13 @@ def test_small_sides(fov, dev, block, c):
     x = torch.randint(0, 256, (61, 83, c), dtype=torch.uint8, device=dev, generator=g)
     p = synth.params_dict(30.0, 20.0, 5.0, 0.2, 16.0, block, -(block // 3), -(block // 2))
     assert torch.equal(fov.forward(x, p, layout="HWC"), expect(fov, x, p))
+
+
+@pytest.mark.parametrize("cap", [10.6, 10.7])  # radii 32 and 33: gray frames of many such fragments change kernels
+@pytest.mark.parametrize("n", [15, 16])  # 255 and 272 fragments
+def test_many_large_gray(fov, dev, n, cap):
+    g = torch.Generator(device=dev).manual_seed(n)
+    x = torch.randint(0, 256, (17 * 33 - 4, n * 33 - 7, 1), dtype=torch.uint8, device=dev, generator=g)
+    p = synth.params_dict(90.0, 200.0, 5.0, 0.08, cap, 33)
+    assert fov.grid(x.shape[0], x.shape[1], p) == (17, n)
+    assert torch.equal(fov.forward(x, p, layout="HWC"), expect(fov, x, p))
