@@ -221,7 +221,8 @@ fov_status foveate_backward(const fov_tensor* grad_out, const fov_tensor* grad_i
  *                the fragment below both equal the cap is one work item with
  *                it (equal taps: the halo rows the two share are computed
  *                once); needs split 1.  By default it is on unless its taller
- *                tiles would let fewer workgroups share a CU.
+ *                tiles would let fewer workgroups share a CU, the chip holds
+ *                the unmerged items all at once, or few pairs would be merged.
  *   chan_split : 1 = a fragment is one work item per channel (short, latency
  *                bound items: its channels then run side by side); needs split
  *                1 and at most 16 channels.  By default on for frames of

@@ -19,6 +19,7 @@
 #include "common.h"
 #include "forward.h"
 #include "host.h"
+#include "order.h"
 
 namespace fov {
 
@@ -407,7 +408,7 @@ size_t plan_bytes(const FwdLaunch& a, int split_log2, bool by_channel, int tap_s
 
 // Launch shape of one forward call over a list of frames (any shapes, one
 // dtype pair): counts, radius bound, LDS and scratch sizes; no device work.
-fov_status plan_forward(const FrameDesc* frames, int nf, int in_dtype, int out_dtype, const LaunchCfg* cfg_in,
+fov_status plan_forward(FrameDesc* frames, int nf, int in_dtype, int out_dtype, const LaunchCfg* cfg_in,
                         ForwardPlan* fp) {
     fov_status s;
     const CallShape cs = call_shape(frames, nf);
@@ -437,18 +438,25 @@ fov_status plan_forward(const FrameDesc* frames, int nf, int in_dtype, int out_d
     const int tile = (cs.bmax + (1 << L) - 1) >> L;
     const int sr = cfg.strip_rows;
     size_t lds = forward_lds_bytes(in_dtype, out_dtype, r_cap, tile, tile, sr, fp32);
-    // vertical pairs at the cap need tiles twice as tall; by default only when the CU holds as
-    // many workgroups with them
     const bool fixed = !fp32 && forward_fixed(in_dtype, out_dtype, r_cap);
+    // One work item per channel where the fragments alone would not fill the chip several times over; above
+    // that an item's sigma, taps and geometry are worked out once for its channels, and a channel is loaded while
+    // the last one is computed.  A configuration may say otherwise.  Kernel time, items of one channel against
+    // items of three: 1024 fragments (4 x 3 x 512 x 512 f32) 45 / 54 us, 1568 (32 x 3 x 224 x 224 f32) 34 / 32, 2048 (8 x 3 x
+    // 512 x 512) 73 / 77, 2400 (16 x 3 x 317 x 451 u8 to f32) 54 / 54, 2888 (2 x 3 x 600 x 600, 16 px) f32 54 / 42 and f64
+    // 157 / 144, 4640 (8 x 3 x 317 x 451 u8 to f32, 16 px) 73 / 64.
+    const bool chan = !fixed && L == 0 && cs.c > 1 && cs.c <= 16 && cs.nfrag * cs.c <= ((int64_t)1 << 30) &&
+                      (cfg.chan_split > 0 || (cfg.chan_split < 0 && cs.nfrag < (int64_t)9 * dev->cus));
+    // vertical pairs at the cap need tiles twice as tall; by default only when the CU holds as
+    // many workgroups with them and they pay
     bool merge = !fixed && cfg.merge != 0 && L == 0 && r_cap > 0;
     if (merge) {
         const size_t lds2 = forward_lds_bytes(in_dtype, out_dtype, r_cap, tile, 2 * tile, sr, fp32);
-        if (lds2 + 64 > dev->lds_limit ||
-            (cfg.merge < 0 && forward_occupancy(in_dtype, out_dtype, r_cap, lds2, fp32) <
-                                  forward_occupancy(in_dtype, out_dtype, r_cap, lds, fp32)))
-            merge = false;
-        else
-            lds = lds2;
+        const int one = cfg.merge < 0 ? forward_occupancy(in_dtype, out_dtype, r_cap, lds, fp32) : 0;
+        merge = lds2 + 64 <= dev->lds_limit &&
+                (cfg.merge > 0 || (forward_occupancy(in_dtype, out_dtype, r_cap, lds2, fp32) >= one &&
+                                   merge_pays(frames, nf, cs.nfrag * (chan ? cs.c : 1), (int64_t)one * dev->cus)));
+        if (merge) lds = lds2;
     }
     if (lds + 64 > dev->lds_limit)
         return set_error(FOV_ERANGE, "radius " + std::to_string(r_cap) + " needs " + std::to_string(lds) +
@@ -459,14 +467,9 @@ fov_status plan_forward(const FrameDesc* frames, int nf, int in_dtype, int out_d
     // frames (no host allocation), else in the table that launch_planned uploads
     if (nf > kArgFrames) fp->prefix_table.assign(nf + 1, 0);
     int32_t* prefix = nf > kArgFrames ? fp->prefix_table.data() : a.kprefix;
-    int64_t total = 0;
-    for (int i = 0; i < nf; ++i) {
-        prefix[i] = (int32_t)total;
-        total += (int64_t)frames[i].p.nbx * frames[i].nby;
-    }
-    prefix[nf] = (int32_t)total;
+    const int64_t units = number_items(frames, nf, merge, prefix);
     a.nframes = nf;
-    a.nfrag = (int32_t)total;
+    a.nfrag = (int32_t)cs.nfrag;
     a.split_log2 = L;
     a.merge = merge ? 1 : 0;
     a.fp32 = fp32 ? 1 : 0;
@@ -475,16 +478,8 @@ fov_status plan_forward(const FrameDesc* frames, int nf, int in_dtype, int out_d
     a.cmax = cs.c;
     a.even = 1;
     for (int i = 0; i < nf; ++i) a.even &= prefix[i + 1] - prefix[i] == prefix[1];
-    // One work item per channel where the fragments alone would not fill the chip several times over; above
-    // that an item's sigma, taps and geometry are worked out once for its channels, and a channel is loaded while
-    // the last one is computed.  A configuration may say otherwise.  Kernel time, items of one channel against
-    // items of three: 1024 fragments (4 x 3 x 512 x 512 f32) 45 / 54 us, 1568 (32 x 3 x 224 x 224 f32) 34 / 32, 2048 (8 x 3 x
-    // 512 x 512) 73 / 77, 2400 (16 x 3 x 317 x 451 u8 to f32) 54 / 54, 2888 (2 x 3 x 600 x 600, 16 px) f32 54 / 42 and f64
-    // 157 / 144, 4640 (8 x 3 x 317 x 451 u8 to f32, 16 px) 73 / 64.
-    const bool chan = cfg.chan_split > 0 || (cfg.chan_split < 0 && cs.nfrag < (int64_t)9 * dev->cus);
-    a.chan = !fixed && chan && L == 0 && cs.c > 1 && cs.c <= 16 &&
-             cs.nfrag * cs.c <= ((int64_t)1 << 30);
-    a.nitems = a.chan ? a.nfrag * cs.c : a.nfrag << (2 * L);
+    a.chan = chan ? 1 : 0;
+    a.nitems = (int32_t)(chan ? units * cs.c : units << (2 * L));
     fp->lds = lds;
     fp->persistent = cfg.persistent;
     fp->tbytes = nf > kArgFrames ? frame_table_bytes(nf) : 0;
@@ -517,7 +512,7 @@ fov_status launch_planned(const FrameDesc* frames, int nf, int in_dtype, int out
 // One forward launch over a list of frames (any shapes, one dtype pair).  Up to
 // kArgFrames descriptors travel in the kernel arguments; more are uploaded
 // as a device table from pinned memory to the per-(device, stream) workspace.
-fov_status run_forward(const std::vector<FrameDesc>& frames, int in_dtype, int out_dtype, hipStream_t stream,
+fov_status run_forward(std::vector<FrameDesc>& frames, int in_dtype, int out_dtype, hipStream_t stream,
                        const LaunchCfg* cfg_in, bool profile) {
     if (frames.empty()) return FOV_OK;
     fov_status s;
@@ -623,6 +618,8 @@ FrameDesc make_frame_desc(const fov_tensor& in, const fov_tensor& out, int n, co
     d.c = in.c; d.h = in.h; d.w = in.w;
     d.p = to_frame(p, in.h, in.w);
     d.nby = grid_extent(in.h, p.origin_y, p.block);
+    d.ahead = lines_ahead(d);
+    d.low_lines = d.low_at = d.low_span = 0;
     return d;
 }
 

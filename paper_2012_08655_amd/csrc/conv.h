@@ -5,7 +5,7 @@
 
 #include <hip/hip_runtime.h>
 
-#include "forward.h"
+#include "order.h"
 
 namespace fov {
 namespace {
@@ -538,8 +538,8 @@ __device__ __forceinline__ Frag frag_of(const FwdLaunch& a, const FrameDesc* __r
 // The k-th fragment of the launch, numbered so that the costliest tend to come first (a launch does not end
 // on a long tail) without any pass over the plan: a frame's fragments go along its longer axis, the lines
 // farthest from the fixation first (sigma grows with the distance), and in turn within a line; frames of
-// equal fragment counts take turns.  ranked_frame() gives its frame f and its rank there, ranked_at() the
-// fragment.
+// equal counts take turns.  ranked_frame() gives its frame f and its rank there, ranked_at() the
+// fragment (order.h).
 template <bool ARGS>
 __device__ __forceinline__ void ranked_frame(const FwdLaunch& a, const int32_t* __restrict__ prefix, int nframes, int k,
                                              int* f, int* rank) {
@@ -560,19 +560,12 @@ __device__ __forceinline__ void ranked_frame(const FwdLaunch& a, const int32_t* 
 }
 
 template <typename D>
-__device__ __forceinline__ Frag ranked_at(const D& d, int f, int rank) {
-    const FrameParams& fp = d.p;
-    // lines along the longer axis: n1 of them, n2 fragments in each
-    const bool cols = fp.nbx >= d.nby;
-    const int n1 = cols ? fp.nbx : d.nby, n2 = cols ? d.nby : fp.nbx;
-    const int line = rank / n2, at = rank - line * n2;
-    // The first t lines are farther from the fixation than the last one: they go first, then the rest from
-    // both ends in turn.  (Any t in 0 .. n1 visits every line once.)
-    const float c1 = (float)((cols ? fp.fix_x - fp.origin_x : fp.fix_y - fp.origin_y) + 0.5) * __builtin_amdgcn_rcpf((float)fp.block);
-    const int t = (int)fminf(fmaxf(2.0f * c1 - (float)n1, 0.0f), (float)n1);
-    const int m = line - t;
-    const int pos = m < 0 ? line : ((m & 1) ? t + (m >> 1) : n1 - 1 - (m >> 1));
-    return fragment_at(d, f, __builtin_amdgcn_readfirstlane(cols ? pos : at), __builtin_amdgcn_readfirstlane(cols ? at : pos));
+__device__ __forceinline__ Frag placed_at(const D& d, int f, const Place& p) {
+    return fragment_at(d, f, __builtin_amdgcn_readfirstlane(p.bx), __builtin_amdgcn_readfirstlane(p.by));
+}
+
+__device__ __forceinline__ Frag ranked_at(const FrameDesc& d, int f, int rank) {
+    return placed_at(d, f, ranked_place(grid_of(d), rank));
 }
 
 // What a work item is decided by, read from its frame in one go: the empty asm keeps the loads together.
@@ -582,15 +575,16 @@ __device__ __forceinline__ Frag ranked_at(const D& d, int f, int rank) {
 struct FrameGeo {
     int32_t c, h, w, nby;
     FrameParams p;
+    int32_t ahead;
 };
 
 template <bool ARGS>
 __device__ __forceinline__ FrameGeo geo_of(const FwdLaunch& a, const FrameDesc* __restrict__ table, int f) {
     const FrameDesc& d = frame_of<ARGS>(a, table, f);
-    FrameGeo g{d.c, d.h, d.w, d.nby, d.p};
+    FrameGeo g{d.c, d.h, d.w, d.nby, d.p, d.ahead};
     asm volatile("" : "+s"(g.c), "+s"(g.h), "+s"(g.w), "+s"(g.nby), "+s"(g.p.fix_x), "+s"(g.p.fix_y), "+s"(g.p.e0),
                  "+s"(g.p.slope), "+s"(g.p.cap), "+s"(g.p.block), "+s"(g.p.origin_x), "+s"(g.p.origin_y), "+s"(g.p.nbx),
-                 "+s"(g.p.sigma_map));
+                 "+s"(g.p.sigma_map), "+s"(g.ahead));
     return g;
 }
 

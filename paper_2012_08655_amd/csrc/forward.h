@@ -12,6 +12,13 @@ struct FrameDesc {
     int64_t isc, ish, isw, osc, osh, osw;  // element strides
     int32_t c, h, w, nby;
     FrameParams p;  // p.nbx filled in
+    // The order of its fragments (order.h).  They go along the longer axis, in lines across it:
+    // the first `ahead` lines (the last -ahead) first, which are farther from the fixation than all others, then from both
+    // ends in turn.
+    int32_t ahead;
+    // With merge: the pairs that may not be merged lie in the last low_lines lines, at low_at .. low_at + low_span - 1
+    // of each.
+    int32_t low_lines, low_at, low_span;
 };
 
 // Frames whose descriptors travel inside the kernel arguments; larger
@@ -22,6 +29,7 @@ constexpr int kArgFrames = 16;
 // frames are numbered consecutively: frame f owns fragments
 // [prefix[f], prefix[f+1]).  Work item i of the forward belongs to fragment
 // i >> (2 split_log2) of the launch order (see decode() in forward.hip).
+// With merge a frame's numbers are those of its pairs, and one more for each pair that may not be merged.
 struct FwdLaunch {
     int32_t nframes, nfrag;
     int32_t nitems;      // work items of the forward
@@ -36,14 +44,14 @@ struct FwdLaunch {
     int32_t cmax;        // largest channel count of the frames
     int32_t even;        // 1: every frame has the same number of fragments (items take the frames in
                          // turn)
-    int32_t merge;       // 1: a fragment at an even row whose sigma and the sigma of the fragment
-                         // below both equal the cap becomes one work item with it (equal taps, so
-                         // the halo rows they share are computed once); split_log2 must be 0
+    int32_t merge;       // 1: fragments of rows 2k and 2k + 1 whose sigmas both equal the cap are filtered
+                         // as one rectangle (equal taps, so the halo rows they share are computed
+                         // once); split_log2 must be 0
     int32_t fp32;        // 1: 8-bit output on the FP32 kernel whatever the radius (see forward_fixed())
     FrameDesc* table;    // device table of nframes entries (read by the main kernel)
     int32_t* prefix;     // device array of nframes+1 entries
     const int32_t* hdr;  // optional device header (BatchHeader): when set, the kernels read the
-                         // counts and the split there and the fields above are capacities (a launch
+                         // counts, the split and merge there and the fields above are capacities (a launch
                          // sequence that can be captured once and replayed for many batches; the
                          // replayer sets the main kernel's grid to the batch's item count)
     int32_t kprefix[kArgFrames + 1];
@@ -53,7 +61,7 @@ static_assert(sizeof(FwdLaunch) <= 4000, "kernel arguments must fit the kernarg 
 
 // Device header of a replayable batch (see FwdLaunch::hdr).
 struct BatchHeader {
-    int32_t nframes, nfrag, nitems, split_log2;
+    int32_t nframes, merge, nitems, split_log2;
 };
 
 // The forward kernel of one launch.  persist selects its dispatch: a persistent

@@ -362,11 +362,11 @@ __device__ __forceinline__ void process_fragment(int r_cap, int strip_rows, int 
         w[i] = v;
         if (kSym && i > r) ws[i - r - 1] = v * kSymScale;
     }
-    st.commit(tile, TP);
-    __builtin_amdgcn_s_setprio(0);
-    __syncthreads();
     int cu = 0, sidx = 0;  // the current unit: channel c_lo + cu, strip sidx
     for (int u = 0; u < nunits; ++u) {
+        st.commit(tile, TP);
+        __builtin_amdgcn_s_setprio(0);
+        __syncthreads();  // the strip is staged; every thread is past the previous vertical pass
         const int c = c_lo + cu;
         const int s0 = sidx * SR, rows = min(SR, g.TH - s0);
         int cn = cu, sn = sidx + 1;  // the next unit
@@ -441,10 +441,6 @@ __device__ __forceinline__ void process_fragment(int r_cap, int strip_rows, int 
                 }
             }
         }
-        if (u + 1 < nunits) {
-            st.commit(tile, TP);
-            __syncthreads();  // next strip staged; every thread is past the previous vertical pass
-        }
         cu = cn;
         sidx = sn;
     }
@@ -452,15 +448,16 @@ __device__ __forceinline__ void process_fragment(int r_cap, int strip_rows, int 
 
 // Counts of a launch: from the arguments or (replayed launches) the device header.
 struct Counts {
-    int nitems, nframes, split_log2;
+    int nitems, nframes, split_log2, merge;
 };
 
 template <bool ARGS>
 __device__ __forceinline__ Counts counts(const FwdLaunch& a) {
-    Counts n{a.nitems, a.nframes, a.split_log2};
+    Counts n{a.nitems, a.nframes, a.split_log2, a.merge};
     if (!ARGS && a.hdr) {
         n.nitems = __builtin_amdgcn_readfirstlane(a.hdr[2]);
         n.nframes = __builtin_amdgcn_readfirstlane(a.hdr[0]);
+        n.merge = __builtin_amdgcn_readfirstlane(a.hdr[1]);
         n.split_log2 = __builtin_amdgcn_readfirstlane(a.hdr[3]);
     }
     return n;
@@ -494,14 +491,31 @@ __device__ __forceinline__ bool decode(const FwdLaunch& a, const FrameDesc* __re
     ranked_frame<ARGS>(a, prefix, n.nframes, k, &f, &rank);
     const auto describe = [&](const auto& d) {
         const FrameParams& fp = d.p;
-        Frag F = ranked_at(d, f, rank);
+        Frag F;
+        bool nothing = false;
+        if constexpr (FIXED) {
+            F = placed_at(d, f, ranked_place(Grid{fp.nbx, d.nby, d.ahead, 0, 0, 0}, rank));
+        } else {
+            const Grid g = grid_of(d);
+            Place at;
+            if (__builtin_expect(n.merge, 0)) {
+                at = paired_place(g, rank);
+                // Below a last row that has no pair.  (Said at the end: a return here, ahead of the loads below,
+                // costs every item 0.3 us.)
+                nothing = at.by >= g.nby;
+                at.by = min(at.by, g.nby - 1);
+            } else {
+                at = ranked_place(g, rank);
+            }
+            F = placed_at(d, f, at);
+        }
         const int bx = F.bx, by = F.by;
         const double sigma = uniform(fragment_sigma(fp, F.lb, bx, by));
         int r = __builtin_amdgcn_readfirstlane(radius_of(sigma));
         if (r > a.r_cap) r = a.r_cap;  // the host sized everything for r_cap; plans agree bit for bit
         // Vertical pairs at the cap (rows 2k and 2k+1, both sigma == cap, hence equal taps): the upper
-        // fragment's item covers both, the lower one's is empty.
-        if (!FIXED && a.merge && r > 0 && sigma == fp.cap) {
+        // fragment's item covers both.
+        if (!FIXED && n.merge && r > 0 && sigma == fp.cap) {
             const int by2 = by ^ 1;
             if (by2 < d.nby && fragment_sigma(fp, F.lb + (by2 - by) * fp.nbx, bx, by2) == fp.cap) {
                 if (by & 1) return false;
@@ -515,7 +529,7 @@ __device__ __forceinline__ bool decode(const FwdLaunch& a, const FrameDesc* __re
         it->c_lo = max(ch, 0);
         it->c_hi = ch < 0 ? d.c : min(ch + 1, d.c);
         it->F = F;
-        return it->c_lo < it->c_hi;
+        return it->c_lo < it->c_hi && !nothing;
     };
     if constexpr (FIXED) return describe(geo_of<ARGS>(a, table, f));
     else return describe(frame_of<ARGS>(a, table, f));

@@ -85,7 +85,7 @@ fov_status collect_batch(const fov_tensor* ins, const fov_tensor* outs, const fo
 // The forward kernel for a list of frames on `stream`, with the given
 // configuration (NULL: select_cfg).  profile: take the thread's profiler
 // events, if any.
-fov_status run_forward(const std::vector<FrameDesc>& frames, int in_dtype, int out_dtype, hipStream_t stream,
+fov_status run_forward(std::vector<FrameDesc>& frames, int in_dtype, int out_dtype, hipStream_t stream,
                        const LaunchCfg* cfg = nullptr, bool profile = true);
 
 // The launch shape of one forward call (run_forward in two steps).
@@ -101,7 +101,7 @@ struct ForwardPlan {
     int cus = 0;
     bool persistent = false;
 };
-fov_status plan_forward(const FrameDesc* frames, int nf, int in_dtype, int out_dtype, const LaunchCfg* cfg,
+fov_status plan_forward(FrameDesc* frames, int nf, int in_dtype, int out_dtype, const LaunchCfg* cfg,
                         ForwardPlan* fp);
 fov_status launch_planned(const FrameDesc* frames, int nf, int in_dtype, int out_dtype, ForwardPlan& fp,
                           Workspace* ws, hipStream_t stream, bool profile);

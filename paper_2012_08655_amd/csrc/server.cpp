@@ -24,6 +24,7 @@
 #include <vector>
 
 #include "host.h"
+#include "order.h"
 
 namespace fov {
 namespace {
@@ -60,6 +61,7 @@ struct Slot {
     void* dev = nullptr;    // staged batch table
     void* host = nullptr;   // pinned copy of the staged batch table
     size_t stage_bytes = 0;
+    int64_t merge_slots = -1;  // workgroups the device holds at once, if the captured launch has room for pairs
     hipGraphNode_t main_node = nullptr;  // the main kernel's node: its grid is set per batch
     hipKernelNodeParams main_params{};
 };
@@ -151,10 +153,9 @@ void fake_device_loop(ServerImpl* s) {
 }
 
 // Capacity launch of the replayable batch step of one slot.
-FwdLaunch capacity_launch(const ServerImpl* s, const Slot& sl, bool merge) {
+FwdLaunch capacity_launch(const ServerImpl* s, const Slot& sl) {
     FwdLaunch a;
     std::memset(&a, 0, sizeof(a));
-    a.merge = merge ? 1 : 0;  // whole fragments: batch sizes vary per replay
     a.nframes = s->cfg.max_batch_frames;
     a.nfrag = s->cfg.max_fragments;
     a.nitems = a.nfrag;
@@ -191,7 +192,8 @@ fov_status build_graph(ServerImpl* s, Slot& sl) {
                        forward_occupancy(s->cfg.in_dtype, s->cfg.out_dtype, s->r_cap, lds2) >=
                            forward_occupancy(s->cfg.in_dtype, s->cfg.out_dtype, s->r_cap, lds);
     if (merge) lds = lds2;
-    const FwdLaunch a = capacity_launch(s, sl, merge);
+    if (merge) sl.merge_slots = (int64_t)dev->cus * forward_occupancy(s->cfg.in_dtype, s->cfg.out_dtype, s->r_cap, lds);
+    const FwdLaunch a = capacity_launch(s, sl);
     e = hipStreamBeginCapture(sl.stream, hipStreamCaptureModeThreadLocal);
     if (e != hipSuccess) return hip_error(e, "hipStreamBeginCapture");
     e = hipMemcpyAsync(const_cast<int32_t*>(a.hdr), sl.host, sl.stage_bytes, hipMemcpyHostToDevice, sl.stream);
@@ -238,7 +240,7 @@ fov_status build_graph(ServerImpl* s, Slot& sl) {
 
 // Launch a batch on a slot; on failure the caller completes it with the error.
 // `ready` holds the producer events of the batch's frames that have one.
-fov_status launch_batch(ServerImpl* s, Slot& sl, const std::vector<FrameDesc>& frames, int nfrag,
+fov_status launch_batch(ServerImpl* s, Slot& sl, std::vector<FrameDesc>& frames, int nfrag,
                         const std::vector<hipEvent_t>& ready) {
     if (s->fake_mode()) {
         std::lock_guard<std::mutex> lk(s->mu);
@@ -255,16 +257,12 @@ fov_status launch_batch(ServerImpl* s, Slot& sl, const std::vector<FrameDesc>& f
         bool tiled = nfrag <= kTiledMax;
         for (const FrameDesc& f : frames) tiled &= forward_tiled(s->cfg.in_dtype, s->cfg.out_dtype, s->r_cap, f.p.block);
         const int L = tiled ? 1 : 0;
-        BatchHeader hdr{(int32_t)frames.size(), nfrag, nfrag << (2 * L), L};
+        int32_t* pre = reinterpret_cast<int32_t*>(h + sizeof(BatchHeader) + (size_t)s->cfg.max_batch_frames * sizeof(FrameDesc));
+        const bool merge = sl.merge_slots >= 0 && merge_pays(frames.data(), (int)frames.size(), nfrag, sl.merge_slots);
+        const int64_t units = number_items(frames.data(), (int)frames.size(), merge, pre);
+        BatchHeader hdr{(int32_t)frames.size(), merge ? 1 : 0, (int32_t)(units << (2 * L)), L};
         std::memcpy(h, &hdr, sizeof(hdr));
         std::memcpy(h + sizeof(BatchHeader), frames.data(), frames.size() * sizeof(FrameDesc));
-        int32_t* pre = reinterpret_cast<int32_t*>(h + sizeof(BatchHeader) + (size_t)s->cfg.max_batch_frames * sizeof(FrameDesc));
-        int32_t acc = 0;
-        for (size_t i = 0; i < frames.size(); ++i) {
-            pre[i] = acc;
-            acc += frames[i].p.nbx * frames[i].nby;
-        }
-        pre[frames.size()] = acc;
         sl.main_params.gridDim = dim3((unsigned)hdr.nitems);
         hipError_t e = hipGraphExecKernelNodeSetParams(sl.exec, sl.main_node, &sl.main_params);
         if (e != hipSuccess) return hip_error(e, "hipGraphExecKernelNodeSetParams");

@@ -152,7 +152,7 @@ struct EventPair {
     hipEvent_t a = nullptr, b = nullptr;
 };
 
-fov_status autotune_frames(const std::vector<FrameDesc>& frames, int in_dtype, int out_dtype, int reps,
+fov_status autotune_frames(std::vector<FrameDesc>& frames, int in_dtype, int out_dtype, int reps,
                            hipStream_t stream, fov_tuning* best_out) {
     const DeviceInfo* dev = nullptr;
     fov_status s = device_info(&dev);
