@@ -397,6 +397,26 @@ CallShape call_shape(const FrameDesc* frames, int nf) {
     return cs;
 }
 
+// Frames whose output the 8-bit kernel cannot store run on the FP32 kernel, with the same bytes.
+//
+// One channel leaves two of the 8-bit kernel's three product waves empty, and fragments of at most 16 px most
+// of its tile: the FP32 kernel then, with the same bytes, unless a configuration says otherwise; so too
+// for large fragments with small radii, whose windows it stages once where the 8-bit kernel stages one per
+// tile, if there are enough of them.  Per call, 8-bit kernel / FP32 kernel, gray, radii up to 24 and 48: 16 px, 600 x
+// 900 22 / 17 and 23 / 17 us, 1080 x 1920 75 / 63 and 87 / 79, 2160 x 3840 273 / 155 and 347 / 239; 24 px, 2160 x 3840
+// 135 / 147 and 176 / 267; 32 px 81 / 96 and 107 / 166; 64 px 81 / 50 and 108 / 121, 1080 x 1920 24 / 19 and 30 / 34, 720 x 1000
+// 12 / 16 and 12 / 24; three channels, 16 px, 1080 x 1920 95 / 147 and 120 / 201.
+bool on_fp32(const FrameDesc* frames, int nf, int in_dtype, int out_dtype, int r_cap, const CallShape& cs, bool by_rule,
+             int cus) {
+    if (!forward_fixed(in_dtype, out_dtype, r_cap)) return false;
+    int bmin = cs.bmax;
+    for (int i = 0; i < nf; ++i) {
+        if (!forward_fixed_reaches(frames[i])) return true;
+        bmin = std::min(bmin, frames[i].p.block);
+    }
+    return by_rule && cs.c == 1 && (cs.bmax <= 16 || (bmin > 32 && cs.r_cap <= 32 && cs.nfrag >= cus));
+}
+
 // Bytes that the plans of a call's fragments (radius, taps and queue slots of every fragment) take when
 // written out; foveate_forward_noalloc's size limit is stated in them.
 size_t plan_bytes(const FwdLaunch& a, int split_log2, bool by_channel, int tap_size) {
@@ -418,17 +438,7 @@ fov_status plan_forward(FrameDesc* frames, int nf, int in_dtype, int out_dtype, 
     const DeviceInfo* dev = nullptr;
     if ((s = device_info(&dev)) != FOV_OK) return s;
     const LaunchCfg cfg = cfg_in ? *cfg_in : select_cfg(nf, in_dtype, out_dtype, cs);
-    // One channel leaves two of the 8-bit kernel's three product waves empty, and fragments of at most 16 px most
-    // of its tile: the FP32 kernel then, with the same bytes, unless a configuration says otherwise; so too
-    // for large fragments with small radii, whose windows it stages once where the 8-bit kernel stages one per
-    // tile, if there are enough of them.  Per call, 8-bit kernel / FP32 kernel, gray, radii up to 24 and 48: 16 px, 600 x
-    // 900 22 / 17 and 23 / 17 us, 1080 x 1920 75 / 63 and 87 / 79, 2160 x 3840 273 / 155 and 347 / 239; 24 px, 2160 x 3840
-    // 135 / 147 and 176 / 267; 32 px 81 / 96 and 107 / 166; 64 px 81 / 50 and 108 / 121, 1080 x 1920 24 / 19 and 30 / 34, 720 x 1000
-    // 12 / 16 and 12 / 24; three channels, 16 px, 1080 x 1920 95 / 147 and 120 / 201.
-    int bmin = cs.bmax;
-    for (int i = 0; i < nf; ++i) bmin = std::min(bmin, frames[i].p.block);
-    const bool fp32 = forward_fixed(in_dtype, out_dtype, cs.r_cap) && cfg.chan_split < 0 && cs.c == 1 &&
-                      (cs.bmax <= 16 || (bmin > 32 && cs.r_cap <= 32 && cs.nfrag >= dev->cus));
+    const bool fp32 = on_fp32(frames, nf, in_dtype, out_dtype, cs.r_cap, cs, cfg.chan_split < 0, dev->cus);
     // the 8-bit kernel's fragments of several tiles: an item each, unless a configuration says otherwise
     bool tiled = !fp32 && cfg.chan_split < 0 && cfg.split_log2 == 0 && cs.nfrag <= kTiledMax;
     for (int i = 0; i < nf && tiled; ++i) tiled = forward_tiled(in_dtype, out_dtype, cs.r_cap, frames[i].p.block);

@@ -129,6 +129,12 @@ __device__ __forceinline__ void load_words(uint32_t* v, global_ptr<const uint8_t
     __builtin_memcpy(v, (const void*)p, 4 * N);
 }
 
+// Whether a tile's bytes lie within 32-bit offsets of its first one in the output.
+__host__ __device__ inline bool fx_reaches(const FrameDesc& d) {
+    const int64_t rows = (d.p.block < kFxTile ? d.p.block : kFxTile) - 1;
+    return (d.h <= rows ? d.h - 1 : rows) * d.osh + (d.w <= rows ? d.w - 1 : rows) * d.osw < (int64_t)1 << 32;
+}
+
 // Staging of a tile's samples (rows y0.., columns x0.., clamped to the frame) in LDS, channel planes
 // apart.  A lane takes 16 columns of a row at a time (8 lanes to a row, 4 where a window is two blocks
 // wide): fewer and wider loads than one group of four columns per lane, whose 12-byte loads cost the

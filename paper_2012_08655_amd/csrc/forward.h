@@ -82,6 +82,10 @@ const void* forward_main_kernel(int in_dtype, int out_dtype, int r_cap, bool fp3
 // cores (8-bit output; see fixed.h).
 bool forward_fixed(int in_dtype, int out_dtype, int r_cap);
 
+// Whether that kernel can store this frame's output, whose rows may lie far apart (it forms
+// a tile's offsets in 32 bits).
+bool forward_fixed_reaches(const FrameDesc& d);
+
 // Whether fragments of this side are split into a work item per tile there.  Each tile is staged and
 // filtered by itself, so an item for each costs nothing more and fills the chip sooner.
 bool forward_tiled(int in_dtype, int out_dtype, int r_cap, int block);

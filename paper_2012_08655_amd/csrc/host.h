@@ -71,6 +71,11 @@ CallShape call_shape(const FrameDesc* frames, int nf);
 // entry for the call's class, else the defaults.
 LaunchCfg select_cfg(int nframes, int in_dtype, int out_dtype, const CallShape& cs);
 
+// Whether a launch runs on the FP32 kernel although its radii (up to r_cap, which the launch is sized
+// for) let 8-bit output run on the matrix cores; by_rule: also where it is only faster.
+bool on_fp32(const FrameDesc* frames, int nf, int in_dtype, int out_dtype, int r_cap, const CallShape& cs, bool by_rule,
+             int cus);
+
 // Validation of a forward (or backward) call's views and parameters.
 fov_status prepare(const fov_tensor* in, const fov_tensor* out, const fov_params* p, int32_t np, bool backward,
                    bool* empty);

@@ -46,6 +46,15 @@ struct Req {
 
 struct ServerImpl;
 
+// A captured batch step: table copy, forward kernel, completion.
+struct Replay {
+    hipGraph_t graph = nullptr;
+    hipGraphExec_t exec = nullptr;
+    hipGraphNode_t main_node = nullptr;  // the forward kernel's node: its grid is set per batch
+    hipKernelNodeParams main_params{};
+    int64_t merge_slots = -1;  // workgroups the device holds at once, if the captured launch has room for pairs
+};
+
 struct Slot {
     ServerImpl* owner = nullptr;
     int index = 0;
@@ -55,15 +64,11 @@ struct Slot {
     std::vector<uint64_t> tickets;
     size_t bytes = 0;
     int status = FOV_OK;
-    // graph replay
-    hipGraph_t graph = nullptr;
-    hipGraphExec_t exec = nullptr;
-    void* dev = nullptr;    // staged batch table
-    void* host = nullptr;   // pinned copy of the staged batch table
+    // graph replay: of the default kernel, and for 8-bit output also of the FP32 kernel (see on_fp32())
+    Replay replay[2];
+    void* dev = nullptr;   // staged batch table
+    void* host = nullptr;  // pinned copy of the staged batch table
     size_t stage_bytes = 0;
-    int64_t merge_slots = -1;  // workgroups the device holds at once, if the captured launch has room for pairs
-    hipGraphNode_t main_node = nullptr;  // the main kernel's node: its grid is set per batch
-    hipKernelNodeParams main_params{};
 };
 
 struct FakeItem {
@@ -91,6 +96,7 @@ namespace {
 struct ServerImpl {
     fov_server_cfg cfg{};
     int device = 0;
+    int cus = 0;
     int r_cap = 0;
     std::mutex mu;
     std::condition_variable cv;
@@ -153,7 +159,7 @@ void fake_device_loop(ServerImpl* s) {
 }
 
 // Capacity launch of the replayable batch step of one slot.
-FwdLaunch capacity_launch(const ServerImpl* s, const Slot& sl) {
+FwdLaunch capacity_launch(const ServerImpl* s, const Slot& sl, bool fp32) {
     FwdLaunch a;
     std::memset(&a, 0, sizeof(a));
     a.nframes = s->cfg.max_batch_frames;
@@ -161,6 +167,7 @@ FwdLaunch capacity_launch(const ServerImpl* s, const Slot& sl) {
     a.nitems = a.nfrag;
     a.r_cap = s->r_cap;
     a.strip_rows = choose_strip_rows();
+    a.fp32 = fp32 ? 1 : 0;
     char* stage = static_cast<char*>(sl.dev);
     a.hdr = reinterpret_cast<const int32_t*>(stage);
     a.table = reinterpret_cast<FrameDesc*>(stage + sizeof(BatchHeader));
@@ -172,34 +179,42 @@ size_t stage_bytes_of(const fov_server_cfg& c) {
     return sizeof(BatchHeader) + (size_t)c.max_batch_frames * sizeof(FrameDesc) + (size_t)(c.max_batch_frames + 1) * 4;
 }
 
-fov_status build_graph(ServerImpl* s, Slot& sl) {
-    const DeviceInfo* dev = nullptr;
-    fov_status st = device_info(&dev);
-    if (st != FOV_OK) return st;
+fov_status build_stage(ServerImpl* s, Slot& sl) {
     sl.stage_bytes = stage_bytes_of(s->cfg);
     hipError_t e = hipMalloc(&sl.dev, sl.stage_bytes);
     if (e != hipSuccess) return set_error(FOV_ENOMEM, "server workspace allocation failed");
     e = hipHostMalloc(&sl.host, sl.stage_bytes, hipHostMallocDefault);
     if (e != hipSuccess) return set_error(FOV_ENOMEM, "server staging allocation failed");
     std::memset(sl.host, 0, sl.stage_bytes);
+    return FOV_OK;
+}
+
+fov_status build_graph(ServerImpl* s, Slot& sl, bool fp32) {
+    const DeviceInfo* dev = nullptr;
+    fov_status st = device_info(&dev);
+    if (st != FOV_OK) return st;
+    Replay& rp = sl.replay[fp32];
+    const int in_dt = s->cfg.in_dtype, out_dt = s->cfg.out_dtype, r_cap = s->r_cap;
     // capped vertical pairs as one item (as the plain forward does by default) when the taller
     // tiles let as many workgroups share a CU
     const int B = s->cfg.max_block, sr = choose_strip_rows();
-    size_t lds = forward_lds_bytes(s->cfg.in_dtype, s->cfg.out_dtype, s->r_cap, B, B, sr);
+    size_t lds = forward_lds_bytes(in_dt, out_dt, r_cap, B, B, sr, fp32);
     if (lds + 64 > dev->lds_limit) return set_error(FOV_ERANGE, "max_sigma needs more LDS than a workgroup may use");
-    const size_t lds2 = forward_lds_bytes(s->cfg.in_dtype, s->cfg.out_dtype, s->r_cap, B, 2 * B, sr);
-    const bool merge = s->r_cap > 0 && !forward_fixed(s->cfg.in_dtype, s->cfg.out_dtype, s->r_cap) && lds2 + 64 <= dev->lds_limit &&
-                       forward_occupancy(s->cfg.in_dtype, s->cfg.out_dtype, s->r_cap, lds2) >=
-                           forward_occupancy(s->cfg.in_dtype, s->cfg.out_dtype, s->r_cap, lds);
-    if (merge) lds = lds2;
-    if (merge) sl.merge_slots = (int64_t)dev->cus * forward_occupancy(s->cfg.in_dtype, s->cfg.out_dtype, s->r_cap, lds);
-    const FwdLaunch a = capacity_launch(s, sl);
-    e = hipStreamBeginCapture(sl.stream, hipStreamCaptureModeThreadLocal);
+    const size_t lds2 = forward_lds_bytes(in_dt, out_dt, r_cap, B, 2 * B, sr, fp32);
+    const bool fixed = !fp32 && forward_fixed(in_dt, out_dt, r_cap);
+    if (r_cap > 0 && !fixed && lds2 + 64 <= dev->lds_limit) {
+        const int one = forward_occupancy(in_dt, out_dt, r_cap, lds, fp32), two = forward_occupancy(in_dt, out_dt, r_cap, lds2, fp32);
+        if (two >= one) {
+            lds = lds2;
+            rp.merge_slots = (int64_t)dev->cus * two;
+        }
+    }
+    const FwdLaunch a = capacity_launch(s, sl, fp32);
+    hipError_t e = hipStreamBeginCapture(sl.stream, hipStreamCaptureModeThreadLocal);
     if (e != hipSuccess) return hip_error(e, "hipStreamBeginCapture");
     e = hipMemcpyAsync(const_cast<int32_t*>(a.hdr), sl.host, sl.stage_bytes, hipMemcpyHostToDevice, sl.stream);
     st = e == hipSuccess ? FOV_OK : hip_error(e, "hipMemcpyAsync(batch table)");
-    if (st == FOV_OK)
-        st = launch_forward(a, s->cfg.in_dtype, s->cfg.out_dtype, lds, sl.stream, dev->lds_limit, dev->cus, false);
+    if (st == FOV_OK) st = launch_forward(a, in_dt, out_dt, lds, sl.stream, dev->lds_limit, dev->cus, false);
     if (st == FOV_OK) {
         e = hipLaunchHostFunc(sl.stream, on_batch_done, &sl);
         if (e != hipSuccess) st = hip_error(e, "hipLaunchHostFunc");
@@ -211,10 +226,10 @@ fov_status build_graph(ServerImpl* s, Slot& sl) {
         return st;
     }
     if (e2 != hipSuccess) return hip_error(e2, "hipStreamEndCapture");
-    sl.graph = g;
+    rp.graph = g;
     // The main kernel was captured with one workgroup per item of the largest
     // batch; each replay sets its grid to the batch's own item count.
-    const void* main_fn = forward_main_kernel(s->cfg.in_dtype, s->cfg.out_dtype, s->r_cap);
+    const void* main_fn = forward_main_kernel(in_dt, out_dt, r_cap, fp32);
     size_t nnodes = 0;
     e = hipGraphGetNodes(g, nullptr, &nnodes);
     if (e != hipSuccess) return hip_error(e, "hipGraphGetNodes");
@@ -228,12 +243,12 @@ fov_status build_graph(ServerImpl* s, Slot& sl) {
         e = hipGraphKernelNodeGetParams(n, &kp);
         if (e != hipSuccess) return hip_error(e, "hipGraphKernelNodeGetParams");
         if (kp.func == main_fn) {
-            sl.main_node = n;
-            sl.main_params = kp;
+            rp.main_node = n;
+            rp.main_params = kp;
         }
     }
-    if (!sl.main_node) return set_error(FOV_EHIP, "captured batch graph has no main kernel node");
-    e = hipGraphInstantiate(&sl.exec, g, nullptr, nullptr, 0);
+    if (!rp.main_node) return set_error(FOV_EHIP, "captured batch graph has no main kernel node");
+    e = hipGraphInstantiate(&rp.exec, g, nullptr, nullptr, 0);
     if (e != hipSuccess) return hip_error(e, "hipGraphInstantiate");
     return FOV_OK;
 }
@@ -253,20 +268,24 @@ fov_status launch_batch(ServerImpl* s, Slot& sl, std::vector<FrameDesc>& frames,
         if (e != hipSuccess) return hip_error(e, "hipStreamWaitEvent(ready)");
     }
     if (s->cfg.use_graph) {
-        char* h = static_cast<char*>(sl.host);
-        bool tiled = nfrag <= kTiledMax;
+        const int nf = (int)frames.size();
+        const CallShape cs = call_shape(frames.data(), nf);
+        const bool fp32 = on_fp32(frames.data(), nf, s->cfg.in_dtype, s->cfg.out_dtype, s->r_cap, cs, true, s->cus);
+        Replay& rp = sl.replay[fp32];
+        bool tiled = !fp32 && nfrag <= kTiledMax;
         for (const FrameDesc& f : frames) tiled &= forward_tiled(s->cfg.in_dtype, s->cfg.out_dtype, s->r_cap, f.p.block);
         const int L = tiled ? 1 : 0;
+        char* h = static_cast<char*>(sl.host);
         int32_t* pre = reinterpret_cast<int32_t*>(h + sizeof(BatchHeader) + (size_t)s->cfg.max_batch_frames * sizeof(FrameDesc));
-        const bool merge = sl.merge_slots >= 0 && merge_pays(frames.data(), (int)frames.size(), nfrag, sl.merge_slots);
-        const int64_t units = number_items(frames.data(), (int)frames.size(), merge, pre);
-        BatchHeader hdr{(int32_t)frames.size(), merge ? 1 : 0, (int32_t)(units << (2 * L)), L};
+        const bool merge = rp.merge_slots >= 0 && merge_pays(frames.data(), nf, nfrag, rp.merge_slots);
+        const int64_t units = number_items(frames.data(), nf, merge, pre);
+        BatchHeader hdr{nf, merge ? 1 : 0, (int32_t)(units << (2 * L)), L};
         std::memcpy(h, &hdr, sizeof(hdr));
         std::memcpy(h + sizeof(BatchHeader), frames.data(), frames.size() * sizeof(FrameDesc));
-        sl.main_params.gridDim = dim3((unsigned)hdr.nitems);
-        hipError_t e = hipGraphExecKernelNodeSetParams(sl.exec, sl.main_node, &sl.main_params);
+        rp.main_params.gridDim = dim3((unsigned)hdr.nitems);
+        hipError_t e = hipGraphExecKernelNodeSetParams(rp.exec, rp.main_node, &rp.main_params);
         if (e != hipSuccess) return hip_error(e, "hipGraphExecKernelNodeSetParams");
-        e = hipGraphLaunch(sl.exec, sl.run);
+        e = hipGraphLaunch(rp.exec, sl.run);
         if (e != hipSuccess) return hip_error(e, "hipGraphLaunch");
         return FOV_OK;
     }
@@ -364,8 +383,10 @@ fov_status validate_cfg(const fov_server_cfg& c) {
 void release(ServerImpl* s) {
     for (Slot& sl : s->slots) {
         if (sl.stream) (void)hipStreamSynchronize(sl.stream);
-        if (sl.exec) (void)hipGraphExecDestroy(sl.exec);
-        if (sl.graph) (void)hipGraphDestroy(sl.graph);
+        for (Replay& rp : sl.replay) {
+            if (rp.exec) (void)hipGraphExecDestroy(rp.exec);
+            if (rp.graph) (void)hipGraphDestroy(rp.graph);
+        }
         if (sl.dev) (void)hipFree(sl.dev);
         if (sl.host) (void)hipHostFree(sl.host);
         if (sl.stream) (void)hipStreamDestroy(sl.stream);
@@ -412,15 +433,25 @@ fov_status foveate_server_create(const fov_server_cfg* cfg, fov_server** out) {
             release(s);
             return hip_error(e, "hipGetDevice");
         }
+        const DeviceInfo* dev = nullptr;
+        if ((st = device_info(&dev)) != FOV_OK) {
+            release(s);
+            return st;
+        }
+        s->cus = dev->cus;
         for (Slot& sl : s->slots) {
             e = hipStreamCreateWithFlags(&sl.stream, hipStreamNonBlocking);
             if (e != hipSuccess) {
                 release(s);
                 return hip_error(e, "hipStreamCreate");
             }
-            if (cfg->use_graph && (st = build_graph(s, sl)) != FOV_OK) {
-                release(s);
-                return st;
+            if (cfg->use_graph) {
+                if ((st = build_stage(s, sl)) == FOV_OK) st = build_graph(s, sl, false);
+                if (st == FOV_OK && forward_fixed(s->cfg.in_dtype, s->cfg.out_dtype, s->r_cap)) st = build_graph(s, sl, true);
+                if (st != FOV_OK) {
+                    release(s);
+                    return st;
+                }
             }
             sl.run = cfg->shared_stream ? s->slots[0].stream : sl.stream;
         }
