@@ -399,22 +399,47 @@ CallShape call_shape(const FrameDesc* frames, int nf) {
 
 // Frames whose output the 8-bit kernel cannot store run on the FP32 kernel, with the same bytes.
 //
-// One channel leaves two of the 8-bit kernel's three product waves empty, and fragments of at most 16 px most
-// of its tile: the FP32 kernel then, with the same bytes, unless a configuration says otherwise; so too
-// for large fragments with small radii, whose windows it stages once where the 8-bit kernel stages one per
-// tile, if there are enough of them.  Per call, 8-bit kernel / FP32 kernel, gray, radii up to 24 and 48: 16 px, 600 x
-// 900 22 / 17 and 23 / 17 us, 1080 x 1920 75 / 63 and 87 / 79, 2160 x 3840 273 / 155 and 347 / 239; 24 px, 2160 x 3840
-// 135 / 147 and 176 / 267; 32 px 81 / 96 and 107 / 166; 64 px 81 / 50 and 108 / 121, 1080 x 1920 24 / 19 and 30 / 34, 720 x 1000
-// 12 / 16 and 12 / 24; three channels, 16 px, 1080 x 1920 95 / 147 and 120 / 201.
+// By rule also those that it is faster for.  A tile of the 8-bit kernel takes the same time whatever it holds (2160 x 3840,
+// radii up to 16 / 32 / 48: 8 / 12 / 15 ns a tile with three channels in flight over the chip, 7 / 9 / 11 with one), so it loses where a
+// tile holds little: fragments of at most 16 px, sides that leave most of their second tile empty, few channels.
+// Calls of 2160 x 3840 x c, 8-bit kernel / FP32 kernel, us:
+//   c = 3, 16 px, radii up to 16 275 / 212, 24 365 / 326, 32 395 / 405; 24 px, 3 128 / 94, 16 138 / 169; 32 px, 3 73 / 73, 16 79 / 110; 40 px, 24
+//   248 / 175, 32 269 / 310; 48 px, 24 178 / 164, 32 196 / 221; 64 px, 3 75 / 67, 16 80 / 102;
+//   c = 2, 16 px, 32 340 / 292, 40 398 / 336, 48 417 / 403; 40 px, 40 273 / 255; 48 px, 32 170 / 150, 40 200 / 214;
+//   c = 4, 16 px, 24 562 / 422, 32 619 / 529, 40 727 / 623, 48 771 / 754;
+//   c = 1, 16 px, 24 274 / 139, 48 350 / 218; 24 px, 48 179 / 163; 32 px, 24 79 / 58, 48 110 / 108; 40 px, 48 246 / 210; 48 px, 40 169 / 110; 64 px,
+//   32 88 / 63, 40 104 / 108.
+// With few fragments the chip is not full and the 8-bit kernel's shorter items win: c = 3, 12 px, 16, 480 x 640 (2160 fragments) 23 / 30, 720 x
+// 1280 (6420) 58 / 50; 40 px, 24, 480 x 640 (192) 14 / 17, 720 x 1280 (576) 34 / 34; c = 1, 48 px, 32, 480 x 640 (140) 10 / 15, 720 x 1280 (405) 22 / 20.
+// Bytewise staging, four interleaved channels: 32 px, 16 270 / 142, 48 1000 / 370; a sixth of the fragments decides.
 bool on_fp32(const FrameDesc* frames, int nf, int in_dtype, int out_dtype, int r_cap, const CallShape& cs, bool by_rule,
              int cus) {
     if (!forward_fixed(in_dtype, out_dtype, r_cap)) return false;
-    int bmin = cs.bmax;
+    int bmin = cs.bmax, cmin = cs.c;
+    int64_t bytewise = 0;  // fragments
     for (int i = 0; i < nf; ++i) {
-        if (!forward_fixed_reaches(frames[i])) return true;
-        bmin = std::min(bmin, frames[i].p.block);
+        const FrameDesc& f = frames[i];
+        if (!forward_fixed_reaches(f)) return true;
+        bmin = std::min(bmin, f.p.block);
+        cmin = std::min(cmin, f.c);
+        if (forward_fixed_bytewise(f)) bytewise += (int64_t)f.p.nbx * f.nby;
     }
-    return by_rule && cs.c == 1 && (cs.bmax <= 16 || (bmin > 32 && cs.r_cap <= 32 && cs.nfrag >= cus));
+    if (!by_rule) return false;
+    const int r = cs.r_cap, bmax = cs.bmax;
+    const int64_t per_cu = cs.nfrag / cus;
+    if (6 * bytewise > cs.nfrag && (cs.c > 1 || 2 * cs.nfrag >= cus)) return true;
+    if (cs.c == 1) {
+        if (bmax <= 16) return true;
+        if (bmax <= 32) return r <= 24 || (r <= 36 && per_cu >= 9) || per_cu >= 24;
+        return bmin > 32 && per_cu >= 1 && (r <= 32 || (bmax <= 48 && (r <= 40 || per_cu >= 5)));
+    }
+    if (cmin < cs.c) return false;
+    const bool sparse = 2 * ((cs.c + 2) / 3) >= cs.c;  // at most two channels a tile on average
+    if (bmax <= 16) return r <= 8 || (r <= 24 && per_cu >= (sparse ? 12 : 28)) || (sparse && r <= 40 && per_cu >= 28);
+    if (bmax <= 32) return r <= 8 && (sparse || (bmax <= 28 && per_cu >= 9));
+    if (bmin <= 32) return false;
+    if (bmax > 48) return bmin > 48 && r <= 4 && per_cu >= 1;
+    return (r <= 24 && per_cu >= 2) || (sparse && per_cu >= 9 && (r <= 36 || (r <= 40 && per_cu >= 16)));
 }
 
 // Bytes that the plans of a call's fragments (radius, taps and queue slots of every fragment) take when

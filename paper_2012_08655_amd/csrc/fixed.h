@@ -141,9 +141,14 @@ __host__ __device__ inline bool fx_reaches(const FrameDesc& d) {
 // L1 twice the accesses per row.
 //   kRgb: interleaved three-channel rows, 48 bytes per lane, split into planes in registers;
 //   kUnit: column stride 1, 16 bytes per lane and channel;
-//   kBytes: any strides (and frames narrower than four columns), byte by byte, straight to LDS.
+//   kBytes: any strides (and frames narrower than four columns), byte by byte, straight to LDS: slower than the
+//   FP32 kernel (on_fp32()).
 // A frame spans less than 2^31 bytes, so offsets are 32-bit.
 enum { kRgb = 0, kUnit = 1, kBytes = 2 };
+template <typename D>
+__host__ __device__ inline int fx_mode(const D& d) {
+    return d.w < 4 ? kBytes : (d.isw == 3 && d.isc == 1 && d.c == 3 ? kRgb : (d.isw == 1 ? kUnit : kBytes));
+}
 
 template <int NK>
 struct FxStager {
@@ -179,7 +184,7 @@ struct FxStager {
                                          int wave, int lane) {
         c0 = c0_;
         nc = nc_;
-        const int mode = d.w < 4 ? kBytes : (d.isw == 3 && d.isc == 1 && d.c == 3 ? kRgb : (d.isw == 1 ? kUnit : kBytes));
+        const int mode = fx_mode(d);
         rgb = mode == kRgb;
         lrow = kRows * wave + lane / kLanes;
         col = 16 * (lane & (kLanes - 1));

@@ -82,6 +82,9 @@ const void* forward_main_kernel(int in_dtype, int out_dtype, int r_cap, bool fp3
 // cores (8-bit output; see fixed.h).
 bool forward_fixed(int in_dtype, int out_dtype, int r_cap);
 
+// Whether that kernel reads this frame byte by byte (interleaved channels other than three, spaced columns).
+bool forward_fixed_bytewise(const FrameDesc& d);
+
 // Whether that kernel can store this frame's output, whose rows may lie far apart (it forms
 // a tile's offsets in 32 bits).
 bool forward_fixed_reaches(const FrameDesc& d);

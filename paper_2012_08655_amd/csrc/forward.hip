@@ -677,6 +677,8 @@ bool forward_fixed(int in_dtype, int out_dtype, int r_cap) {
     return in_dtype == FOV_U8 && out_dtype == FOV_U8 && r_cap >= 1 && r_cap <= kFxRadius;
 }
 
+bool forward_fixed_bytewise(const FrameDesc& d) { return d.w >= 4 && fx_mode(d) == kBytes; }
+
 bool forward_fixed_reaches(const FrameDesc& d) { return fx_reaches(d); }
 
 // Per call: 354 x 563 gray, 64 px fragments, 24.1 -> 9.8 us; 1080 x 1920 x 3, 64 px, 63 -> 46; 400 x 600 x 3, 48 px, 33 -> 11.5.
