@@ -228,9 +228,15 @@ fov_status foveate_backward(const fov_tensor* grad_out, const fov_tensor* grad_i
  *                1 and at most 16 channels.  By default on for frames of
  *                several channels in calls of fewer fragments than nine per
  *                compute unit.
- * 8-bit output of radii up to 48 runs on a kernel of its own that takes a
- * fragment's channels together and follows `split` alone.
  *   time_us    : (output of foveate_autotune) median time of one call.
+ * 8-bit to 8-bit calls with radii up to 48 run on one of two kernels, whichever
+ * is the faster one for their layout, channels, sides, radii and number of
+ * fragments; no configuration changes that.  The one for 8-bit output takes a fragment's
+ * channels together, one workgroup per work item, and follows `split` alone:
+ * strip_rows, persistent (also as FOV_PERSISTENT in the environment), merge and
+ * chan_split have no effect there.  Its default for fragments above 32 pixels
+ * is split 2, an item for each of the tiles that it filters a fragment by anyway; a
+ * configuration that names split 1 is followed.
  */
 typedef struct {
     int32_t split, strip_rows, persistent, merge, chan_split;
@@ -244,11 +250,13 @@ typedef struct {
  * fastest in the library's tuning cache under the call's workload class:
  * device architecture and CU count, dtype pair, channels, largest fragment
  * side, the bit length of the largest radius, the bit length of the fragment
- * count and the frame-count class (1, 2..16, more).  Later forward calls of
+ * count, the frame-count class (1, 2..16, more) and, for calls of the kernel for
+ * 8-bit output, the smallest fragment side.  Later forward calls of
  * that class, from any thread, use the cached configuration; others use the
- * defaults (split 1, 64 strip rows, one workgroup per work item, merge and
- * chan_split as described above).  Writes
- * the chosen configuration to *best (may be NULL).  Arguments and errors as
+ * defaults (split 1 or as described above, 64 strip rows, one workgroup per work
+ * item, merge and chan_split as described above).  The defaults are timed as well, and
+ * kept as defaults where they are the fastest.  Writes
+ * the chosen configuration to *best (may be NULL), defaults as what they came to.  Arguments and errors as
  * foveate_forward / foveate_forward_batch; `out` holds the foveated frames on
  * return.  Synchronises `stream`.
  */
@@ -275,7 +283,9 @@ fov_status foveate_tuning_count(int32_t* n);
 /*
  * Write the tuning cache to a text file (one entry per line), or merge such a
  * file into it.  FOV_EINVAL (with the line number) for a malformed line; the
- * cache is left unchanged then.
+ * cache is left unchanged then.  Lines of the format before this one (fov-tune-v3) are
+ * taken for calls of the kernel that they were timed on, with the default's choice in place
+ * of chan_split 1, which meant something else, and are saved as they were.
  */
 fov_status foveate_tuning_save(const char* path);
 fov_status foveate_tuning_load(const char* path);

@@ -392,6 +392,7 @@ CallShape call_shape(const FrameDesc* frames, int nf) {
         cs.nfrag += (int64_t)f.p.nbx * f.nby;
         cs.r_cap = std::max(cs.r_cap, frame_r_max(f.p, f.h));
         cs.bmax = std::max(cs.bmax, f.p.block);
+        cs.bmin = i ? std::min(cs.bmin, f.p.block) : f.p.block;
         cs.c = std::max(cs.c, f.c);
     }
     return cs;
@@ -412,20 +413,17 @@ CallShape call_shape(const FrameDesc* frames, int nf) {
 // With few fragments the chip is not full and the 8-bit kernel's shorter items win: c = 3, 12 px, 16, 480 x 640 (2160 fragments) 23 / 30, 720 x
 // 1280 (6420) 58 / 50; 40 px, 24, 480 x 640 (192) 14 / 17, 720 x 1280 (576) 34 / 34; c = 1, 48 px, 32, 480 x 640 (140) 10 / 15, 720 x 1280 (405) 22 / 20.
 // Bytewise staging, four interleaved channels: 32 px, 16 270 / 142, 48 1000 / 370; a sixth of the fragments decides.
-bool on_fp32(const FrameDesc* frames, int nf, int in_dtype, int out_dtype, int r_cap, const CallShape& cs, bool by_rule,
-             int cus) {
+bool on_fp32(const FrameDesc* frames, int nf, int in_dtype, int out_dtype, int r_cap, const CallShape& cs, int cus) {
     if (!forward_fixed(in_dtype, out_dtype, r_cap)) return false;
-    int bmin = cs.bmax, cmin = cs.c;
+    int cmin = cs.c;
     int64_t bytewise = 0;  // fragments
     for (int i = 0; i < nf; ++i) {
         const FrameDesc& f = frames[i];
         if (!forward_fixed_reaches(f)) return true;
-        bmin = std::min(bmin, f.p.block);
         cmin = std::min(cmin, f.c);
         if (forward_fixed_bytewise(f)) bytewise += (int64_t)f.p.nbx * f.nby;
     }
-    if (!by_rule) return false;
-    const int r = cs.r_cap, bmax = cs.bmax;
+    const int r = cs.r_cap, bmax = cs.bmax, bmin = cs.bmin;
     const int64_t per_cu = cs.nfrag / cus;
     if (6 * bytewise > cs.nfrag && (cs.c > 1 || 2 * cs.nfrag >= cus)) return true;
     if (cs.c == 1) {
@@ -462,18 +460,18 @@ fov_status plan_forward(FrameDesc* frames, int nf, int in_dtype, int out_dtype, 
                                          " pixels; no workgroup can stage its window");
     const DeviceInfo* dev = nullptr;
     if ((s = device_info(&dev)) != FOV_OK) return s;
-    const LaunchCfg cfg = cfg_in ? *cfg_in : select_cfg(nf, in_dtype, out_dtype, cs);
-    const bool fp32 = on_fp32(frames, nf, in_dtype, out_dtype, cs.r_cap, cs, cfg.chan_split < 0, dev->cus);
+    const bool fp32 = on_fp32(frames, nf, in_dtype, out_dtype, cs.r_cap, cs, dev->cus);
+    const bool fixed = !fp32 && forward_fixed(in_dtype, out_dtype, cs.r_cap);
+    const LaunchCfg cfg = cfg_in ? *cfg_in : select_cfg(nf, in_dtype, out_dtype, cs, fixed);
     // the 8-bit kernel's fragments of several tiles: an item each, unless a configuration says otherwise
-    bool tiled = !fp32 && cfg.chan_split < 0 && cfg.split_log2 == 0 && cs.nfrag <= kTiledMax;
-    for (int i = 0; i < nf && tiled; ++i) tiled = forward_tiled(in_dtype, out_dtype, cs.r_cap, frames[i].p.block);
+    const bool tiled = fixed && cfg.chan_split < 0 && cfg.split_log2 == 0 && cs.nfrag <= kTiledMax &&
+                       forward_tiled(in_dtype, out_dtype, cs.r_cap, cs.bmin);
     const int L = tiled ? 1 : cfg.split_log2;
     if ((cs.nfrag << (2 * L)) > ((int64_t)1 << 30)) return set_error(FOV_EINVAL, "too many fragments in one call");
     const int r_cap = cs.r_cap;
     const int tile = (cs.bmax + (1 << L) - 1) >> L;
     const int sr = cfg.strip_rows;
     size_t lds = forward_lds_bytes(in_dtype, out_dtype, r_cap, tile, tile, sr, fp32);
-    const bool fixed = !fp32 && forward_fixed(in_dtype, out_dtype, r_cap);
     // One work item per channel where the fragments alone would not fill the chip several times over; above
     // that an item's sigma, taps and geometry are worked out once for its channels, and a channel is loaded while
     // the last one is computed.  A configuration may say otherwise.  Kernel time, items of one channel against

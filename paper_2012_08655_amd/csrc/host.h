@@ -62,19 +62,19 @@ struct LaunchCfg {
 
 // What a forward call launches: largest radius and fragment side, fragments.
 struct CallShape {
-    int r_cap = 0, bmax = 1, c = 1;
+    int r_cap = 0, bmax = 1, bmin = 0, c = 1;
     int64_t nfrag = 0;
 };
 CallShape call_shape(const FrameDesc* frames, int nf);
 
 // Configuration for a call: the thread's forced one, else the tuning cache's
-// entry for the call's class, else the defaults.
-LaunchCfg select_cfg(int nframes, int in_dtype, int out_dtype, const CallShape& cs);
+// entry for the call's class, else the defaults.  fixed: the call runs on the
+// 8-bit kernel.
+LaunchCfg select_cfg(int nframes, int in_dtype, int out_dtype, const CallShape& cs, bool fixed);
 
 // Whether a launch runs on the FP32 kernel although its radii (up to r_cap, which the launch is sized
-// for) let 8-bit output run on the matrix cores; by_rule: also where it is only faster.
-bool on_fp32(const FrameDesc* frames, int nf, int in_dtype, int out_dtype, int r_cap, const CallShape& cs, bool by_rule,
-             int cus);
+// for) let 8-bit output run on the matrix cores.
+bool on_fp32(const FrameDesc* frames, int nf, int in_dtype, int out_dtype, int r_cap, const CallShape& cs, int cus);
 
 // Validation of a forward (or backward) call's views and parameters.
 fov_status prepare(const fov_tensor* in, const fov_tensor* out, const fov_params* p, int32_t np, bool backward,

@@ -270,10 +270,9 @@ fov_status launch_batch(ServerImpl* s, Slot& sl, std::vector<FrameDesc>& frames,
     if (s->cfg.use_graph) {
         const int nf = (int)frames.size();
         const CallShape cs = call_shape(frames.data(), nf);
-        const bool fp32 = on_fp32(frames.data(), nf, s->cfg.in_dtype, s->cfg.out_dtype, s->r_cap, cs, true, s->cus);
+        const bool fp32 = on_fp32(frames.data(), nf, s->cfg.in_dtype, s->cfg.out_dtype, s->r_cap, cs, s->cus);
         Replay& rp = sl.replay[fp32];
-        bool tiled = !fp32 && nfrag <= kTiledMax;
-        for (const FrameDesc& f : frames) tiled &= forward_tiled(s->cfg.in_dtype, s->cfg.out_dtype, s->r_cap, f.p.block);
+        const bool tiled = !fp32 && nfrag <= kTiledMax && forward_tiled(s->cfg.in_dtype, s->cfg.out_dtype, s->r_cap, cs.bmin);
         const int L = tiled ? 1 : 0;
         char* h = static_cast<char*>(sl.host);
         int32_t* pre = reinterpret_cast<int32_t*>(h + sizeof(BatchHeader) + (size_t)s->cfg.max_batch_frames * sizeof(FrameDesc));

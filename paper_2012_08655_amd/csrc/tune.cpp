@@ -26,15 +26,18 @@ namespace {
 struct TuneKey {
     std::string arch;
     int cus, in_dtype, out_dtype, c, bmax, r_bits, frag_bits, frames_class;
+    int fixed_bmin = 0;  // calls of the 8-bit kernel: their smallest fragment side (a split suits the kernel
+                         // and the sides that it was timed with); else 0
     bool operator<(const TuneKey& o) const {
-        return std::tie(arch, cus, in_dtype, out_dtype, c, bmax, r_bits, frag_bits, frames_class) <
-               std::tie(o.arch, o.cus, o.in_dtype, o.out_dtype, o.c, o.bmax, o.r_bits, o.frag_bits, o.frames_class);
+        return std::tie(arch, cus, in_dtype, out_dtype, c, bmax, r_bits, frag_bits, frames_class, fixed_bmin) <
+               std::tie(o.arch, o.cus, o.in_dtype, o.out_dtype, o.c, o.bmax, o.r_bits, o.frag_bits, o.frames_class, o.fixed_bmin);
     }
 };
 
 struct TuneEntry {
     LaunchCfg cfg;
     float us = 0.0f;
+    bool v3 = false;  // loaded from a version-3 line, and saved as one
 };
 
 std::mutex g_tune_mu;
@@ -51,7 +54,7 @@ int bit_length(int64_t v) {
     return b;
 }
 
-TuneKey make_key(const DeviceInfo& dev, int nframes, int in_dtype, int out_dtype, const CallShape& cs) {
+TuneKey make_key(const DeviceInfo& dev, int nframes, int in_dtype, int out_dtype, const CallShape& cs, bool fixed) {
     TuneKey k;
     k.arch = dev.arch;
     // the arch string has no blanks in practice; keep the text format safe anyway
@@ -65,6 +68,7 @@ TuneKey make_key(const DeviceInfo& dev, int nframes, int in_dtype, int out_dtype
     k.r_bits = bit_length(cs.r_cap);
     k.frag_bits = bit_length(cs.nfrag);
     k.frames_class = nframes <= 1 ? 0 : (nframes <= kArgFrames ? 1 : 2);
+    k.fixed_bmin = fixed ? cs.bmin : 0;
     return k;
 }
 
@@ -107,15 +111,15 @@ fov_tuning to_public(const LaunchCfg& c, float us) {
     return t;
 }
 
-// Every configuration that fits the device's LDS for this call.  Strip heights
+// The default and every configuration that fits the device's LDS for this call.  Strip heights
 // at or above the tallest padded tile behave alike; only the smallest such is
 // kept.  Splits stop at tiles of 8 pixels, and calls with enough fragments to
 // fill the chip several times over are not split (more halo work for
-// nothing).  The matrix-core kernel of 8-bit output has the split alone.
+// nothing).  The 8-bit kernel (fixed) has the split alone; its default may be an item
+// per tile, which no other configuration is where fragments are many.
 constexpr int64_t kSplitMaxFragments = 4096;
-std::vector<LaunchCfg> candidates(const DeviceInfo& dev, int in_dtype, int out_dtype, const CallShape& cs) {
-    std::vector<LaunchCfg> out;
-    const bool fixed = forward_fixed(in_dtype, out_dtype, cs.r_cap);
+std::vector<LaunchCfg> candidates(const DeviceInfo& dev, int in_dtype, int out_dtype, const CallShape& cs, bool fixed) {
+    std::vector<LaunchCfg> out{default_cfg()};
     for (int L = 0; L <= 2; ++L) {
         const int tile = (cs.bmax + (1 << L) - 1) >> L;
         if (L > 0 && (tile < 8 || tile == cs.bmax || cs.nfrag >= kSplitMaxFragments)) break;
@@ -129,7 +133,7 @@ std::vector<LaunchCfg> candidates(const DeviceInfo& dev, int in_dtype, int out_d
                 const int eff = std::min(sr, rows);
                 if (eff == prev) continue;
                 prev = eff;
-                if (forward_lds_bytes(in_dtype, out_dtype, cs.r_cap, tile, th, sr) + 64 > dev.lds_limit) continue;
+                if (forward_lds_bytes(in_dtype, out_dtype, cs.r_cap, tile, th, sr, !fixed) + 64 > dev.lds_limit) continue;
                 for (bool persist : {false, true})
                     for (int chan : {0, 1}) {
                         if (fixed && (persist || chan)) continue;
@@ -148,6 +152,17 @@ std::vector<LaunchCfg> candidates(const DeviceInfo& dev, int in_dtype, int out_d
     return out;
 }
 
+// The configuration that a call launches with, the default's choices named.
+fov_status effective(std::vector<FrameDesc>& frames, int in_dtype, int out_dtype, LaunchCfg* c) {
+    ForwardPlan fp;
+    const fov_status s = plan_forward(frames.data(), (int)frames.size(), in_dtype, out_dtype, c, &fp);
+    if (s != FOV_OK) return s;
+    c->split_log2 = fp.a.split_log2;
+    c->merge = fp.a.merge;
+    c->chan_split = fp.a.chan;
+    return FOV_OK;
+}
+
 struct EventPair {
     hipEvent_t a = nullptr, b = nullptr;
 };
@@ -160,11 +175,12 @@ fov_status autotune_frames(std::vector<FrameDesc>& frames, int in_dtype, int out
     if (reps < 0 || reps > 1000) return set_error(FOV_EINVAL, "reps must be in 0..1000");
     if (reps == 0) reps = 5;
     const CallShape cs = call_shape(frames.data(), (int)frames.size());
-    const std::vector<LaunchCfg> cands = candidates(*dev, in_dtype, out_dtype, cs);
-    if (cands.empty()) {
+    const bool fixed = forward_fixed(in_dtype, out_dtype, cs.r_cap) &&
+                       !on_fp32(frames.data(), (int)frames.size(), in_dtype, out_dtype, cs.r_cap, cs, dev->cus);
+    const std::vector<LaunchCfg> cands = candidates(*dev, in_dtype, out_dtype, cs, fixed);
+    if (cands.size() == 1) {
         // no configuration fits: let a plain call report the LDS error
-        const LaunchCfg d = default_cfg();
-        return run_forward(frames, in_dtype, out_dtype, stream, &d, false);
+        return run_forward(frames, in_dtype, out_dtype, stream, &cands[0], false);
     }
     std::vector<EventPair> ev(reps);
     auto release = [&]() {
@@ -218,23 +234,33 @@ fov_status autotune_frames(std::vector<FrameDesc>& frames, int in_dtype, int out
     if (e != hipSuccess) return hip_error(e, "hipStreamSynchronize(autotune)");
     {
         std::lock_guard<std::mutex> lk(g_tune_mu);
-        TuneEntry& te = g_tune[make_key(*dev, (int)frames.size(), in_dtype, out_dtype, cs)];
+        TuneEntry& te = g_tune[make_key(*dev, (int)frames.size(), in_dtype, out_dtype, cs, fixed)];
         te.cfg = bc;
         te.us = best_us;
+        te.v3 = false;
     }
-    if (best_out) *best_out = to_public(bc, best_us);
+    if (best_out) {
+        LaunchCfg named = bc;
+        if ((s = effective(frames, in_dtype, out_dtype, &named)) != FOV_OK) return s;
+        *best_out = to_public(named, best_us);
+    }
     return FOV_OK;
 }
 
-constexpr const char* kTag = "fov-tune-v3";
+// Lines of a tuning file.  Version 4 has one more field in the key (fixed_bmin), and its merge and chan_split may be
+// -1, the default's choice.  Version 3 was written when all calls ran on the FP32 kernel and chan_split 1 meant items of
+// one channel for small radii alone: such an entry is taken for calls of that kernel, with the default's choice in
+// place of that 1.
+constexpr const char* kTag = "fov-tune-v4";
+constexpr const char* kTagV3 = "fov-tune-v3";
 
 }  // namespace
 
-LaunchCfg select_cfg(int nframes, int in_dtype, int out_dtype, const CallShape& cs) {
+LaunchCfg select_cfg(int nframes, int in_dtype, int out_dtype, const CallShape& cs, bool fixed) {
     if (g_forced_on) return g_forced;
     const DeviceInfo* dev = nullptr;
     if (device_info(&dev) == FOV_OK) {
-        const TuneKey k = make_key(*dev, nframes, in_dtype, out_dtype, cs);
+        const TuneKey k = make_key(*dev, nframes, in_dtype, out_dtype, cs, fixed);
         std::lock_guard<std::mutex> lk(g_tune_mu);
         auto it = g_tune.find(k);
         if (it != g_tune.end()) return it->second.cfg;
@@ -303,14 +329,21 @@ fov_status foveate_tuning_save(const char* path) {
     }
     FILE* f = std::fopen(path, "w");
     if (!f) return set_error(FOV_EINVAL, std::string("cannot open ") + path + " for writing");
-    std::fprintf(f, "# %s arch cus in_dtype out_dtype channels block r_bits frag_bits frames_class : split strip_rows "
+    std::fprintf(f, "# %s arch cus in_dtype out_dtype channels block r_bits frag_bits frames_class fixed_block : split strip_rows "
                     "persistent merge chan_split time_us\n", kTag);
     for (const auto& kv : copy) {
         const TuneKey& k = kv.first;
-        const fov_tuning t = to_public(kv.second.cfg, kv.second.us);
-        std::fprintf(f, "%s %s %d %d %d %d %d %d %d %d : %d %d %d %d %d %.3f\n", kTag, k.arch.c_str(), k.cus,
-                     k.in_dtype, k.out_dtype, k.c, k.bmax, k.r_bits, k.frag_bits, k.frames_class, t.split,
-                     t.strip_rows, t.persistent, t.merge, t.chan_split, (double)t.time_us);
+        const LaunchCfg& c = kv.second.cfg;
+        const int split = 1 << c.split_log2, persistent = c.persistent ? 1 : 0;
+        const double us = kv.second.us;
+        if (kv.second.v3)
+            std::fprintf(f, "%s %s %d %d %d %d %d %d %d %d : %d %d %d %d %d %.3f\n", kTagV3, k.arch.c_str(), k.cus, k.in_dtype,
+                         k.out_dtype, k.c, k.bmax, k.r_bits, k.frag_bits, k.frames_class, split, c.strip_rows, persistent,
+                         c.merge, c.chan_split != 0 ? 1 : 0, us);
+        else
+            std::fprintf(f, "%s %s %d %d %d %d %d %d %d %d %d : %d %d %d %d %d %.3f\n", kTag, k.arch.c_str(), k.cus, k.in_dtype,
+                         k.out_dtype, k.c, k.bmax, k.r_bits, k.frag_bits, k.frames_class, k.fixed_bmin, split, c.strip_rows,
+                         persistent, c.merge, c.chan_split, us);
     }
     const bool ok = std::fclose(f) == 0;
     if (!ok) return set_error(FOV_EINVAL, std::string("error writing ") + path);
@@ -336,24 +369,34 @@ fov_status foveate_tuning_load(const char* path) {
         if (*p == '#' || *p == '\n' || *p == '\r' || *p == '\0') continue;
         char tag[32], arch[64];
         TuneKey k;
-        fov_tuning t;
+        fov_tuning t{};
         double us = 0.0;
         int used = 0;
-        const int got = std::sscanf(p, "%31s %63s %d %d %d %d %d %d %d %d : %d %d %d %d %d %lf %n", tag, arch,
-                                    &k.cus, &k.in_dtype, &k.out_dtype, &k.c, &k.bmax, &k.r_bits, &k.frag_bits,
-                                    &k.frames_class, &t.split, &t.strip_rows, &t.persistent, &t.merge,
-                                    &t.chan_split, &us, &used);
-        if (got != 16 || std::strcmp(tag, kTag) != 0 || p[used] != '\0' || !valid_public(t) || k.cus < 1 ||
+        const bool v3 = std::strncmp(p, kTagV3, std::strlen(kTagV3)) == 0;
+        const int got = v3 ? std::sscanf(p, "%31s %63s %d %d %d %d %d %d %d %d : %d %d %d %d %d %lf %n", tag, arch,
+                                         &k.cus, &k.in_dtype, &k.out_dtype, &k.c, &k.bmax, &k.r_bits, &k.frag_bits,
+                                         &k.frames_class, &t.split, &t.strip_rows, &t.persistent, &t.merge,
+                                         &t.chan_split, &us, &used)
+                           : std::sscanf(p, "%31s %63s %d %d %d %d %d %d %d %d %d : %d %d %d %d %d %lf %n", tag, arch,
+                                         &k.cus, &k.in_dtype, &k.out_dtype, &k.c, &k.bmax, &k.r_bits, &k.frag_bits,
+                                         &k.frames_class, &k.fixed_bmin, &t.split, &t.strip_rows, &t.persistent, &t.merge,
+                                         &t.chan_split, &us, &used);
+        fov_tuning named = t;  // the default's choices count as "off" here
+        if (!v3 && named.merge == -1) named.merge = 0;
+        if (!v3 && named.chan_split == -1) named.chan_split = 0;
+        if (got != (v3 ? 16 : 17) || std::strcmp(tag, v3 ? kTagV3 : kTag) != 0 || p[used] != '\0' || !valid_public(named) || k.cus < 1 ||
             k.in_dtype < 0 || k.in_dtype > 2 || k.out_dtype < 0 || k.out_dtype > 2 || k.c < 1 || k.bmax < 1 ||
             k.bmax > kMaxBlock || k.r_bits < 0 || k.r_bits > 31 || k.frag_bits < 0 || k.frag_bits > 62 ||
-            k.frames_class < 0 || k.frames_class > 2 || !(us >= 0.0)) {
+            k.frames_class < 0 || k.frames_class > 2 || k.fixed_bmin < 0 || k.fixed_bmin > k.bmax || !(us >= 0.0)) {
             s = set_error(FOV_EINVAL, std::string(path) + ":" + std::to_string(lineno) + ": malformed tuning entry");
             break;
         }
         k.arch = arch;
         TuneEntry te;
         te.cfg = from_public(t);
+        if (v3 && t.chan_split == 1) te.cfg.chan_split = -1;
         te.us = (float)us;
+        te.v3 = v3;
         add[k] = te;
     }
     std::fclose(f);
