@@ -92,7 +92,8 @@ bool forward_fixed_reaches(const FrameDesc& d);
 // Whether fragments of this side are split into a work item per tile there.  Each tile is staged and
 // filtered by itself, so an item for each costs nothing more and fills the chip sooner.
 bool forward_tiled(int in_dtype, int out_dtype, int r_cap, int block);
-constexpr int64_t kTiledMax = (int64_t)1 << 26;  // fragments of a call up to which that is done
+// Fragments of a call up to which that is done: a launch holds fewer than 2^32 threads, and there are four items each.
+constexpr int64_t kTiledMax = (((int64_t)1 << 32) / kThreads - 1) / 4;
 
 // Device plan for foveate_plan(): sigma and radius of every fragment.
 fov_status launch_plan(const FrameParams& fp, int nblk, double* sigma_out, int32_t* r_out, hipStream_t stream);
