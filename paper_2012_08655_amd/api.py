@@ -100,10 +100,10 @@ def _packer(n: int) -> struct.Struct:
 assert _packer(2).size == 2 * ctypes.sizeof(N.FovParams)
 
 
-def _pack_params(plist, keep: list):
+def _pack_params(plist, keep: list, n: int = 0):
     """The dicts of ``plist`` in their C form, packed by one call: 0.4 us a frame against 1.0 through a FovParams
     object each (a training batch converts its parameters twice per step).  What struct does not take as it
-    is, such as a float for ``block``, goes through make_params' conversions."""
+    is, such as a float for ``block``, goes through make_params' conversions.  At least n entries, zero past the dicts."""
     vals, ptrs = [], []
     for p in plist:
         sm = p.get("sigma_map")
@@ -119,7 +119,7 @@ def _pack_params(plist, keep: list):
             vals += _with_defaults(p)
         vals += 0, ptr or 0
         ptrs.append(ptr)
-    arr = (N.FovParams * max(len(plist), 1))()
+    arr = (N.FovParams * max(len(plist), n, 1))()
     try:
         if len(plist) <= _PACK_FRAMES:
             _packer(len(plist)).pack_into(arr, 0, *vals)
@@ -133,9 +133,13 @@ def _pack_params(plist, keep: list):
     return arr
 
 
-def _frame_params(params, keep: list):
-    """One C form per entry of ``params`` (dicts, or lists of one dict)."""
-    return _pack_params([p if isinstance(p, Mapping) else _one(p) for p in params], keep)
+def _frame_params(params, keep: list, n: int | None = None):
+    """The C forms of ``params`` (dicts, or lists of one dict), for n frames if n is given: no more than n of them, and
+    zeros, which the library refuses, where there are fewer."""
+    plist = [p if isinstance(p, Mapping) else _one(p) for p in params]
+    if n is not None and len(plist) > n:
+        raise IndexError("more params dicts than frames")
+    return _pack_params(plist, keep, n or 0)
 
 
 def _one(p):
@@ -185,7 +189,7 @@ def forward_batch(frames, params, outs=None, layout: str = "HWC", out_dtype: tor
     di = (N.FovTensor * max(n, 1))(*[tensor_desc(f, layout) for f in frames])
     do = (N.FovTensor * max(n, 1))(*[tensor_desc(o, layout) for o in outs])
     keep = []
-    arr = _frame_params(params, keep)
+    arr = _frame_params(params, keep, n)
     N.check(N.lib().foveate_forward_batch(di, do, arr, n, _stream_handle(stream)))
     return outs
 
@@ -216,7 +220,7 @@ def autotune_batch(frames, params, outs, layout: str = "HWC", reps: int = 5, str
     di = (N.FovTensor * max(n, 1))(*[tensor_desc(f, layout) for f in frames])
     do = (N.FovTensor * max(n, 1))(*[tensor_desc(o, layout) for o in outs])
     keep = []
-    arr = _frame_params(params, keep)
+    arr = _frame_params(params, keep, n)
     t = N.FovTuning()
     N.check(N.lib().foveate_autotune_batch(di, do, arr, n, int(reps), _stream_handle(stream), ctypes.byref(t)))
     return _tuning_dict(t)
