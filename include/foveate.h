@@ -87,7 +87,9 @@ typedef struct {
                                each fragment's sigma directly, in place of the
                                ramp (Sec. 4: any image may define blur strength);
                                values are clipped to [0, cap]; NaN counts as 0.
-                               NULL = use the ramp.                              */
+                               NULL = use the ramp.  Read as it is before the
+                               call's first output is written: a map that lies in
+                               an output is copied first (on the call's stream)  */
 } fov_params;
 
 /*
@@ -156,7 +158,8 @@ fov_status foveate_plan_host(int32_t h, int32_t w, const fov_params* p, double* 
  *   stream  : hipStream_t (NULL = default stream).
  * Empty views (any extent 0) are a no-op.  Fails with FOV_ERANGE when a
  * fragment's radius needs more on-chip memory than one workgroup may use.
- * The library keeps a per-(device, stream) workspace for fragment plans (grown
+ * Calls of more than 16 frames, or with a sigma map in an output, use a
+ * per-(device, stream) workspace of the library (grown
  * with hipMalloc on first use or when a call needs more); calls on one stream
  * are ordered and may share it, calls on different streams use their own.
  */
@@ -189,7 +192,9 @@ fov_status foveate_forward_batch(const fov_tensor* ins, const fov_tensor* outs, 
  *   - the plans of the call's fragments, counted as written out (per fragment
  *     about 4 * (2r_max + 1) bytes of taps plus a few words), must stay within
  *     16 MiB, else FOV_EINVAL with the size; a 3840x2160 frame in 32 px
- *     fragments does at every radius the on-chip memory allows.
+ *     fragments does at every radius the on-chip memory allows;
+ *   - no sigma map may overlap the output (there is no memory for a copy of it),
+ *     else FOV_EALIAS.
  */
 fov_status foveate_forward_noalloc(const fov_tensor* in, const fov_tensor* out, const fov_params* p,
                                    int32_t np, void* stream);

@@ -542,19 +542,50 @@ fov_status launch_planned(const FrameDesc* frames, int nf, int in_dtype, int out
     return launch_forward(a, in_dtype, out_dtype, fp.lds, stream, fp.lds_limit, fp.cus, fp.persistent, e0, e1);
 }
 
+bool map_in_output(const FrameDesc* frames, int nf, int i, int out_dtype) {
+    const FrameDesc& f = frames[i];
+    const char* m0 = reinterpret_cast<const char*>(f.p.sigma_map);
+    const char* m1 = m0 + (size_t)f.p.nbx * f.nby * sizeof(float);
+    for (int j = 0; j < nf; ++j) {
+        const FrameDesc& o = frames[j];
+        const char* o0 = static_cast<const char*>(o.out);
+        const char* o1 = o0 + ((o.c - 1) * o.osc + (o.h - 1) * o.osh + (o.w - 1) * o.osw + 1) * (int64_t)dtype_size(out_dtype);
+        if (m0 < o1 && o0 < m1) return true;
+    }
+    return false;
+}
+
 // One forward launch over a list of frames (any shapes, one dtype pair).  Up to
 // kArgFrames descriptors travel in the kernel arguments; more are uploaded
 // as a device table from pinned memory to the per-(device, stream) workspace.
-fov_status run_forward(std::vector<FrameDesc>& frames, int in_dtype, int out_dtype, hipStream_t stream,
+// Sigma maps that lie in an output are read from copies there.
+fov_status run_forward(std::vector<FrameDesc>& given, int in_dtype, int out_dtype, hipStream_t stream,
                        const LaunchCfg* cfg_in, bool profile) {
-    if (frames.empty()) return FOV_OK;
+    if (given.empty()) return FOV_OK;
+    const int nf = (int)given.size();
+    std::vector<FrameDesc> moved;  // frames whose maps are copies
+    const bool in_out = maps_in_outputs(given.data(), nf, out_dtype);
+    if (in_out) moved = given;
+    std::vector<FrameDesc>& frames = in_out ? moved : given;
     fov_status s;
     ForwardPlan fp;
-    if ((s = plan_forward(frames.data(), (int)frames.size(), in_dtype, out_dtype, cfg_in, &fp)) != FOV_OK) return s;
+    if ((s = plan_forward(frames.data(), nf, in_dtype, out_dtype, cfg_in, &fp)) != FOV_OK) return s;
+    const auto map_bytes = [](const FrameDesc& f) { return (size_t)f.p.nbx * f.nby * sizeof(float); };
+    size_t mbytes = 0;
+    for (int i = 0; i < nf && in_out; ++i)
+        if (frames[i].p.sigma_map) mbytes += map_bytes(frames[i]);
     Workspace* ws = nullptr;
     std::unique_lock<std::mutex> hold;
-    if (fp.tbytes > 0 && (s = workspace(stream, fp.tbytes, fp.tbytes, &ws, &hold)) != FOV_OK) return s;
-    return launch_planned(frames.data(), (int)frames.size(), in_dtype, out_dtype, fp, ws, stream, profile);
+    if (fp.tbytes + mbytes > 0 && (s = workspace(stream, fp.tbytes + mbytes, fp.tbytes, &ws, &hold)) != FOV_OK) return s;
+    char* to = in_out ? static_cast<char*>(ws->dev) + fp.tbytes : nullptr;
+    for (int i = 0; i < nf && in_out; ++i) {
+        if (!frames[i].p.sigma_map) continue;
+        const hipError_t e = hipMemcpyAsync(to, frames[i].p.sigma_map, map_bytes(frames[i]), hipMemcpyDeviceToDevice, stream);
+        if (e != hipSuccess) return hip_error(e, "hipMemcpyAsync(sigma map)");
+        frames[i].p.sigma_map = reinterpret_cast<const float*>(to);
+        to += map_bytes(frames[i]);
+    }
+    return launch_planned(frames.data(), nf, in_dtype, out_dtype, fp, ws, stream, profile);
 }
 
 // Scratch of the adjoint's horizontal transposes, per launch: frames are

@@ -76,6 +76,14 @@ LaunchCfg select_cfg(int nframes, int in_dtype, int out_dtype, const CallShape& 
 // for) let 8-bit output run on the matrix cores.
 bool on_fp32(const FrameDesc* frames, int nf, int in_dtype, int out_dtype, int r_cap, const CallShape& cs, int cus);
 
+// Whether frame i's sigma map overlaps an output of the frames: its items read it while others write.
+bool map_in_output(const FrameDesc* frames, int nf, int i, int out_dtype);
+inline bool maps_in_outputs(const FrameDesc* frames, int nf, int out_dtype) {
+    for (int i = 0; i < nf; ++i)
+        if (frames[i].p.sigma_map && map_in_output(frames, nf, i, out_dtype)) return true;
+    return false;
+}
+
 // Validation of a forward (or backward) call's views and parameters.
 fov_status prepare(const fov_tensor* in, const fov_tensor* out, const fov_params* p, int32_t np, bool backward,
                    bool* empty);

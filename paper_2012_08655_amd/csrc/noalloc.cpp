@@ -26,6 +26,9 @@ extern "C" fov_status foveate_forward_noalloc(const fov_tensor* in, const fov_te
                                          " frames per call (their descriptors travel in the kernel arguments)");
     FrameDesc frames[kArgFrames];
     for (int i = 0; i < in->n; ++i) frames[i] = make_frame_desc(*in, *out, i, p[np == 1 ? 0 : i]);
+    if (maps_in_outputs(frames, in->n, out->dtype))
+        return set_error(FOV_EALIAS, "a sigma map overlaps the output; foveate_forward_noalloc has no memory for a copy of it "
+                                     "(use foveate_forward)");
     ForwardPlan fp;
     if ((s = plan_forward(frames, in->n, in->dtype, out->dtype, nullptr, &fp)) != FOV_OK) return s;
     if (fp.plan_bytes > kPlanLimit)

@@ -267,7 +267,7 @@ fov_status launch_batch(ServerImpl* s, Slot& sl, std::vector<FrameDesc>& frames,
         hipError_t e = hipStreamWaitEvent(sl.run, ev, 0);
         if (e != hipSuccess) return hip_error(e, "hipStreamWaitEvent(ready)");
     }
-    if (s->cfg.use_graph) {
+    if (s->cfg.use_graph && !maps_in_outputs(frames.data(), (int)frames.size(), s->cfg.out_dtype)) {
         const int nf = (int)frames.size();
         const CallShape cs = call_shape(frames.data(), nf);
         const bool fp32 = on_fp32(frames.data(), nf, s->cfg.in_dtype, s->cfg.out_dtype, s->r_cap, cs, s->cus);
