@@ -92,11 +92,12 @@ constexpr int kBufferWord3 = 0x00020000;
 // Byte offset past any descriptor's range: a buffer load there returns 0.
 constexpr uint32_t kOutside = 0x7fffffffu;
 
-// Frames whose bytes fit 31 bits are read with buffer loads (larger ones are loaded in commit()): each lane's column offsets are fixed for the
+// Rows are read with buffer loads: each lane's column offsets are fixed for the
 // fragment (past the range beyond the tile, so that no lane predicate stands around the loads) and a row's
 // offset is a wave-uniform scalar that steps inside the frame.  Per-row clamps, 64-bit products and lane
 // predicates were most of the scalar instructions of a work item: FP32 kernel, 4 x 3 x 512 x 512 48.5 -> 44.0 us,
-// 32 x 3 x 224 x 224 41.4 -> 37.7 us, 256 x 256 8.8 -> 8.3 us.
+// 32 x 3 x 224 x 224 41.4 -> 37.7 us, 256 x 256 8.8 -> 8.3 us.  The offsets are from the frame's first byte where its bytes
+// fit 31 bits, else (far) from each strip's first row; frames of which not even a strip does are loaded in commit().
 template <typename TIn, typename TS>
 struct Stager {
     static constexpr int KB = 2;  // prefetched 64-column chunks
@@ -107,13 +108,14 @@ struct Stager {
     const TIn* plane;
     int64_t ish, isw;
     int y0, rows, h, w, x_first, TW;
-    bool near;
+    bool near, far;
 
     __device__ __forceinline__ void setup(int x_first_, int TW_, int w_, int64_t isw_, int64_t ish_, int h_,
                                           const TIn* base_, int64_t span) {
         x_first = x_first_; TW = TW_; w = w_; isw = isw_; ish = ish_; h = h_;
         base = base_;
-        near = span * (int64_t)sizeof(TIn) < (int64_t)kOutside;
+        far = span * (int64_t)sizeof(TIn) >= (int64_t)kOutside;
+        near = !far || ((kStripMax - 1) * ish_ + (w_ - 1) * isw_ + 1) * (int64_t)sizeof(TIn) < (int64_t)kOutside;
         rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<TIn*>(base_), 0, (int)(span * sizeof(TIn)), kBufferWord3);
         const int lane = threadIdx.x & 63;
 #pragma unroll
@@ -128,7 +130,13 @@ struct Stager {
         const int wave = wave_id();
         if (!near) return;
         const bool inside = y0 >= 0 && y0 + rows <= h;
-        const uint32_t ib = (uint32_t)ish * (uint32_t)sizeof(TIn), poff = (uint32_t)((plane - base) * sizeof(TIn));
+        const uint32_t ib = (uint32_t)ish * (uint32_t)sizeof(TIn);
+        uint32_t poff = (uint32_t)((plane - base) * sizeof(TIn));
+        if (__builtin_expect(far, 0)) {
+            const int first = clampi(y0, 0, h - 1);
+            rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<TIn*>(plane + first * ish), 0, (int)kOutside, kBufferWord3);
+            poff = 0u - (uint32_t)first * ib;
+        }
         const uint32_t step = (uint32_t)(kThreads / 64) * ib;
         uint32_t so = poff + (uint32_t)(y0 + wave) * ib;
 #pragma unroll
