@@ -166,8 +166,8 @@ def forward(x: torch.Tensor, params, out: torch.Tensor | None = None, layout: st
 
 def forward_noalloc(x: torch.Tensor, params, out: torch.Tensor, layout: str = "NCHW", stream=None) -> torch.Tensor:
     """``forward`` through the library's allocation-free entry point: the
-    plan workspace is the library's fixed device array, so ``out`` must be
-    given (at most 16 frames per call; calls on one GPU must not overlap)."""
+    library allocates nothing and keeps nothing, so ``out`` must be given (at
+    most 16 frames per call, of limited size; see foveate_forward_noalloc)."""
     di, do = tensor_desc(x, layout), tensor_desc(out, layout)
     arr, npar, _keep = _params_array(params, di.n)
     N.check(N.lib().foveate_forward_noalloc(ctypes.byref(di), ctypes.byref(do), arr, npar, _stream_handle(stream)))

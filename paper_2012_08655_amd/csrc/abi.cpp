@@ -440,15 +440,6 @@ bool on_fp32(const FrameDesc* frames, int nf, int in_dtype, int out_dtype, int r
     return (r <= 24 && per_cu >= 2) || (sparse && per_cu >= 9 && (r <= 36 || (r <= 40 && per_cu >= 16)));
 }
 
-// Bytes that the plans of a call's fragments (radius, taps and queue slots of every fragment) take when
-// written out; foveate_forward_noalloc's size limit is stated in them.
-size_t plan_bytes(const FwdLaunch& a, int split_log2, bool by_channel, int tap_size) {
-    const auto up = [](size_t v, size_t m) { return (v + m - 1) / m * m; };
-    const size_t nfrag = a.nfrag, pad = 8 * (size_t)std::min(a.r_cap + 1, 1024);
-    const size_t slots = by_channel && nfrag < ((size_t)1 << 26) ? a.cmax * (nfrag + pad) : (nfrag << (2 * split_log2)) + pad;
-    return up(2 * up(nfrag * 4, 16) + up(slots * 8, 16) + 256 + nfrag * up(2 * (size_t)a.r_cap + 1, 16) * tap_size, 256);
-}
-
 // Launch shape of one forward call over a list of frames (any shapes, one
 // dtype pair): counts, radius bound, LDS and scratch sizes; no device work.
 fov_status plan_forward(FrameDesc* frames, int nf, int in_dtype, int out_dtype, const LaunchCfg* cfg_in,
@@ -516,8 +507,7 @@ fov_status plan_forward(FrameDesc* frames, int nf, int in_dtype, int out_dtype, 
     fp->lds = lds;
     fp->persistent = cfg.persistent;
     fp->tbytes = nf > kArgFrames ? frame_table_bytes(nf) : 0;
-    fp->plan_bytes = plan_bytes(a, cfg.split_log2, cfg.chan_split != 0 && cfg.split_log2 == 0 && cs.c > 1 && cs.c <= 16, in_dtype == FOV_F64 ? 8 : 4) +
-                     frame_table_bytes(nf);
+    fp->cfg = cfg;
     fp->lds_limit = dev->lds_limit;
     fp->cus = dev->cus;
     return FOV_OK;

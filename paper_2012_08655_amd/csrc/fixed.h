@@ -162,19 +162,14 @@ struct FxStager {
     __device__ __forceinline__ void put(unsigned char* tile, int i, int ch, int g, uint32_t t) const {
         *reinterpret_cast<uint32_t*>(tile + (lrow + 4 * kRows * i) * fx_pitch(NK) + col + ch * fx_plane(NK) + 4 * g) = t;
     }
-    // Three words of four interleaved pixels to their channels' words.
+    // Three words of four interleaved pixels to their channels' words (frames of three channels, all staged together).
     __device__ __forceinline__ void put_rgb(unsigned char* tile, int i, int g, uint32_t a, uint32_t b, uint32_t c) const {
         const uint32_t r = perm(c, perm(b, a, 0x0c060300u), 0x05020100u);
         const uint32_t gr = perm(c, perm(b, a, 0x0c070401u), 0x06020100u);
         const uint32_t bl = perm(c, perm(b, a, 0x0c0c0502u), 0x07040100u);
-        if (nc == 3) {
-            put(tile, i, 0, g, r);
-            put(tile, i, 1, g, gr);
-            put(tile, i, 2, g, bl);
-        } else {  // some of the channels, c0 first
-            put(tile, i, 0, g, c0 == 0 ? r : (c0 == 1 ? gr : bl));
-            if (nc > 1) put(tile, i, 1, g, c0 == 0 ? gr : bl);
-        }
+        put(tile, i, 0, g, r);
+        put(tile, i, 1, g, gr);
+        put(tile, i, 2, g, bl);
     }
 
     // A tile of TH rows from column x0, row y0 of the frame: issues the loads (store() writes them to LDS).

@@ -109,7 +109,7 @@ struct ForwardPlan {
     const int32_t* prefix() const { return a.nframes > kArgFrames ? prefix_table.data() : a.kprefix; }
     size_t lds = 0;               // dynamic LDS per workgroup
     size_t tbytes = 0;            // frame table bytes to upload (0: the frames travel in a.fr)
-    size_t plan_bytes = 0;        // size of the fragments' plans written out (noalloc's limit)
+    LaunchCfg cfg;                // the configuration it was planned with
     size_t lds_limit = 0;
     int cus = 0;
     bool persistent = false;

@@ -4,6 +4,7 @@
 // bitwise the same.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <string>
 
 #include "host.h"
@@ -11,9 +12,20 @@
 using namespace fov;
 
 namespace {
-// Largest call taken, by the size of its fragment plans (ForwardPlan::plan_bytes).  A 3840x2160 frame in
-// 32 px fragments at radius 150 (the widest window a workgroup can stage) needs about 10 MiB.
+// Largest call taken, by the size that its fragments' plans (radius, taps and queue slots of every fragment) and its
+// frame table would have written out, as an earlier form of the launch did: programs rely on the refusal as on the
+// rest.  A 3840x2160 frame in 32 px fragments at radius 150 (the widest window a workgroup can stage) comes to about 10 MiB.
 constexpr size_t kPlanLimit = (size_t)16 << 20;
+
+size_t plan_bytes(const ForwardPlan& fp, int in_dtype) {
+    const auto up = [](size_t v, size_t m) { return (v + m - 1) / m * m; };
+    const FwdLaunch& a = fp.a;
+    const size_t nfrag = a.nfrag, pad = 8 * (size_t)std::min(a.r_cap + 1, 1024);
+    const bool by_channel = fp.cfg.chan_split != 0 && fp.cfg.split_log2 == 0 && a.cmax > 1 && a.cmax <= 16 && nfrag < ((size_t)1 << 26);
+    const size_t slots = by_channel ? a.cmax * (nfrag + pad) : (nfrag << (2 * fp.cfg.split_log2)) + pad;
+    const size_t taps = nfrag * up(2 * (size_t)a.r_cap + 1, 16) * (in_dtype == FOV_F64 ? 8 : 4);
+    return up(2 * up(nfrag * 4, 16) + up(slots * 8, 16) + 256 + taps, 256) + up(148 * (size_t)a.nframes + 4, 256);
+}
 }  // namespace
 
 extern "C" fov_status foveate_forward_noalloc(const fov_tensor* in, const fov_tensor* out, const fov_params* p,
@@ -31,9 +43,10 @@ extern "C" fov_status foveate_forward_noalloc(const fov_tensor* in, const fov_te
                                      "(use foveate_forward)");
     ForwardPlan fp;
     if ((s = plan_forward(frames, in->n, in->dtype, out->dtype, nullptr, &fp)) != FOV_OK) return s;
-    if (fp.plan_bytes > kPlanLimit)
-        return set_error(FOV_EINVAL, "this call needs " + std::to_string(fp.plan_bytes) +
-                                         " bytes of plan workspace; foveate_forward_noalloc takes calls of up to " +
-                                         std::to_string(kPlanLimit) + " (use foveate_forward)");
+    const size_t size = plan_bytes(fp, in->dtype);
+    if (size > kPlanLimit)
+        return set_error(FOV_EINVAL, "the call is too large: by its size in bytes of plan workspace, " + std::to_string(size) +
+                                         ", foveate_forward_noalloc takes up to " + std::to_string(kPlanLimit) +
+                                         " (use foveate_forward)");
     return launch_planned(frames, in->n, in->dtype, out->dtype, fp, nullptr, (hipStream_t)stream, false);
 }
