@@ -672,8 +672,9 @@ FrameDesc make_frame_desc(const fov_tensor& in, const fov_tensor& out, int n, co
     d.c = in.c; d.h = in.h; d.w = in.w;
     d.p = to_frame(p, in.h, in.w);
     d.nby = grid_extent(in.h, p.origin_y, p.block);
-    d.ahead = lines_ahead(d);
-    d.low_lines = d.low_at = d.low_span = 0;
+    d.ahead_x = lines_ahead(p.fix_x, p.origin_x, p.block, d.p.nbx);
+    d.ahead_y = lines_ahead(p.fix_y, p.origin_y, p.block, d.nby);
+    d.low_x = d.low_y = d.low_w = d.low_h = 0;
     return d;
 }
 

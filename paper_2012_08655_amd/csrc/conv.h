@@ -536,10 +536,8 @@ __device__ __forceinline__ Frag frag_of(const FwdLaunch& a, const FrameDesc* __r
 }
 
 // The k-th fragment of the launch, numbered so that the costliest tend to come first (a launch does not end
-// on a long tail) without any pass over the plan: a frame's fragments go along its longer axis, the lines
-// farthest from the fixation first (sigma grows with the distance), and in turn within a line; frames of
-// equal counts take turns.  ranked_frame() gives its frame f and its rank there, ranked_at() the
-// fragment (order.h).
+// on a long tail) without any pass over the plan; frames of equal counts take turns.  ranked_frame() gives its frame f
+// and its rank there, ranked_at() the fragment (order.h).
 template <bool ARGS>
 __device__ __forceinline__ void ranked_frame(const FwdLaunch& a, const int32_t* __restrict__ prefix, int nframes, int k,
                                              int* f, int* rank) {
@@ -565,7 +563,7 @@ __device__ __forceinline__ Frag placed_at(const D& d, int f, const Place& p) {
 }
 
 __device__ __forceinline__ Frag ranked_at(const FrameDesc& d, int f, int rank) {
-    return placed_at(d, f, ranked_place(grid_of(d), rank));
+    return placed_at(d, f, item_place(grid_of(d), rank, false));
 }
 
 // What a work item is decided by, read from its frame in one go: the empty asm keeps the loads together.
@@ -575,16 +573,16 @@ __device__ __forceinline__ Frag ranked_at(const FrameDesc& d, int f, int rank) {
 struct FrameGeo {
     int32_t c, h, w, nby;
     FrameParams p;
-    int32_t ahead;
+    int32_t ahead_x, ahead_y;
 };
 
 template <bool ARGS>
 __device__ __forceinline__ FrameGeo geo_of(const FwdLaunch& a, const FrameDesc* __restrict__ table, int f) {
     const FrameDesc& d = frame_of<ARGS>(a, table, f);
-    FrameGeo g{d.c, d.h, d.w, d.nby, d.p, d.ahead};
+    FrameGeo g{d.c, d.h, d.w, d.nby, d.p, d.ahead_x, d.ahead_y};
     asm volatile("" : "+s"(g.c), "+s"(g.h), "+s"(g.w), "+s"(g.nby), "+s"(g.p.fix_x), "+s"(g.p.fix_y), "+s"(g.p.e0),
                  "+s"(g.p.slope), "+s"(g.p.cap), "+s"(g.p.block), "+s"(g.p.origin_x), "+s"(g.p.origin_y), "+s"(g.p.nbx),
-                 "+s"(g.p.sigma_map), "+s"(g.ahead));
+                 "+s"(g.p.sigma_map), "+s"(g.ahead_x), "+s"(g.ahead_y));
     return g;
 }
 

@@ -12,13 +12,12 @@ struct FrameDesc {
     int64_t isc, ish, isw, osc, osh, osw;  // element strides
     int32_t c, h, w, nby;
     FrameParams p;  // p.nbx filled in
-    // The order of its fragments (order.h).  They go along the longer axis, in lines across it:
-    // the first `ahead` lines (the last -ahead) first, which are farther from the fixation than all others, then from both
-    // ends in turn.
-    int32_t ahead;
-    // With merge: the pairs that may not be merged lie in the last low_lines lines, at low_at .. low_at + low_span - 1
-    // of each.
-    int32_t low_lines, low_at, low_span;
+    // The order of its fragments (order.h): on each axis, how many lines lie farther from the fixation than all
+    // lines on its other side (of the frame, or with merge of the rectangle low_*).
+    int32_t ahead_x, ahead_y;
+    // With merge: the pairs that may not be merged, columns low_x .. low_x + low_w - 1 and rows low_y .. low_y + low_h - 1
+    // (whole pairs).
+    int32_t low_x, low_y, low_w, low_h;
 };
 
 // Frames whose descriptors travel inside the kernel arguments; larger

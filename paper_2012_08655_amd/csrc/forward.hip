@@ -499,36 +499,23 @@ __device__ __forceinline__ bool decode(const FwdLaunch& a, const FrameDesc* __re
     ranked_frame<ARGS>(a, prefix, n.nframes, k, &f, &rank);
     const auto describe = [&](const auto& d) {
         const FrameParams& fp = d.p;
-        Frag F;
-        bool nothing = false;
-        if constexpr (FIXED) {
-            F = placed_at(d, f, ranked_place(Grid{fp.nbx, d.nby, d.ahead, 0, 0, 0}, rank));
-        } else {
-            const Grid g = grid_of(d);
-            Place at;
-            if (__builtin_expect(n.merge, 0)) {
-                at = paired_place(g, rank);
-                // Below a last row that has no pair.  (Said at the end: a return here, ahead of the loads below,
-                // costs every item 0.3 us.)
-                nothing = at.by >= g.nby;
-                at.by = min(at.by, g.nby - 1);
-            } else {
-                at = ranked_place(g, rank);
-            }
-            F = placed_at(d, f, at);
-        }
+        Place at;
+        if constexpr (FIXED) at = item_place(Grid{fp.nbx, d.nby, d.ahead_x, d.ahead_y, 0, 0, 0, 0}, rank, false);
+        else at = item_place(grid_of(d), rank, n.merge);
+        Frag F = placed_at(d, f, at);
         const int bx = F.bx, by = F.by;
         const double sigma = uniform(fragment_sigma(fp, F.lb, bx, by));
         int r = __builtin_amdgcn_readfirstlane(radius_of(sigma));
         if (r > a.r_cap) r = a.r_cap;  // the host sized everything for r_cap; plans agree bit for bit
-        // Vertical pairs at the cap (rows 2k and 2k+1, both sigma == cap, hence equal taps): the upper
-        // fragment's item covers both.
+        // Vertical pairs at the cap (rows 2k and 2k+1, both sigma == cap, hence equal taps): one fragment's item covers
+        // both (see item_place()).
         if (!FIXED && n.merge && r > 0 && sigma == fp.cap) {
             const int by2 = by ^ 1;
             if (by2 < d.nby && fragment_sigma(fp, F.lb + (by2 - by) * fp.nbx, bx, by2) == fp.cap) {
-                if (by & 1) return false;
-                const Frag F2 = fragment_at(d, f, bx, by2);
-                F.bh = F2.ya + F2.bh - F.ya;
+                if (at.box && ((__popc((by >> 1) ^ bx) ^ by) & 1)) return false;
+                const Frag U = fragment_at(d, f, bx, by & ~1), V = fragment_at(d, f, bx, by | 1);
+                F.ya = U.ya;
+                F.bh = V.ya + V.bh - U.ya;
             }
         }
         if (!narrow_to_tile(F, d, L, sub)) return false;
@@ -537,7 +524,7 @@ __device__ __forceinline__ bool decode(const FwdLaunch& a, const FrameDesc* __re
         it->c_lo = max(ch, 0);
         it->c_hi = ch < 0 ? d.c : min(ch + 1, d.c);
         it->F = F;
-        return it->c_lo < it->c_hi && !nothing;
+        return it->c_lo < it->c_hi;
     };
     if constexpr (FIXED) return describe(geo_of<ARGS>(a, table, f));
     else return describe(frame_of<ARGS>(a, table, f));

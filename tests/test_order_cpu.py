@@ -56,7 +56,8 @@ int main() {
                 if (pick(2)) d.p.cap = s < 1e100 ? s : 1.0;
             }
             d.p.sigma_map = pick(10) ? nullptr : &map_tag;
-            d.ahead = lines_ahead(d);
+            d.ahead_x = lines_ahead(d.p.fix_x, d.p.origin_x, d.p.block, d.p.nbx);
+            d.ahead_y = lines_ahead(d.p.fix_y, d.p.origin_y, d.p.block, d.nby);
         }
         // sigmas: a map's are drawn, often the cap
         std::vector<std::vector<double>> sigma(nf);
@@ -75,20 +76,19 @@ int main() {
                 std::vector<int> done((size_t)d.p.nbx * d.nby);
                 int empty = 0;
                 for (int k = 0; k < prefix[f + 1] - prefix[f]; ++k) {
-                    const Place p = merge ? paired_place(grid_of(d), k) : ranked_place(grid_of(d), k);
-                    if (p.bx < 0 || p.bx >= d.p.nbx || p.by < 0 || p.by > d.nby) return fail(d, "out of the grid", merge);
-                    if (p.by == d.nby) {
-                        ++empty;
-                        continue;
-                    }
+                    const Place p = item_place(grid_of(d), k, merge);
+                    if (p.bx < 0 || p.bx >= d.p.nbx || p.by < 0 || p.by >= d.nby) return fail(d, "out of the grid", merge);
                     const auto at = [&](int by) { return sigma[f][(size_t)by * d.p.nbx + p.bx]; };
-                    int rows = 1;
+                    int rows = 1, first = p.by;  // as decode() in forward.hip does
                     if (merge && at(p.by) == d.p.cap && radius_of(d.p.cap) > 0) {
                         const int by2 = p.by ^ 1;
-                        if (by2 < d.nby && at(by2) == d.p.cap) rows = p.by & 1 ? 0 : 2;
+                        if (by2 < d.nby && at(by2) == d.p.cap) {
+                            rows = p.box && ((__builtin_popcount((p.by >> 1) ^ p.bx) ^ p.by) & 1) ? 0 : 2;
+                            first = p.by & ~1;
+                        }
                     }
                     empty += rows == 0;
-                    for (int r = 0; r < rows; ++r) ++done[(size_t)(p.by + r) * d.p.nbx + p.bx];
+                    for (int r = 0; r < rows; ++r) ++done[(size_t)(first + r) * d.p.nbx + p.bx];
                 }
                 for (int v : done)
                     if (v != 1) return fail(d, v ? "filtered twice" : "left out", merge);
