@@ -500,7 +500,14 @@ __device__ __forceinline__ bool decode(const FwdLaunch& a, const FrameDesc* __re
     const auto describe = [&](const auto& d) {
         const FrameParams& fp = d.p;
         Place at;
-        if constexpr (FIXED) at = item_place(Grid{fp.nbx, d.nby, d.ahead_x, d.ahead_y, 0, 0, 0, 0}, rank, false);
+        if constexpr (FIXED) {
+            // Tiles of small radii cost much the same and are bound by memory: their order there.  (A run of eight
+            // along a row of fragments stays on one XCD, and its tiles share lines.)  Per call, this order / the costliest first, 3 x
+            // 1080 x 1920 planar, radii up to 3 22.0 / 27.2 us, 15 24.2 / 28.9, up to 48 over the whole frame 37.8 / 37.1, from the middle on 44.1 / 43.0;
+            // interleaved 22.3 / 24.1, 24.3 / 25.6, 38.0 / 34.3, 43.5 / 39.6.
+            if (a.r_cap <= 16) at = row_place(fp.nbx, rank);
+            else at = item_place(Grid{fp.nbx, d.nby, d.ahead_x, d.ahead_y, 0, 0, 0, 0}, rank, false);
+        }
         else at = item_place(grid_of(d), rank, n.merge);
         Frag F = placed_at(d, f, at);
         const int bx = F.bx, by = F.by;
@@ -555,8 +562,8 @@ __global__ __launch_bounds__(kThreads) void fov_fwd_kernel(const FwdLaunch a, co
 //
 // The FP32 passes for a tile that the matrix cores leave.  A function of its own: it is rare, and inlined
 // it would take registers from the common path.  Its arguments arrive in vector registers; they are made scalar again, as
-// the passes need them: 1080 x 1920 x 3, radii up to 48, of a one-pixel checkerboard, all of whose tiles come here, 180 us with
-// them as they arrive, 147 so (86 on the FP32 kernel alone; 33 for stripes, none of whose do).
+// the passes need them: 1080 x 1920 x 3, radii up to 48, of a one-pixel checkerboard, all of whose tiles come here, 177 us a
+// call with them as they arrive, 136 so (86 on the FP32 kernel alone; 32 for stripes, none of whose do).
 __device__ __attribute__((noinline)) void fp32_tile(FrameDesc fd, double sigma, int r_cap, int strip_rows, int r,
                                                     int xa, int ya, int bw, int bh, int c_lo, int c_hi) {
     extern __shared__ __align__(16) unsigned char smem[];

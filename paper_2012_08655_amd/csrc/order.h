@@ -100,6 +100,12 @@ __host__ __device__ inline Place item_place(const Grid& g, int rank, bool pairs)
     return Place{x0 + (cols ? c.u : c.v), y0 + (cols ? c.v : c.u), pairs};
 }
 
+// The rank-th fragment in the order of memory.
+__host__ __device__ inline Place row_place(int nbx, int rank) {
+    const int by = rank / nbx;
+    return Place{rank - by * nbx, by, false};
+}
+
 // Ahead of the others on an axis of n fragments from `origin` on: how many more lie on one side of the fixation than on
 // the other.
 inline int lines_ahead(double fix, double origin, int block, int n) {
