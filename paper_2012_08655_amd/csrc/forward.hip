@@ -504,8 +504,9 @@ __device__ __forceinline__ bool decode(const FwdLaunch& a, const FrameDesc* __re
             // Tiles of small radii cost much the same and are bound by memory: their order there.  (A run of eight
             // along a row of fragments stays on one XCD, and its tiles share lines.)  Per call, this order / the costliest first, 3 x
             // 1080 x 1920 planar, radii up to 3 22.0 / 27.2 us, 15 24.2 / 28.9, up to 48 over the whole frame 37.8 / 37.1, from the middle on 44.1 / 43.0;
-            // interleaved 22.3 / 24.1, 24.3 / 25.6, 38.0 / 34.3, 43.5 / 39.6.
-            if (a.r_cap <= 16) at = row_place(fp.nbx, rank);
+            // interleaved 22.3 / 24.1, 24.3 / 25.6, 38.0 / 34.3, 43.5 / 39.6.  Frames that an XCD's cache of 4 MB holds gain less,
+            // 480 x 640 x 3, up to 3 8.5 / 9.9, 15 9.1 / 10.0, and where a radius counts may lose, 16 with 20 px 12.1 / 10.9.
+            if (a.r_cap <= 8 || (a.r_cap <= 16 && (int64_t)d.h * d.w * d.c >= 4 << 20)) at = row_place(fp.nbx, rank);
             else at = item_place(Grid{fp.nbx, d.nby, d.ahead_x, d.ahead_y, 0, 0, 0, 0}, rank, false);
         }
         else at = item_place(grid_of(d), rank, n.merge);
