@@ -315,7 +315,7 @@ typedef struct {
     int32_t max_inflight_batches; /* batches on the device at once, 1..8 (one stream each)      */
     int32_t max_requests;         /* request table size: queued + in flight + done, not polled  */
     int32_t in_dtype, out_dtype;  /* the one dtype pair this server serves (as forward)         */
-    int32_t max_fragments;        /* fragments per batch (sizes the plan workspace)             */
+    int32_t max_fragments;        /* fragments per batch                                        */
     int32_t max_block;            /* largest fragment side a request may use (1..64)            */
     double max_sigma;             /* largest sigma a request may produce (sizes LDS and taps)   */
     int32_t use_graph;            /* 1: every batch replays a hipGraph captured at creation     */
@@ -338,9 +338,9 @@ double foveate_now(void);
 
 /*
  * Create a server on the current device: streams, the scheduler thread and,
- * with use_graph, one captured batch graph per stream with its own workspace
- * (allocated here, sized by max_batch_frames, max_fragments, max_block and
- * max_sigma).  FOV_EINVAL for bad configuration, FOV_ENOMEM, FOV_EHIP.
+ * with use_graph, a captured batch graph per stream and forward kernel and a frame
+ * table per stream (allocated here, sized by max_batch_frames; the graphs are laid out for
+ * max_fragments, max_block and max_sigma).  FOV_EINVAL for bad configuration, FOV_ENOMEM, FOV_EHIP.
  */
 fov_status foveate_server_create(const fov_server_cfg* cfg, fov_server** out);
 

@@ -404,15 +404,15 @@ CallShape call_shape(const FrameDesc* frames, int nf) {
 // radii up to 16 / 32 / 48: 8 / 12 / 15 ns a tile with three channels in flight over the chip, 7 / 9 / 11 with one), so it loses where a
 // tile holds little: fragments of at most 16 px, sides that leave most of their second tile empty, few channels.
 // Calls of 2160 x 3840 x c, 8-bit kernel / FP32 kernel, us:
-//   c = 3, 16 px, radii up to 16 275 / 212, 24 365 / 326, 32 395 / 405; 24 px, 3 128 / 94, 16 138 / 169; 32 px, 3 73 / 73, 16 79 / 110; 40 px, 24
-//   248 / 175, 32 269 / 310; 48 px, 24 178 / 164, 32 196 / 221; 64 px, 3 75 / 67, 16 80 / 102;
-//   c = 2, 16 px, 32 340 / 292, 40 398 / 336, 48 417 / 403; 40 px, 40 273 / 255; 48 px, 32 170 / 150, 40 200 / 214;
-//   c = 4, 16 px, 24 562 / 422, 32 619 / 529, 40 727 / 623, 48 771 / 754;
-//   c = 1, 16 px, 24 274 / 139, 48 350 / 218; 24 px, 48 179 / 163; 32 px, 24 79 / 58, 48 110 / 108; 40 px, 48 246 / 210; 48 px, 40 169 / 110; 64 px,
-//   32 88 / 63, 40 104 / 108.
-// With few fragments the chip is not full and the 8-bit kernel's shorter items win: c = 3, 12 px, 16, 480 x 640 (2160 fragments) 23 / 30, 720 x
-// 1280 (6420) 58 / 50; 40 px, 24, 480 x 640 (192) 14 / 17, 720 x 1280 (576) 34 / 34; c = 1, 48 px, 32, 480 x 640 (140) 10 / 15, 720 x 1280 (405) 22 / 20.
-// Bytewise staging, four interleaved channels: 32 px, 16 270 / 142, 48 1000 / 370; a sixth of the fragments decides.
+//   c = 3, 16 px, radii up to 16 271 / 211, 24 340 / 318, 32 364 / 395; 24 px, 3 128 / 96, 16 136 / 168; 32 px, 3 78 / 74, 16 83 / 109; 40 px, 24
+//   229 / 171, 32 250 / 296; 48 px, 24 163 / 155, 32 181 / 216; 64 px, 3 74 / 67, 16 79 / 101;
+//   c = 2, 16 px, 32 337 / 281, 40 394 / 327, 48 414 / 395; 40 px, 40 270 / 243; 48 px, 32 167 / 149, 40 197 / 206;
+//   c = 4, 16 px, 24 557 / 413, 32 606 / 519, 40 717 / 606, 48 750 / 742;
+//   c = 1, 16 px, 24 271 / 137, 48 347 / 217; 24 px, 48 175 / 159; 32 px, 24 78 / 56, 48 106 / 99; 40 px, 48 242 / 200; 48 px, 40 169 / 107; 64 px,
+//   32 87 / 62, 40 101 / 108.
+// With few fragments the chip is not full and the 8-bit kernel's shorter items win: c = 3, 12 px, 16, 480 x 640 (2160 fragments) 22 / 29, 720 x
+// 1280 (6420) 57 / 49; 40 px, 24, 480 x 640 (192) 13 / 15, 720 x 1280 (576) 30 / 29; c = 1, 48 px, 32, 480 x 640 (140) 10 / 16, 720 x 1280 (405) 21 / 20.
+// Bytewise staging, four interleaved channels: 32 px, 16 279 / 145, 48 982 / 361; a sixth of the fragments decides.
 bool on_fp32(const FrameDesc* frames, int nf, int in_dtype, int out_dtype, int r_cap, const CallShape& cs, int cus) {
     if (!forward_fixed(in_dtype, out_dtype, r_cap)) return false;
     int cmin = cs.c;
@@ -463,12 +463,15 @@ fov_status plan_forward(FrameDesc* frames, int nf, int in_dtype, int out_dtype, 
     const int tile = (cs.bmax + (1 << L) - 1) >> L;
     const int sr = cfg.strip_rows;
     size_t lds = forward_lds_bytes(in_dtype, out_dtype, r_cap, tile, tile, sr, fp32);
-    // One work item per channel where the fragments alone would not fill the chip several times over; above
-    // that an item's sigma, taps and geometry are worked out once for its channels, and a channel is loaded while
-    // the last one is computed.  A configuration may say otherwise.  Kernel time, items of one channel against
-    // items of three: 1024 fragments (4 x 3 x 512 x 512 f32) 45 / 54 us, 1568 (32 x 3 x 224 x 224 f32) 34 / 32, 2048 (8 x 3 x
-    // 512 x 512) 73 / 77, 2400 (16 x 3 x 317 x 451 u8 to f32) 54 / 54, 2888 (2 x 3 x 600 x 600, 16 px) f32 54 / 42 and f64
-    // 157 / 144, 4640 (8 x 3 x 317 x 451 u8 to f32, 16 px) 73 / 64.
+    // One work item per channel where the fragments alone would not fill the chip several times over; above that
+    // an item's sigma, taps and geometry are worked out once for its channels, and a channel is loaded while
+    // the last one is computed.  A configuration may say otherwise.  Call time, items of one channel against items of
+    // all.  Above the line: 2888 fragments (2 x 3 x 600 x 600, 16 px) f32 57 / 46 us and f64 104 / 85, 3072 (12 x 3 x 512 x 512 f32)
+    // 89 / 75, 4640 (8 x 3 x 317 x 451 u8 to f32, 16 px) 76 / 55.  Below it the two alternate: where most fragments are at the cap,
+    // so equally costly, larger items leave a longer last round, 510 (1080 x 1920 f64, 64 px) 72 / 95, 1024 (4 x 3 x 512 x 512 f32, a
+    // fixation each) 38 / 44, 800 (32 x 3 x 224 x 224 u8 to f32, 48 px) 30 / 32, 2040 (1080 x 1920 u8 to f32) radii up to 3 28 / 31, 60 125 / 141;
+    // where the ramp takes the whole frame the small ones at its inner end are set-up alone, 1008 fragments of 32 px, radii up to
+    // 12 22 / 17, 36 41 / 48, 2040 33 / 29; 32 x 3 x 224 x 224 f32, 32 px (1568), all frames alike 36 / 33.
     const bool chan = !fixed && L == 0 && cs.c > 1 && cs.c <= 16 && cs.nfrag * cs.c <= ((int64_t)1 << 30) &&
                       (cfg.chan_split > 0 || (cfg.chan_split < 0 && cs.nfrag < (int64_t)9 * dev->cus));
     // vertical pairs at the cap need tiles twice as tall; by default only when the CU holds as

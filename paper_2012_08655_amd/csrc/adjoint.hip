@@ -872,7 +872,9 @@ size_t adjoint_scratch_elems(const AdjShape& s, int nfrag) { return (size_t)nfra
 // A tile is 32 x 32 whatever the fragments: sides that leave much of it empty do better with the windows.  Per
 // call, gather / windows, 4 x 3 x 512 x 512 with radii up to 36 and then 3, 3 x 1080 x 1920 with radii up to 3: 16 px
 // 128 / 347, 66 / 111 and 128 / 205 us; 17 px 303 / 282, 129 / 109 and 241 / 191; 24 px 106 / 155 but 59 / 64 and 107 / 104;
-// 26 px 90 / 114, 51 / 58 and 95 / 95; 28 px 78 / 104, 47 / 56 and 84 / 86; 32 px 57 / 85, 37 / 44 and 67 / 71.
+// 26 px 90 / 114, 51 / 58 and 95 / 95; 28 px 78 / 104, 47 / 56 and 84 / 86; 32 px 57 / 85, 37 / 44 and 67 / 71.  (Measured
+// later, other fixation, 14 px 102 / 352, 70 / 145, 138 / 275 and 15 px 99 / 304, 69 / 132, 149 / 238, beside 16 px 82 / 280, 61 / 111,
+// 106 / 205: two such sides fill a tile as 28 and 30 px do, but the rule does not take them.)
 bool adjoint_gathers(int es, int block) {
     return es == 4 && (block == kGatherTile / 2 || (block >= 28 && block <= kGatherTile));
 }

@@ -52,9 +52,10 @@
 // straight into the vertical operand, lane by lane, with byte permutes only, and
 // the samples are read from LDS in the same order.
 //
-// Measured, kernel time with the FP32 kernel (and the two kernels it needed before it) in brackets: 1080 x 1920
-// x 3, radii up to 48, 41.5 us (67 + 12), 1080 x 1920 gray 27 us; whole calls: 2160 x 3840 x 3 169 us (271), 64 mixed
-// frames 3272 us (5740).  A tile takes 31 thousand cycles: 4 to find the item, 3 to issue its loads, 8
+// Measured per call (gratings with noise, 32 px fragments, radii up to 48, calls back to back from Python), in brackets as
+// the FP32 kernel and the two kernels that it needed then took: 1080 x 1920 x 3 39.6 - 40.0 us (75.6), 480 x 640 gray 8.9 (17.7; now on the
+// FP32 kernel by rule where radii are small or frames large), 2160 x 3840 x 3 158 - 163 (275), 64 mixed frames 3110 (5800).  The kernel alone, 1080 x
+// 1920 x 3, other frames: 43 us in a trace.  A tile takes 31 thousand cycles (stamps of a 42 us launch): 4 to find the item, 3 to issue its loads, 8
 // until the samples are in LDS, 1 for the tap digits, 7 for the products and 6 for the undecided
 // pixels; vector units 50 % busy, matrix cores 11 %, waves wait 49 % of their time.  53 KB of LDS and 168 registers
 // allow three workgroups a CU.
