@@ -184,17 +184,19 @@ fov_status foveate_forward_batch(const fov_tensor* ins, const fov_tensor* outs, 
 /*
  * foveate_forward for callers that cannot allocate device memory (code under
  * HIP graph capture, tight serving loops, harnesses that forbid hipMalloc).
- * Same arguments, kernel and bitwise the same outputs as foveate_forward; the
- * launch uses no device memory of the library's own, and the call makes no
+ * Same arguments, kernel and bitwise the same outputs as foveate_forward; but for
+ * the maps below the launch uses no device memory of the library's own, and the call makes no
  * hipMalloc, hipFree, pinned or other allocation.  Limits:
  *   - at most 16 frames per call (n <= 16; their descriptors travel in the
  *     kernel arguments), else FOV_EINVAL;
  *   - the plans of the call's fragments, counted as written out (per fragment
  *     about 4 * (2r_max + 1) bytes of taps plus a few words), must stay within
  *     16 MiB, else FOV_EINVAL with the size; a 3840x2160 frame in 32 px
- *     fragments does at every radius the on-chip memory allows;
- *   - no sigma map may overlap the output (there is no memory for a copy of it),
- *     else FOV_EALIAS.
+ *     fragments does at every radius the on-chip memory allows.
+ * Sigma maps of a call of which one overlaps the output are copied to a fixed
+ * 1 MiB array of device memory that the code object holds on every GPU; such
+ * calls of one GPU wait for each other there.  Captured ones cannot: replays of them
+ * must not overlap one another or such a call.
  */
 fov_status foveate_forward_noalloc(const fov_tensor* in, const fov_tensor* out, const fov_params* p,
                                    int32_t np, void* stream);

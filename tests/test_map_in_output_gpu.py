@@ -1,11 +1,10 @@
 """Sigma maps that lie in an output buffer on the GPU: read as they were before the call, plain, in batches, through
-the server; refused where the call has no memory for a copy."""
+the server, by the call that allocates nothing, also captured."""
 import pytest
 import torch
 
 import synth
 from paper_2012_08655_amd import api
-from paper_2012_08655_amd._native import FoveateError
 
 pytestmark = pytest.mark.gpu
 
@@ -58,9 +57,33 @@ def test_served(fov, dev, use_graph):
             assert torch.equal(out, want)
 
 
-def test_noalloc(fov, dev):
-    x, m, out, inside, p = make(dev, 6, torch.float32)
-    with pytest.raises(FoveateError, match="overlaps"):
-        api.forward_noalloc(x, dict(p, sigma_map=inside), out, layout="CHW")
+@pytest.mark.parametrize("dtype", [torch.uint8, torch.float32])
+def test_noalloc(fov, dev, dtype):
+    cases = [make(dev, 60 + i, dtype) for i in range(6)]
+    want = [fov.forward(x, dict(p, sigma_map=m.view(-1)), layout="CHW") for x, m, _, _, p in cases]
+    for streams in (1, 3):  # in order on one stream; on several, where calls wait for each other
+        for _, m, out, inside, _ in cases:
+            inside.copy_(m.view(-1))
+        torch.cuda.synchronize()
+        s = [torch.cuda.Stream() for _ in range(streams)]
+        for i, (x, m, out, inside, p) in enumerate(cases):
+            api.forward_noalloc(x, dict(p, sigma_map=inside), out, layout="CHW", stream=s[i % streams])
+        torch.cuda.synchronize()
+        for (_, _, out, _, _), y in zip(cases, want):
+            assert torch.equal(out, y), streams
+
+
+def test_noalloc_captured(fov, dev):
+    x, m, out, inside, p = make(dev, 70, torch.float32)
     want = fov.forward(x, dict(p, sigma_map=m.view(-1)), layout="CHW")
-    assert torch.equal(api.forward_noalloc(x, dict(p, sigma_map=m.view(-1)), out, layout="CHW"), want)
+    api.forward_noalloc(x, dict(p, sigma_map=m.view(-1)), out, layout="CHW")
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        inside.copy_(m.view(-1))
+        api.forward_noalloc(x, dict(p, sigma_map=inside), out, layout="CHW")
+    for k in range(4):
+        out.fill_(float(k))
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, want), k
