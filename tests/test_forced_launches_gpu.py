@@ -43,3 +43,13 @@ def test_item_counts(fov, dev, orc, n):
         assert torch.equal(fov.forward(x, p, layout="HWC", out_dtype=torch.float32), f)
     finally:
         fov.tuning_force(None)
+
+
+@pytest.mark.parametrize("radius", [3, 8, 9, 16, 17])
+@pytest.mark.parametrize("w", [1365, 1366])  # 3 x 1024 x w bytes: below and above 4 MiB, from which rows are taken up to radius 16
+def test_order_of_small_radii(fov, dev, radius, w):
+    g = torch.Generator(device=dev).manual_seed(radius)
+    x = torch.randint(0, 256, (3, 1024, w), dtype=torch.uint8, device=dev, generator=g)
+    p = synth.params_dict(0.3 * w, 700.0, 32.0, 0.02, (radius - 0.5) / 3.0, 32)
+    f = fov.forward(x, p, layout="CHW", out_dtype=torch.float32)
+    assert torch.equal(fov.forward(x, p, layout="CHW"), f.round().clamp(0, 255).to(torch.uint8))
